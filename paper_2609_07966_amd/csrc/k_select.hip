@@ -5,6 +5,8 @@
 // observation window votes for (SnapKV), then attends to a top-k subset per decode step.
 // Selections are block-wide radix selects on order-preserving 32-bit keys followed by an
 // ascending-position compaction, so ties resolve by position exactly as specified.
+#include <algorithm>
+
 #include "select_dev.h"
 
 namespace mkv {
@@ -29,17 +31,34 @@ __global__ __launch_bounds__(kTopkThreads, 8) void k_topk(const SeqDesc *__restr
 }
 
 // ---- causal prefill attention statistics for H2O scoring, on the matrix cores ------------------
-// Logit tiles S = Q K^T of 16 query rows x 16 keys come from v_mfma_f32_16x16x32_f16: Q and K are
-// fp16 exactly, products exact, sums in float32.  Operand lane roles (lr = lane % 16, lq = lane /
-// 16): A (16 rows x 32 channels) row lr, channels 8 lq .. 8 lq + 7 of the k-step; B (32 channels x
-// 16 keys) key lr, the same channels; result rows 4 lq + j (j = 0..3), key lr.
-constexpr int TB = 64;
-
+// A kv head's query rows are taken as virtual rows r = position * G + g (its G query heads at one
+// position are adjacent in memory).  Logit tiles S^T = K Q^T of 32 keys x 32 virtual rows come from
+// v_mfma_f32_32x32x16_f16: Q and K are fp16 exactly, products exact, sums in float32.  Operand lane
+// roles (lr = lane % 32, lh = lane / 32): A key lr, B row lr, both channels 8 lh .. 8 lh + 7 of the
+// k-step; result element i: key 8 (i / 4) + 4 lh + i % 4, row lr.  A lane thus owns one row of a
+// tile and 16 of its keys: row statistics stay in the lane, and a row's (max, 1 / sum) is one pair
+// per lane in the column sums.
+//
+// Both kernels hold 64 rows or keys per wave in registers (64 VGPRs at d = 128) and stream 64-item
+// tiles of the other side through a double-buffered LDS stage shared by the 4 waves, so an operand
+// read from LDS feeds two matrix instructions and an item is read from L2 once per 256 on the other
+// side.  Tiles wholly below the diagonal take a path without masks, where a logit costs one fma, one
+// exp2 and one add or fma; with the exp2 at half rate the vector unit bounds both kernels (counters:
+// it is busy 71 % of the row statistics' cycles, the matrix cores 53 %, at a clock of 1.7 GHz under
+// this load).  Heads are the fastest grid index, so that with 8 kv heads each head's K and Q stay in
+// one XCD's L2.  8 prompts of 8192 tokens, 32 query / 8 kv heads x 128: row statistics 4.75 -> 2.31 ms
+// (950 TFLOP/s of causal products), column sums 7.30 -> 2.80 ms (790), where one workgroup per 64
+// rows or keys and launches per sequence stood before; a library matrix product reaches 1150 here.
+// The column sums are held to 168 registers (three waves per SIMD; 2.90 ms at 220 and two).
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
 
 MKV_DEV f4v mfma_k32(const uint4 &a, const uint4 &b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, b), c, 0, 0, 0);
+}
+MKV_DEV f16v mfma32(const uint4 &a, const uint4 &b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, b), c, 0, 0, 0);
 }
 
 // Sum and max over the 16 lanes of a row (lanes with the same lq).
@@ -54,188 +73,260 @@ MKV_DEV float row16_sum(float x) {
   return x;
 }
 
-// Row statistics (max, sum of exp2) of query head gq's causal logits over the prompt keys: a
-// workgroup takes 64 query rows (16 per wave, their Q operands in registers) and walks the
-// 64-key tiles up to the diagonal, each staged once in LDS for the four waves.  Every lane keeps
-// a running (max, sum) for its 4 rows over the keys of its column, merged across the row's 16
-// lanes at the end.
+constexpr int kScoreTile = 64;  // streamed items per LDS stage
+constexpr int kScoreBlock = 4 * kScoreTile;  // resident rows or keys per workgroup
+
+// A streamed tile: kScoreTile rows of D halves, padded by one 16-byte unit so that the 16 lanes of
+// a read phase start in different banks.
 template <int D>
-__global__ __launch_bounds__(NT) void k_h2o_rowstats(const SeqDesc *__restrict__ seqs, int seq,
-                                                     const uint16_t *__restrict__ qrows, int Hq, int G,
+struct ScoreStage {
+  uint4 row[2][kScoreTile][D / 8 + 1];
+};
+
+// Query row of virtual row r (clamped to the prompt) of kv head h, in 16-byte units.
+template <int D>
+MKV_DEV const uint4 *vrow_ptr(const uint16_t *q, const SeqDesc &sd, int r, int h, int Hq, int lg) {
+  const int rc = min(r, (sd.n0 << lg) - 1);
+  return reinterpret_cast<const uint4 *>(
+      q + ((size_t)(sd.q_off + (rc >> lg)) * Hq + (h << lg) + (rc & ((1 << lg) - 1))) * D);
+}
+
+// Row statistics (reference m, 1 / sum of exp2(logit - m)) of every virtual row over its causal
+// keys.  A workgroup takes kScoreBlock virtual rows, the longest first, and walks the key tiles up
+// to the diagonal.  A lane's reference is the largest logit of its row's first tile and moves only
+// when a tile's sum passes 2^80: float32 sums are as precise at any scale, so the tile maximum is
+// not needed otherwise.
+template <int D>
+__global__ __launch_bounds__(NT) void k_h2o_rowstats(const SeqDesc *__restrict__ seqs,
+                                                     const int32_t *__restrict__ list,
+                                                     const uint16_t *__restrict__ q, int Hq, int Hkv, int lg,
                                                      float scale2) {
-  constexpr int KS = D / 32, U = D / 8;  // k-steps; 16-byte units per row
-  __shared__ uint4 sk[TB][U + 1];
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0;
-  const int rb = blockIdx.x, gq = blockIdx.y, h = gq / G, g = gq % G;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
-  const int r0 = rb * TB + 16 * wave;  // this wave's first row
-  uint4 qa[KS];
-  {
-    const uint4 *qp = reinterpret_cast<const uint4 *>(qrows + (size_t)min(r0 + lr, n0 - 1) * Hq * D + (size_t)gq * D);
+  constexpr int KS = D / 16, U = D / 8, PER = kScoreTile * U / NT;
+  constexpr float kMove = 1.2089258196146292e24f;  // 2^80
+  __shared__ ScoreStage<D> L;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv;
+  const int rb = ((n0 << lg) + kScoreBlock - 1) / kScoreBlock - 1 - (int)blockIdx.x / Hkv;
+  if (rb < 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
+  const int r0 = rb * kScoreBlock + 64 * wave;  // this wave's first virtual row
+  const int p0 = min(r0 >> lg, n0 - 1), p1 = min((r0 + 63) >> lg, n0 - 1);
+  uint4 qa[2][KS];
+  int pos[2];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qa[s] = gld16(qp + 4 * s + lq);
+  for (int t = 0; t < 2; ++t) {
+    const uint4 *qp = vrow_ptr<D>(q, sd, r0 + 32 * t + lr, h, Hq, lg);
+    pos[t] = min((r0 + 32 * t + lr) >> lg, n0 - 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qa[t][s] = gld16(qp + 2 * s + lh);
   }
   const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
                                                     h * stride_stage(sd, D));
-  float m[4], l[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    m[j] = -INFINITY;
-    l[j] = 0.f;
-  }
-  // the next tile's loads are in flight while the current one is computed
-  constexpr int PER = TB * U / NT;  // 16-byte units per thread and tile
+  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
+  const int last = min((rb * kScoreBlock + kScoreBlock - 1) >> lg, n0 - 1) / kScoreTile;
   uint4 nxt[PER];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + k * NT, r = e / U, u = e % U;
-    nxt[k] = gld16(ks + (size_t)min(r, n0 - 1) * U + u);
-  }
-  for (int kb = 0; kb <= rb; ++kb) {
-    __syncthreads();
+  auto load = [&](int kb) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = threadIdx.x + k * NT;
-      sk[e / U][e % U] = nxt[k];
-    }
-    __syncthreads();
-    if (kb < rb) {
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        const int e = threadIdx.x + k * NT, r = e / U, u = e % U;
-        nxt[k] = gld16(ks + (size_t)min((kb + 1) * TB + r, n0 - 1) * U + u);
-      }
-    }
-    if (kb * TB > r0 + 15) continue;  // the tile lies wholly above this wave's rows
-    float v[4][4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      f4v S = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < KS; ++s) S = mfma_k32(qa[s], sk[16 * n + lr][4 * s + lq], S);
-      const int key = kb * TB + 16 * n + lr;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[n][j] = (key <= r0 + 4 * lq + j && key < n0) ? S[j] * scale2 : -INFINITY;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float mx = fmaxf(fmaxf(m[j], fmaxf(v[0][j], v[1][j])), fmaxf(v[2][j], v[3][j]));
-      if (mx == -INFINITY) continue;
-      float acc = l[j] * fexp2(m[j] - mx);
-#pragma unroll
-      for (int n = 0; n < 4; ++n) acc += fexp2(v[n][j] - mx);
-      l[j] = acc;
-      m[j] = mx;
-    }
-  }
-  float2 *out = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * G * n0 + (size_t)g * n0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float M = row16_max(m[j]);
-    const float L = row16_sum(m[j] == -INFINITY ? 0.f : l[j] * fexp2(m[j] - M));
-    const int i = r0 + 4 * lq + j;
-    if (lr == 0 && i < n0) out[i] = make_float2(M, L);
-  }
-}
-
-// Column sums S_j = sum_g sum_{i >= j} p_gij over a block of 64 keys: every wave holds the
-// block's K operands in registers and takes every fourth 16-row chunk of the rows at or below
-// the block, for each of the kv head's query heads; the waves' sums meet in LDS.
-template <int D>
-__global__ __launch_bounds__(NT) void k_h2o_colsums(const SeqDesc *__restrict__ seqs, int seq,
-                                                    const uint16_t *__restrict__ qrows, int Hq, int G,
-                                                    float scale2) {
-  constexpr int KS = D / 32, U = D / 8;
-  __shared__ float scol[NT / 64][TB];
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0;
-  const int kb = blockIdx.x, h = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
-  const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
-                                                    h * stride_stage(sd, D));
-  uint4 kop[4][KS];
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kop[n][s] = gld16(ks + (size_t)min(kb * TB + 16 * n + lr, n0 - 1) * U + 4 * s + lq);
-  const float2 *stat = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * G * n0;
-  float col[4] = {0.f, 0.f, 0.f, 0.f};
-  const int nchunk = (n0 + 15) / 16;
-  // (query head, 16-row chunk) items of this wave in order, the next item's loads in flight while
-  // the current one is computed
-  const int c0 = kb * (TB / 16) + wave, per_g = c0 < nchunk ? (nchunk - c0 + NT / 64 - 1) / (NT / 64) : 0;
-  const int items = G * per_g;
-  auto load = [&](int it, uint4 (&qa)[KS], float (&M)[4], float (&iL)[4]) {
-    const int g = it / per_g, c = c0 + (it % per_g) * (NT / 64);
-    const uint4 *qp = reinterpret_cast<const uint4 *>(qrows + (size_t)min(16 * c + lr, n0 - 1) * Hq * D +
-                                                      (size_t)(h * G + g) * D);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) qa[s] = gld16(qp + 4 * s + lq);
-    const float2 *sg = stat + (size_t)g * n0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float *ml = reinterpret_cast<const float *>(sg + min(16 * c + 4 * lq + j, n0 - 1));
-      M[j] = gld(ml);
-      iL[j] = gld(ml + 1);
+      nxt[k] = gld16(ks + (size_t)min(kb * kScoreTile + e / U, n0 - 1) * U + e % U);
     }
   };
-  uint4 qn[KS];
-  float Mn[4], Ln[4];
-  if (items > 0) load(0, qn, Mn, Ln);
-  for (int it = 0; it < items; ++it) {
-    const int c = c0 + (it % per_g) * (NT / 64);
-    uint4 qa[KS];
-    float M[4], iL[4];
+  load(0);
+  for (int kb = 0; kb <= last; ++kb) {
+    // one barrier per tile: a stage is rewritten two tiles later, after every wave has passed the
+    // barrier between
+    auto &st = L.row[kb & 1];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qa[s] = qn[s];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      M[j] = Mn[j];
-      iL[j] = 1.f / Ln[j];
+    for (int k = 0; k < PER; ++k) {
+      const int e = threadIdx.x + k * NT;
+      st[e / U][e % U] = nxt[k];
     }
-    if (it + 1 < items) load(it + 1, qn, Mn, Ln);
-    {
+    __syncthreads();
+    if (kb < last) load(kb + 1);
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        f4v S = {0.f, 0.f, 0.f, 0.f};
+    for (int sub = 0; sub < 2; ++sub) {
+      const int key0 = kb * kScoreTile + 32 * sub;
+      if (key0 > p1) break;
+      f16v S[2] = {};
 #pragma unroll
-        for (int s = 0; s < KS; ++s) S = mfma_k32(qa[s], kop[n][s], S);
-        const int key = kb * TB + 16 * n + lr;
+      for (int s = 0; s < KS; ++s) {
+        const uint4 a = st[32 * sub + lr][2 * s + lh];
+        S[0] = mfma32(a, qa[0][s], S[0]);
+        S[1] = mfma32(a, qa[1][s], S[1]);
+      }
+      bool open = key0 + 31 <= p0 && key0 > 0;  // no mask, and every lane has a reference
+      if (open) {
+        float t[2][2] = {};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int i = 16 * c + 4 * lq + j;
-          // arguments <= 0 wherever the row statistics hold this logit
-          col[n] += (i < n0 && key <= i && key < n0) ? fexp2(S[j] * scale2 - M[j]) * iL[j] : 0.f;
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) t[u][i & 1] += fexp2(fmaf(S[u][i], scale2, -m[u]));
+        t[0][0] += t[0][1];
+        t[1][0] += t[1][1];
+        open = !__any(!(t[0][0] < kMove && t[1][0] < kMove));
+        if (open) {
+          l[0] += t[0][0];
+          l[1] += t[1][0];
+        }
+      }
+      if (!open) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int rel = pos[u] - key0 - 4 * lh;  // compared with constants
+          float mx = m[u];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) mx = fmaxf(mx, 8 * (i / 4) + (i & 3) <= rel ? S[u][i] * scale2 : -INFINITY);
+          if (mx == -INFINITY) continue;  // every key so far is masked
+          l[u] *= fexp2(m[u] - mx);
+          m[u] = mx;
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            l[u] += 8 * (i / 4) + (i & 3) <= rel ? fexp2(fmaf(S[u][i], scale2, -mx)) : 0.f;
         }
       }
     }
   }
+  float2 *out = reinterpret_cast<float2 *>(sd.aux1) + ((size_t)h * n0 << lg);
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    float x = col[n];
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
-    if (lq == 0) scol[wave][16 * n + lr] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x < TB) {
-    float acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) acc += scol[w][threadIdx.x];
-    const int jj = kb * TB + threadIdx.x;
-    if (jj < n0) (reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0)[jj] = acc;
+  for (int u = 0; u < 2; ++u) {
+    // the two halves of a wave hold disjoint keys of the row (a half without keys: m = -inf, l = 0)
+    const float mo = __shfl_xor(m[u], 32), lo = __shfl_xor(l[u], 32);
+    const float M = fmaxf(m[u], mo);
+    const float sum = (m[u] == -INFINITY ? 0.f : l[u] * fexp2(m[u] - M)) + (mo == -INFINITY ? 0.f : lo * fexp2(mo - M));
+    const int r = r0 + 32 * u + lr;
+    if (lh == 0 && r < (n0 << lg)) out[r] = make_float2(M, 1.f / sum);
   }
 }
 
-// Keep the R most recent prompt tokens plus the top B - R scores of the rest (newer on ties),
-// gathered into slots 0..kept-1 in ascending position order.  The selection runs over the
-// candidates in reverse order (index ncand - 1 - j), so that its lower-index tie rule prefers
-// newer tokens; its ascending output, reversed, is ascending in position.
+// Column sums S_j = sum_r p_rj of kScoreBlock keys over one segment of the virtual rows (those at or
+// below the diagonal), into that segment's row of the partial sums; k_h2o_sum adds the segments in
+// order.  Splitting the rows into up to kScoreSegs segments gives one prompt enough workgroups of
+// similar length (a block of keys would otherwise carry up to all rows), and the workgroups in
+// flight of one segment share its query rows in L2.
 template <int D>
-__global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__restrict__ seqs, int seq, int32_t *state,
+__global__ __launch_bounds__(NT, 3) void k_h2o_colsums(const SeqDesc *__restrict__ seqs,
+                                                    const int32_t *__restrict__ list,
+                                                    const uint16_t *__restrict__ q, int Hq, int Hkv, int lg,
+                                                    float scale2) {
+  constexpr int KS = D / 16, U = D / 8, PER = kScoreTile * U / NT;
+  __shared__ ScoreStage<D> L;
+  __shared__ float2 s_stat[2][kScoreTile];  // (reference, 1 / sum) of the streamed rows
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, V = n0 << lg;
+  const int nkb = (n0 + kScoreBlock - 1) / kScoreBlock, item = (int)blockIdx.x / Hkv;
+  const int seg = sd.nseg - 1 - item / nkb, kb = item % nkb;
+  const int v0 = max(seg * sd.seg_rows, (kb * kScoreBlock) << lg), v1 = min((seg + 1) * sd.seg_rows, V);
+  if (seg < 0 || v0 >= v1) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
+  const int key0 = kb * kScoreBlock + 64 * wave;
+  const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
+                                                    h * stride_stage(sd, D));
+  const float *stat = reinterpret_cast<const float *>(sd.aux1) + 2 * ((size_t)h * n0 << lg);
+  uint4 ka[2][KS];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) ka[u][s] = gld16(ks + (size_t)min(key0 + 32 * u + lr, n0 - 1) * U + 2 * s + lh);
+  float acc[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) acc[i] = 0.f;
+  // v0 is a multiple of kScoreTile (segments and key blocks are)
+  // (a tile starts at a whole position: its rows' offsets from there are the same for every tile, up
+  // to the clamp to the prompt, so addresses are a uniform base plus a 32-bit offset)
+  uint4 nxt[PER];
+  float Mn = 0.f, In = 0.f;  // the next tile's statistics: thread t < kScoreTile takes row t
+  const uint32_t pitch = (uint32_t)Hq * D * 2;
+  auto load = [&](int v) {
+    const char *qt = reinterpret_cast<const char *>(q + ((size_t)(sd.q_off + (v >> lg)) * Hq + ((size_t)h << lg)) * D);
+    const char *ml = reinterpret_cast<const char *>(stat + 2 * (size_t)v);
+    const int end = V - 1 - v;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int r = min((int)(threadIdx.x / U) + k * (NT / U), end);
+      nxt[k] = gld16(qt + ((uint32_t)(r >> lg) * pitch + (uint32_t)(r & ((1 << lg) - 1)) * (D * 2) + (threadIdx.x % U) * 16));
+    }
+    if (threadIdx.x < kScoreTile) {
+      const float *p = reinterpret_cast<const float *>(ml + (uint32_t)min((int)threadIdx.x, end) * 8);
+      Mn = gld(p);
+      const float x = gld(p + 1);
+      In = (int)threadIdx.x <= end ? x : 0.f;  // rows past the prompt add nothing
+    }
+  };
+  load(v0);
+  int buf = 0;
+  for (int v = v0; v < v1; v += kScoreTile, buf ^= 1) {
+    auto &st = L.row[buf];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int e = threadIdx.x + k * NT;
+      st[e / U][e % U] = nxt[k];
+    }
+    if (threadIdx.x < kScoreTile) s_stat[buf][threadIdx.x] = make_float2(Mn, In);
+    __syncthreads();
+    if (v + kScoreTile < v1) load(v + kScoreTile);
+#pragma unroll 1
+    for (int t = 0; t < 2; ++t) {
+      const int r = v + 32 * t;
+      if (key0 > (r + 31) >> lg) continue;  // wholly above the diagonal
+      const float2 mi = s_stat[buf][32 * t + lr];
+      f16v S[2] = {};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const uint4 b = st[32 * t + lr][2 * s + lh];
+        S[0] = mfma32(ka[0][s], b, S[0]);
+        S[1] = mfma32(ka[1][s], b, S[1]);
+      }
+      if (key0 + 63 <= r >> lg) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) acc[i] = fmaf(fexp2(fmaf(S[i / 16][i % 16], scale2, -mi.x)), mi.y, acc[i]);
+      } else {
+        const int rel = ((r + lr) >> lg) - key0 - 4 * lh;  // compared with constants
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+          const float p = fexp2(fmaf(S[i / 16][i % 16], scale2, -mi.x)) * mi.y;
+          acc[i] += 8 * (i / 4) + (i & 3) <= rel ? p : 0.f;
+        }
+      }
+    }
+  }
+  // sum over the 32 lanes of a half: at step o the lanes with bit o clear keep the even values of
+  // each pair and the others the odd ones, so lane lr ends with the total of value lr
+#pragma unroll
+  for (int o = 1, n = 32; o < 32; o <<= 1, n >>= 1) {
+    const bool odd = lane & o;
+#pragma unroll
+    for (int i = 0; i < n / 2; ++i) {
+      const float keep = odd ? acc[2 * i + 1] : acc[2 * i], send = odd ? acc[2 * i] : acc[2 * i + 1];
+      acc[i] = keep + __shfl_xor(send, o);
+    }
+  }
+  const int key = key0 + 32 * (lr / 16) + 8 * ((lr / 4) & 3) + 4 * lh + (lr & 3);
+  if (key < n0) gst(reinterpret_cast<float *>(sd.colpart) + ((size_t)h * sd.nseg + seg) * n0 + key, acc[0]);
+}
+
+// Scores: the segments' column sums added in ascending order (a key's first segment is the one its
+// block's diagonal lies in).
+__global__ __launch_bounds__(NT) void k_h2o_sum(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                int Hkv, int lg) {
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, j = (int)blockIdx.x / Hkv * NT + (int)threadIdx.x;
+  if (j >= n0) return;
+  const float *part = reinterpret_cast<const float *>(sd.colpart) + (size_t)h * sd.nseg * n0 + j;
+  float acc = 0.f;
+  for (int s = (j / kScoreBlock * kScoreBlock << lg) / sd.seg_rows; s < sd.nseg; ++s) acc += gld(part + (size_t)s * n0);
+  gst(reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0 + j, acc);
+}
+
+// Keep the R most recent prompt tokens plus the top B - R scores of the rest (newer on ties): their
+// positions into slots 0..kept-1 in ascending order, and the head's state.  The selection runs over
+// the candidates in reverse order (index ncand - 1 - j), so that its lower-index tie rule prefers
+// newer tokens; its ascending output, reversed, is ascending in position.
+__global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__restrict__ seqs,
+                                                           const int32_t *__restrict__ list, int32_t *state,
                                                            int Hkv) {
   __shared__ SelLds L;
+  const int seq = list[blockIdx.y];
   const SeqDesc &sd = seqs[seq];
   const int h = blockIdx.x, n0 = sd.n0;
   const float *S = reinterpret_cast<const float *>(sd.aux0) + (size_t)h * n0;
@@ -257,19 +348,6 @@ __global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__rest
     }
     for (int i = threadIdx.x; i < R; i += kTopkThreads) pos[H + i] = ncand + i;
   }
-  __syncthreads();
-  const uint16_t *sk = reinterpret_cast<const uint16_t *>(sd.stage_k) + h * stride_stage(sd, D);
-  const uint16_t *sv = reinterpret_cast<const uint16_t *>(sd.stage_v) + h * stride_stage(sd, D);
-  uint16_t *dk = reinterpret_cast<uint16_t *>(sd.k) + h * stride_rows(sd, D);
-  uint16_t *dvv = reinterpret_cast<uint16_t *>(sd.v) + h * stride_rows(sd, D);
-  float *score = reinterpret_cast<float *>(sd.score) + h * stride_slots(sd);
-  for (int it = threadIdx.x; it < kept * (D / 8); it += kTopkThreads) {
-    const int slot = it / (D / 8), u = it % (D / 8);
-    const int j = gld(pos + slot);
-    *reinterpret_cast<uint4 *>(dk + (size_t)slot * D + 8 * u) = gld16(sk + (size_t)j * D + 8 * u);
-    *reinterpret_cast<uint4 *>(dvv + (size_t)slot * D + 8 * u) = gld16(sv + (size_t)j * D + 8 * u);
-    if (u == 0) score[slot] = gld(S + j);
-  }
   // no eviction candidates before the first attention pass
   uint32_t *vb = reinterpret_cast<uint32_t *>(sd.vbest) + (size_t)h * sd.vparts * 4;
   for (int p = threadIdx.x; p < sd.vparts; p += kTopkThreads) {
@@ -283,6 +361,45 @@ __global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__rest
     st[ST_COUNT] = kept;
     st[ST_FREE_SLOT] = kept;
     st[ST_KEPT] = kept;
+  }
+}
+
+// The kept rows and their scores, gathered from the staged prompt: a workgroup per kGatherSlots
+// slots (selection and gather of 8 x 8192 prompts: 490 us with the gather in the selecting workgroup,
+// one per kv head, and launches per sequence; 38 us apart and over all sequences).
+constexpr int kGatherSlots = 64;
+template <int D>
+__global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                   int Hkv) {
+  constexpr int U = D / 8, PER = kGatherSlots * U / NT;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int h = blockIdx.x % Hkv, s0 = (int)blockIdx.x / Hkv * kGatherSlots, n0 = sd.n0;
+  const int kept = sd.B >= n0 ? n0 : min(sd.B, sd.cap);
+  if (s0 >= kept) return;
+  const int32_t *pos = reinterpret_cast<const int32_t *>(sd.pos) + h * stride_slots(sd);
+  const uint16_t *sk = reinterpret_cast<const uint16_t *>(sd.stage_k) + h * stride_stage(sd, D);
+  const uint16_t *sv = reinterpret_cast<const uint16_t *>(sd.stage_v) + h * stride_stage(sd, D);
+  uint16_t *dk = reinterpret_cast<uint16_t *>(sd.k) + h * stride_rows(sd, D);
+  uint16_t *dvv = reinterpret_cast<uint16_t *>(sd.v) + h * stride_rows(sd, D);
+  int jj[PER];
+  uint4 a[PER], b[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) jj[k] = gld(pos + min(s0 + (int)(threadIdx.x + k * NT) / U, kept - 1));
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int u = threadIdx.x % U;
+    a[k] = gld16(sk + (size_t)jj[k] * D + 8 * u);
+    b[k] = gld16(sv + (size_t)jj[k] * D + 8 * u);
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int slot = s0 + (int)(threadIdx.x + k * NT) / U, u = threadIdx.x % U;
+    if (slot >= kept) break;
+    *reinterpret_cast<uint4 *>(dk + (size_t)slot * D + 8 * u) = a[k];
+    *reinterpret_cast<uint4 *>(dvv + (size_t)slot * D + 8 * u) = b[k];
+    if (u == 0)
+      (reinterpret_cast<float *>(sd.score) + h * stride_slots(sd))[slot] =
+          gld(reinterpret_cast<const float *>(sd.aux0) + (size_t)h * n0 + jj[k]);
   }
 }
 
@@ -540,15 +657,27 @@ hipError_t topk_impl(const Dev &dv, const Shape &sh, const uint16_t *q, int32_t 
 }
 
 template <int D>
-hipError_t h2o_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq, const uint16_t *q,
-                            hipStream_t st) {
+hipError_t h2o_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *q, hipStream_t st) {
   const float scale2 = kLog2e / sqrtf((float)D);
-  const int nb = (hs.n0 + TB - 1) / TB;
-  // one query head per workgroup: sharing a staged key tile among several heads of a kv head was
-  // measured slower (fewer, longer workgroups at lower occupancy)
-  hipLaunchKernelGGL(k_h2o_rowstats<D>, dim3(nb, sh.Hq), dim3(NT), 0, st, dv.seqs, seq, q, sh.Hq, sh.G, scale2);
-  hipLaunchKernelGGL(k_h2o_colsums<D>, dim3(nb, sh.Hkv), dim3(NT), 0, st, dv.seqs, seq, q, sh.Hq, sh.G, scale2);
-  hipLaunchKernelGGL(k_h2o_keep<D>, dim3(sh.Hkv), dim3(kTopkThreads), 0, st, dv.seqs, seq, dv.state, sh.Hkv);
+  const MethodSeqs &ms = dv.of[H2O];
+  const int lg = __builtin_ctz((unsigned)sh.G);
+  // grid x: kv heads (fastest) x the longest prompt's blocks; workgroups past a shorter prompt's end
+  // leave at once
+  const unsigned vblocks = (unsigned)((((int64_t)longest.n0 << lg) + kScoreBlock - 1) / kScoreBlock);
+  const unsigned kblocks = (longest.n0 + kScoreBlock - 1) / kScoreBlock, H = sh.Hkv;
+  for (int a = 0; a < ms.n; a += kMaxGridY) {
+    const unsigned n = std::min(ms.n - a, kMaxGridY);
+    const int32_t *list = ms.list + a;
+    hipLaunchKernelGGL(k_h2o_rowstats<D>, dim3(H * vblocks, n), dim3(NT), 0, st, dv.seqs, list, q, sh.Hq, sh.Hkv, lg,
+                       scale2);
+    hipLaunchKernelGGL(k_h2o_colsums<D>, dim3(H * kblocks * kScoreSegs, n), dim3(NT), 0, st, dv.seqs, list, q, sh.Hq,
+                       sh.Hkv, lg, scale2);
+    hipLaunchKernelGGL(k_h2o_sum, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list, sh.Hkv,
+                       lg);
+    hipLaunchKernelGGL(k_h2o_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, list, dv.state, sh.Hkv);
+    hipLaunchKernelGGL(k_h2o_gather<D>, dim3(H * ((ms.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0,
+                       st, dv.seqs, list, sh.Hkv);
+  }
   return hipGetLastError();
 }
 
@@ -587,10 +716,9 @@ hipError_t launch_topk(const Dev &dv, const Shape &sh, const uint16_t *q, int32_
   }
 }
 
-hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
-                                  const uint16_t *q_rows, hipStream_t st) {
-  return sh.D == 64 ? h2o_prefill_impl<64>(dv, sh, hs, seq, q_rows, st)
-                    : h2o_prefill_impl<128>(dv, sh, hs, seq, q_rows, st);
+hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *q_rows,
+                                  hipStream_t st) {
+  return sh.D == 64 ? h2o_prefill_impl<64>(dv, sh, hs, q_rows, st) : h2o_prefill_impl<128>(dv, sh, hs, q_rows, st);
 }
 
 hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,

@@ -49,12 +49,14 @@ constexpr int kProfKinds = 5;
 struct Layout {
   std::vector<SeqDesc> seqs;  // offsets (relative to the arena) in the pointer fields
   size_t off_seqs = 0, off_state = 0, off_tiles = 0, off_cbtab = 0, off_partials = 0, total = 0;
-  size_t off_prep = 0, off_rk_pairs = 0, off_comb = 0;
+  size_t off_prep = 0, off_rk_pairs = 0, off_comb = 0, off_lists = 0;
   int n_tiles = 0, n_tiles_uq = 0, n_tiles_rk = 0;
   std::vector<int4> tiles;
   std::vector<int4> prep;      // decode-step append / scoring work list
   std::vector<int2> rk_pairs;  // RocketKV (seq, kv head) pairs
   std::vector<int4> comb;      // combine work list
+  std::vector<int32_t> lists;  // sequences grouped by method, longest prompt first
+  MethodSeqs of[kMethods];     // `list` not set (the place in `lists` follows from the counts)
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -65,7 +67,7 @@ constexpr uint64_t SeqDesc::*kRegionFields[] = {
     &SeqDesc::k,      &SeqDesc::v,      &SeqDesc::kc,      &SeqDesc::vc,      &SeqDesc::kmeta, &SeqDesc::vmeta,
     &SeqDesc::kres,   &SeqDesc::krow,   &SeqDesc::kout,    &SeqDesc::vout,    &SeqDesc::vdel,  &SeqDesc::pos,
     &SeqDesc::score,  &SeqDesc::logits, &SeqDesc::vbest,   &SeqDesc::stage_k, &SeqDesc::stage_v,
-    &SeqDesc::kcm,    &SeqDesc::sel,    &SeqDesc::akeys,   &SeqDesc::aux0,    &SeqDesc::aux1};
+    &SeqDesc::kcm,    &SeqDesc::sel,    &SeqDesc::akeys,   &SeqDesc::aux0,    &SeqDesc::aux1,  &SeqDesc::colpart};
 static_assert(offsetof(SeqDesc, k) + sizeof(kRegionFields) / sizeof(kRegionFields[0]) * sizeof(uint64_t) ==
                   sizeof(SeqDesc),
               "every region pointer of SeqDesc is relocated");
@@ -227,6 +229,13 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
         d.stage_v = take(H * n0 * D * 2);
         d.aux0 = take(H * n0 * 4);
         d.aux1 = take(H * G * n0 * 8);
+        {
+          // row segments of the column sums: whole streamed tiles, at least 512 virtual rows each
+          const long long rows = (long long)n0 * G;
+          d.seg_rows = (int)std::max<long long>(512, ((rows + kScoreSegs - 1) / kScoreSegs + 255) / 256 * 256);
+          d.nseg = (int)((rows + d.seg_rows - 1) / d.seg_rows);
+          d.colpart = take(H * d.nseg * n0 * 4);
+        }
         d.q_off = q_h2o;
         q_h2o += n0;
         break;
@@ -381,6 +390,22 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     }
   L->off_comb = take(sizeof(int4) * L->comb.size());
   L->off_rk_pairs = take(sizeof(int2) * std::max<size_t>(1, L->rk_pairs.size()));
+  L->lists.clear();
+  for (int m = 0; m < kMethods; ++m) {
+    MethodSeqs &ms = L->of[m];
+    ms = MethodSeqs{};
+    for (int s = 0; s < S; ++s) {
+      const SeqDesc &d = L->seqs[s];
+      if (d.method != m) continue;
+      L->lists.push_back(s);
+      ++ms.n;
+      ms.max_kept = std::max(ms.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
+    }
+    std::stable_sort(L->lists.end() - ms.n, L->lists.end(),
+                     [&](int32_t a, int32_t b) { return L->seqs[a].n0 > L->seqs[b].n0; });
+    if (ms.n > 0) ms.longest = L->lists[L->lists.size() - ms.n];
+  }
+  L->off_lists = take(sizeof(int32_t) * L->lists.size());
   L->off_partials = take(sizeof(float) * (size_t)L->n_tiles * G * (D + 2));
   L->total = off;
   return MKV_OK;
@@ -556,6 +581,12 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
   c->dv.n_rk_pairs = (int)L.rk_pairs.size();
   c->dv.n_tiles_uq = L.n_tiles_uq;
   c->dv.n_tiles_rk = L.n_tiles_rk;
+  const int32_t *list = reinterpret_cast<const int32_t *>(c->arena + L.off_lists);
+  for (int m = 0; m < kMethods; ++m) {
+    c->dv.of[m] = L.of[m];
+    c->dv.of[m].list = list;
+    list += L.of[m].n;
+  }
   hipStream_t hst = static_cast<hipStream_t>(stream);
   hipError_t e = hipMemcpyAsync(c->arena + L.off_seqs, c->hs.data(), sizeof(SeqDesc) * c->hs.size(),
                                 hipMemcpyHostToDevice, hst);
@@ -569,6 +600,9 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
   if (e == hipSuccess && !L.rk_pairs.empty())
     e = hipMemcpyAsync(c->arena + L.off_rk_pairs, L.rk_pairs.data(), sizeof(int2) * L.rk_pairs.size(),
                        hipMemcpyHostToDevice, hst);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(c->arena + L.off_lists, L.lists.data(), sizeof(int32_t) * L.lists.size(), hipMemcpyHostToDevice,
+                       hst);
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->arena + L.off_cbtab, table, sizeof table, hipMemcpyHostToDevice, hst);
   if (e == hipSuccess) e = launch_init_state(c->dv, c->sh, hst);
@@ -652,10 +686,9 @@ mkv_status mkv_h2o_update_evict(mkv_cache *c, const uint16_t *q_prompt, void *st
   if (q_prompt != nullptr) {
     if (c->phase != PH_PROMPT || c->h2o_done)
       return fail(MKV_ESTATE, "H2O prefill scoring runs once, after the prefill append");
-    const size_t row = (size_t)c->sh.Hq * c->sh.D;
-    for (int s = 0; s < c->sh.S; ++s) {
-      if (c->hs[s].method != H2O) continue;
-      hipError_t e = launch_h2o_prefill_seq(c->dv, c->sh, c->hs[s], s, q_prompt + (size_t)c->hs[s].q_off * row, hst);
+    if (c->any_h2o) {
+      const int longest = c->dv.of[H2O].longest;
+      hipError_t e = launch_h2o_prefill_seq(c->dv, c->sh, c->hs[longest], longest, q_prompt, hst);
       if (e != hipSuccess) return hip_fail(e, "H2O prefill");
     }
     c->h2o_done = true;

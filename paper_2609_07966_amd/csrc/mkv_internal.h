@@ -17,6 +17,7 @@ namespace mkv {
 mkv_status report_error(mkv_status s, const char *msg);
 
 enum Method : int32_t { FP16 = 0, UQ = 1, KVQ = 2, H2O = 3, ROCKET = 4 };
+constexpr int kMethods = 5;
 
 // Per-(sequence, kv head) device state words.
 enum StateWord : int32_t {
@@ -52,7 +53,8 @@ struct SeqDesc {
   int32_t pool_cap, nblk, w_eff, chunk;   // KVQ outlier pool; UQ blocks; window rows; tile tokens
   int32_t tile_first, tile_count, q_off, cstride;  // partial tiles (per kv head); prompt-q row offset;
                                                    // ROCKET channel-major row stride (cap rounded to 8)
-  int32_t vparts, spare0, spare1, spare2;  // H2O: eviction candidates per kv head (one per combine part)
+  int32_t vparts, nseg, seg_rows, spare0;  // H2O: eviction candidates per kv head (one per combine part);
+                                           // prefill scoring: row segments and virtual rows of each
   uint64_t k, v;            // fp16 [cap][d] rows (FP16 / H2O / ROCKET)
   uint64_t kc, vc;          // packed codes [cap][rowbytes] (UQ / KVQ)
   uint64_t kmeta, vmeta;    // UQ: float2 [nblk][d], float2 [cap][d/64]; KVQ: float2 tau/inv [d], float [cap]
@@ -68,6 +70,7 @@ struct SeqDesc {
   uint64_t sel, akeys;      // ROCKET: int32 [topk] selected slots; u32 [cap] score keys
   uint64_t aux0, aux1;      // prefill scratch: H2O float [n0] scores, float2 [G][n0] row stats;
                             // ROCKET float [n0] votes, float2 [G*w][nchunk] partial row stats
+  uint64_t colpart;         // H2O prefill scratch: float [nseg][n0] column sums per row segment
 };
 
 struct Shape {
@@ -138,6 +141,18 @@ constexpr int kScoreTokensPerPart = 1024;
 // H2O slots one combine workgroup scores (an H2O kv head has ceil(cap / kCombineSlots) parts).
 constexpr int kCombineSlots = 2048;
 
+// H2O prefill scoring: a prompt's query rows are summed over in at most this many segments.
+constexpr int kScoreSegs = 8;
+// Sequences of one launch over a method's sequences (the grid's y extent).
+constexpr int kMaxGridY = 32768;
+
+// The sequences of one method, longest prompt first, and the most tokens one of them keeps after
+// prefill.
+struct MethodSeqs {
+  const int32_t *list = nullptr;  // device
+  int n = 0, longest = -1, max_kept = 0;
+};
+
 // Kernel launchers (defined in the .hip files).  All enqueue on `st`.
 struct Dev {
   const SeqDesc *seqs;   // device [S]
@@ -153,6 +168,7 @@ struct Dev {
   const int2 *rk_pairs;  // device [n_rk_pairs]: the RocketKV (seq, kv head) pairs
   const int4 *comb;      // device [n_comb]: combine work (seq, kv head, part, parts)
   int n_prep, n_rk_pairs, n_comb;
+  MethodSeqs of[kMethods];
 };
 
 // Optional timing events of one launch: when set, they record the kernel's own start and end
@@ -185,6 +201,8 @@ hipError_t launch_topk(const Dev &dv, const Shape &sh, const uint16_t *q, int32_
 // launch_append_decode followed by launch_topk without positions.
 hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                                 const uint16_t *q, hipStream_t st, LaunchEv ev_score = {}, LaunchEv ev_select = {});
+// Scoring and keep-set of every H2O sequence, one launch per stage; hs, seq: the one with the longest
+// prompt; q_rows: the prompt queries of all of them, in sequence order.
 hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
                                   const uint16_t *q_rows, hipStream_t st);
 hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
