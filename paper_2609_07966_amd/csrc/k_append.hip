@@ -5,6 +5,8 @@
 // per-channel key thresholds calibrated on the prompt and fp16 outliers.  The quantizer steps are
 // written with explicit round-to-nearest float32 operations (__fmul_rn, __fsub_rn, __fdiv_rn)
 // so that codes are reproducible bit for bit.
+#include <algorithm>
+
 #include "select_dev.h"
 
 namespace mkv {
@@ -537,145 +539,393 @@ __global__ __launch_bounds__(128) void k_prefill_uq_keys(const SeqDesc *__restri
   }
 }
 
+// ---- KVQ prompts: every KVQ sequence in one launch per stage ------------------------------------
+// Grid: x = kv head (fastest) x blocks of the longest prompt, y = sequence (longest first);
+// workgroups past a shorter prompt's end leave at once.  Lanes take 8 consecutive channels of a token
+// (one 16-byte load), LT = D / 8 lanes a token, so that reductions over a token's channels are 3 or 4
+// DPP steps for 4 or 8 tokens at once and codes pack within a lane.  8 prompts of 3000-6000 tokens
+// (8 kv heads x 128), where launches per sequence, one workgroup per token (keys) or 4-token block
+// (values) and 16 workgroups per calibration stood before: thresholds 1176 -> 58 us, key codes and
+// outliers 364 -> 54, values 201 -> 57, scan 72 -> 5.  Reading K or V once takes 15 us here; the
+// codes' compares bound the quantizing kernels, LDS atomics and load latency the calibration.
+
+constexpr int kKvqThreads = 256;
+constexpr int kKvqTokens = 64;  // tokens per workgroup of the quantizing kernels
+
+template <int LT, typename Op>
+MKV_DEV float lane_group_reduce(float x, Op op) {  // over aligned groups of LT (8 or 16) lanes
+  x = op(x, dpp<0xB1>(x));
+  x = op(x, dpp<0x4E>(x));
+  x = op(x, dpp<0x141>(x));
+  if constexpr (LT == 16) x = op(x, dpp<0x140>(x));
+  return x;
+}
+template <int LT>
+MKV_DEV int lane_group_sum(int x) {
+  auto step = [](int v, auto ctrl) { return __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xF, 0xF, false); };
+  x += step(x, std::integral_constant<int, 0xB1>{});
+  x += step(x, std::integral_constant<int, 0x4E>{});
+  x += step(x, std::integral_constant<int, 0x141>{});
+  if constexpr (LT == 16) x += step(x, std::integral_constant<int, 0x140>{});
+  return x;
+}
+// Sum of x over the lower lanes of the group.
+template <int LT>
+MKV_DEV int lane_group_before(int x) {
+  int inc = x;
+#pragma unroll
+  for (int o = 1; o < LT; o <<= 1) {
+    const int y = __shfl_up(inc, o, LT);
+    inc += (int)(threadIdx.x % LT) >= o ? y : 0;
+  }
+  return inc - x;
+}
+
 // KVQ key thresholds: the n_o-th largest |k| (0-based) of every channel over the prompt, by a
-// two-pass radix select on the 15-bit fp16 magnitude.  A workgroup takes 64 channels of one kv
-// head: lane l of every wave owns channel c0 + l (one coalesced 128-byte load per token), the 8
-// waves take every eighth token, kCalibBatch tokens' loads in flight at a time, and count into
-// one 256-bin histogram per channel by LDS atomics (rows padded so that the lanes' bins spread
-// over the banks); thread c < 64 then finds its channel's digit.
+// two-pass radix select on the 15-bit fp16 magnitude.  A workgroup takes 32 channels of one kv head;
+// its waves read 16 tokens per load, kCalibBatch loads in flight, and count into one 256-bin
+// histogram per channel by LDS atomics (in the second pass only keys of the selected digit count);
+// then a wave per channel finds its digit by a scan.  32 channels instead of 64 per workgroup give
+// 256 of them on 8 sequences.
 constexpr int kCalibThreads = 512;
-constexpr int kCalibBatch = 16;
+constexpr int kCalibBatch = 8;
+constexpr int kCalibChannels = 32;
 template <int D>
-__global__ __launch_bounds__(kCalibThreads) void k_kvq_calibrate(const SeqDesc *__restrict__ seqs, int seq,
-                                                                 const uint16_t *__restrict__ k, int Hkv, int n0) {
-  __shared__ uint32_t hist[64][257];
-  __shared__ uint32_t s_sel[64], s_rem[64];
-  const SeqDesc &sd = seqs[seq];
-  const int h = blockIdx.x, c0 = 64 * blockIdx.y;
+__global__ __launch_bounds__(kCalibThreads) void k_kvq_calibrate(const SeqDesc *__restrict__ seqs,
+                                                                 const int32_t *__restrict__ list,
+                                                                 const uint16_t *__restrict__ k, int Hkv) {
+  constexpr int NW = kCalibThreads / 64, LC = kCalibChannels / 8, TPL = 64 / LC;  // lanes a token, tokens a load
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kCalibChannels][260];
+  __shared__ uint32_t s_sel[kCalibChannels], s_rem[kCalibChannels];
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, c0 = kCalibChannels * (int)(blockIdx.x / Hkv);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int NW = kCalibThreads / 64;
+  float2 *tau = reinterpret_cast<float2 *>(sd.kmeta) + (size_t)h * D + c0;
   const int want = sd.bp > 0 ? sd.n_o : 0;  // 0-based rank from the top
   if (want >= n0) {  // fewer prompt tokens than the rank: no threshold (every key is an inlier)
-    if (threadIdx.x < 64)
-      (reinterpret_cast<float2 *>(sd.kmeta) + (size_t)h * D)[c0 + threadIdx.x] = make_float2(0.f, 0.f);
+    if (threadIdx.x < kCalibChannels) tau[threadIdx.x] = make_float2(0.f, 0.f);
     return;
   }
-  if (threadIdx.x < 64) s_rem[threadIdx.x] = (uint32_t)want + 1;  // 1-based rank
-  const uint16_t *kc = k + (size_t)h * D + c0 + lane;
-  const size_t tstride = (size_t)Hkv * D;
+  if (threadIdx.x < kCalibChannels) s_rem[threadIdx.x] = (uint32_t)want + 1;  // 1-based rank
+  const int cl = 8 * (lane % LC);  // this lane's first channel of the workgroup's
+  const uint16_t *kc = k + ((size_t)sd.row0 * Hkv + h) * D + c0 + cl;
+  const size_t pitch = (size_t)Hkv * D;
   for (int pass = 0; pass < 2; ++pass) {
-    for (int e = threadIdx.x; e < 64 * 257; e += kCalibThreads) (&hist[0][0])[e] = 0u;
+    for (int e = threadIdx.x; e < kCalibChannels * 260; e += kCalibThreads) (&hist[0][0])[e] = 0u;
     __syncthreads();
-    const uint32_t sel = pass == 0 ? 0u : s_sel[lane];
-    for (int t0 = wave; t0 < n0; t0 += NW * kCalibBatch) {
-      uint32_t key[kCalibBatch];
+    uint32_t sel[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sel[e] = pass == 0 ? 0u : s_sel[cl + e];
+    for (int t0 = wave * TPL; t0 < n0; t0 += NW * TPL * kCalibBatch) {
+      uint4 w[kCalibBatch];
 #pragma unroll
       for (int b = 0; b < kCalibBatch; ++b)
-        key[b] = (uint32_t)gld(kc + (size_t)min(t0 + b * NW, n0 - 1) * tstride) & 0x7FFFu;
+        w[b] = gld16h(kc + (size_t)min(t0 + b * NW * TPL + lane / LC, n0 - 1) * pitch);
 #pragma unroll
       for (int b = 0; b < kCalibBatch; ++b) {
-        if (t0 + b * NW >= n0) break;
-        if (pass == 0) atomicAdd(&hist[lane][key[b] >> 8], 1u);
-        else if ((key[b] >> 8) == sel) atomicAdd(&hist[lane][key[b] & 255u], 1u);
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-      const int c = threadIdx.x;
-      const uint32_t remaining = s_rem[c];
-      uint32_t cum = 0;
-      int dg = 0;
-      for (int bb = 255; bb >= 0; --bb) {
-        if (cum + hist[c][bb] >= remaining) {
-          dg = bb;
-          break;
+        if (t0 + b * NW * TPL + lane / LC >= n0) break;
+        const uint32_t ww[4] = {w[b].x, w[b].y, w[b].z, w[b].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t key = (ww[e / 2] >> (16 * (e & 1))) & 0x7FFFu;
+          if (pass == 0) atomicAdd(&hist[cl + e][key >> 8], 1u);
+          else if ((key >> 8) == sel[e]) atomicAdd(&hist[cl + e][key & 255u], 1u);
         }
-        cum += hist[c][bb];
       }
-      s_rem[c] = remaining - cum;
-      if (pass == 0) {
-        s_sel[c] = (uint32_t)dg;
-      } else {
-        const float tau = h2f((s_sel[c] << 8) | (uint32_t)dg);
-        const float inv = tau > 0.f ? __fdiv_rn(1.0f, tau) : 0.f;
-        (reinterpret_cast<float2 *>(sd.kmeta) + (size_t)h * D)[c0 + c] = make_float2(tau, inv);
+    }
+    __syncthreads();
+    for (int c = wave; c < kCalibChannels; c += NW) {
+      // lane l owns digits 255 - 4l .. 252 - 4l, so the scan over lanes counts the larger digits
+      const uint4 h4 = *reinterpret_cast<const uint4 *>(&hist[c][252 - 4 * lane]);
+      const int cnt[4] = {(int)h4.w, (int)h4.z, (int)h4.y, (int)h4.x};
+      const int rem = (int)s_rem[c], tot = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+      int above = wave_incl_scan(tot) - tot;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (above < rem && rem <= above + cnt[i]) {  // in exactly one lane
+          const uint32_t dg = 255 - (4 * lane + i);
+          if (pass == 0) {
+            s_sel[c] = dg;
+            s_rem[c] = (uint32_t)(rem - above);
+          } else {
+            const float t = h2f((s_sel[c] << 8) | dg);
+            tau[c] = make_float2(t, t > 0.f ? __fdiv_rn(1.0f, t) : 0.f);
+          }
+        }
+        above += cnt[i];
       }
     }
     __syncthreads();
   }
 }
 
-// KVQ prompt keys, pass 1 (write codes, count outliers per token into krow[t+1]) or pass 2
-// (write the outlier entries at their CSR offsets).
-template <int D>
-__global__ __launch_bounds__(128) void k_kvq_keys(const SeqDesc *__restrict__ seqs, int seq,
-                                                 const uint16_t *__restrict__ k, const float *__restrict__ cbtab,
-                                                 int Hkv, int pass) {
-  __shared__ uint8_t s_code[D];
-  __shared__ int s_tmp[4];
-  const SeqDesc &sd = seqs[seq];
-  const int t = blockIdx.x, h = blockIdx.y, c = threadIdx.x;
-  const uint32_t kb = k[((size_t)t * Hkv + h) * D + c];
-  bool outl;
-  const int code = kvq_key_code(sd, kvq_key_tau(sd, h, c, D), kb, cbtab, &outl);
-  uint32_t *krow = reinterpret_cast<uint32_t *>(sd.krow) + h * stride_krow(sd);
-  if (pass == 0) {
-    uint8_t *row = reinterpret_cast<uint8_t *>(sd.kc) + h * stride_codes(sd) + (size_t)t * sd.rowbytes;
-    pack_row<D>(code, sd.bits, s_code, row);
-    int total;
-    flag_rank<D>(outl, s_tmp, &total);
-    if (c == 0) krow[t + 1] = (uint32_t)total;
+// A lane's 8 key codes are 8 * BITS consecutive bits of its token's packed row (see packed_word).
+template <int BITS>
+MKV_DEV void store_key_codes(const int (&code)[8], uint8_t *row, int l) {
+  uint32_t v = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v |= (uint32_t)code[e] << (BITS * e);
+  if constexpr (BITS == 4) {
+    gst(reinterpret_cast<uint32_t *>(row) + l, v);
+  } else if constexpr (BITS == 2) {
+    gst(reinterpret_cast<uint16_t *>(row) + l, (uint16_t)v);
   } else {
-    int total;
-    const int r = flag_rank<D>(outl, s_tmp, &total);
-    if (outl) (reinterpret_cast<uint32_t *>(sd.kout) + h * stride_kout(sd))[krow[t] + r] = outlier_entry(kb, t, code, c);
+    // four lanes' 24-bit pieces make three words: word i takes piece i from bit 8 i up and the foot of
+    // piece i + 1
+    const uint32_t nx = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xF9, 0xF, 0xF, false);  // quad_perm [1,2,3,3]
+    const int i = l & 3;
+    if (i < 3) gst(reinterpret_cast<uint32_t *>(row) + 3 * (l >> 2) + i, (v >> (8 * i)) | (nx << (24 - 8 * i)));
   }
 }
 
-// In-place inclusive scan of krow[1..n0] (per-token outlier counts) per kv head.
-__global__ __launch_bounds__(256) void k_kvq_scan(const SeqDesc *__restrict__ seqs, int seq, int32_t *state,
-                                                  int Hkv, int n0) {
-  __shared__ int s_tmp[4];
+// A lane's 8 channels of key thresholds, as kvq_key_tau gives them.
+MKV_DEV void load_tau8(const SeqDesc &sd, int h, int c, int D, float (&tau)[8], float (&inv)[8]) {
+  const uint32_t *p = reinterpret_cast<const uint32_t *>(sd.kmeta) + 2 * ((size_t)h * D + c);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint4 u = gld16(p + 4 * e);
+    tau[2 * e] = __builtin_bit_cast(float, u.x);
+    inv[2 * e] = __builtin_bit_cast(float, u.y);
+    tau[2 * e + 1] = __builtin_bit_cast(float, u.z);
+    inv[2 * e + 1] = __builtin_bit_cast(float, u.w);
+  }
+}
+
+// KVQ prompt keys: codes, and each token's outlier count into krow[t + 1].
+template <int D>
+__global__ __launch_bounds__(kKvqThreads) void k_kvq_keys(const SeqDesc *__restrict__ seqs,
+                                                          const int32_t *__restrict__ list,
+                                                          const uint16_t *__restrict__ k,
+                                                          const float *__restrict__ cbtab, int Hkv) {
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  if (t0 >= n0) return;
+  const int l = threadIdx.x % LT, tl = threadIdx.x / LT;
+  const uint16_t *kp = k + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
+  uint4 nx = gld16h(kp + (size_t)min(t0 + tl, n0 - 1) * Hkv * D);
+  float tau[8], inv[8];
+  load_tau8(sd, h, 8 * l, D, tau, inv);
+  const bool outliers = sd.bp > 0;
+  uint8_t *rows = reinterpret_cast<uint8_t *>(sd.kc) + h * stride_codes(sd);
+  uint32_t *krow = reinterpret_cast<uint32_t *>(sd.krow) + h * stride_krow(sd);
+  auto run = [&](auto bits_tag) {
+    constexpr int BITS = decltype(bits_tag)::value, NC = 1 << BITS;
+    const float *mid = cbtab + cb_offset(BITS) + 2 * NC;
+#pragma unroll 1
+    for (int i = 0; i < NI; ++i) {
+      const int t = t0 + i * TPI + tl;
+      const uint4 w = nx;
+      if (i + 1 < NI) nx = gld16h(kp + (size_t)min(t + TPI, n0 - 1) * Hkv * D);
+      float x[8];
+      unpack8(w, x);
+      int code[8], n = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        code[e] = code_from_mid(__fmul_rn(x[e], inv[e]), mid, NC - 1);
+        n += outliers && fabsf(x[e]) > tau[e] ? 1 : 0;
+      }
+      n = lane_group_sum<LT>(n);
+      if (t < n0) {
+        store_key_codes<BITS>(code, rows + (size_t)t * sd.rowbytes, l);
+        if (l == 0) gst(krow + t + 1, (uint32_t)n);
+      }
+    }
+  };
+  if (sd.bits == 4) run(std::integral_constant<int, 4>{});
+  else if (sd.bits == 3) run(std::integral_constant<int, 3>{});
+  else run(std::integral_constant<int, 2>{});
+}
+
+// In-place inclusive scan of krow[1..n0] (per-token outlier counts) per kv head, 4 tokens a thread;
+// and the head's state after the prompt.
+constexpr int kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void k_kvq_scan(const SeqDesc *__restrict__ seqs,
+                                                           const int32_t *__restrict__ list, int32_t *state,
+                                                           int Hkv) {
+  __shared__ int s_tmp[kScanThreads / 64];
+  const int seq = list[blockIdx.y], h = blockIdx.x;
   const SeqDesc &sd = seqs[seq];
-  const int h = blockIdx.x;
+  const int n0 = sd.n0;
   uint32_t *krow = reinterpret_cast<uint32_t *>(sd.krow) + h * stride_krow(sd);
   int run = 0;
-  for (int a = 0; a < n0; a += 256) {
-    const int i = a + (int)threadIdx.x;
-    const int x = (i < n0) ? (int)krow[i + 1] : 0;
+  for (int a = 4 * (int)threadIdx.x; a - 4 * (int)threadIdx.x < n0; a += 4 * kScanThreads) {
+    int x[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = a + i < n0 ? (int)gld(krow + a + i + 1) : 0;
+      sum += x[i];
+    }
     int total;
-    const int ex = block_exclusive_scan<256>(x, s_tmp, &total);
-    if (i < n0) krow[i + 1] = (uint32_t)(run + ex + x);
+    int pre = run + block_exclusive_scan<kScanThreads>(sum, s_tmp, &total);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      pre += x[i];
+      if (a + i < n0) gst(krow + a + i + 1, (uint32_t)pre);
+    }
     run += total;
   }
   if (threadIdx.x == 0) {
     krow[0] = 0;
-    state[((size_t)seq * Hkv + h) * ST_WORDS + ST_KOUT_FILL] = run;
+    int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
+    st[ST_KOUT_FILL] = run;
+    st[ST_COUNT] = n0;
+    st[ST_NEXT_POS] = n0;
+    st[ST_KEPT] = n0;
   }
 }
 
-// KVQ prompt values: one workgroup per (4-token block, kv head) quantizes the block's tokens and
-// writes the block.
+// KVQ prompt keys: the outlier entries at their CSR offsets, ascending channels; codes come from the
+// rows that k_kvq_keys wrote.
 template <int D>
-__global__ __launch_bounds__(128) void k_prefill_kvq_values(const SeqDesc *__restrict__ seqs, int seq,
-                                                           const uint16_t *__restrict__ v,
-                                                           const float *__restrict__ cbtab, int Hkv, int n0) {
-  __shared__ float s_abs[D];
-  __shared__ float s_scale;
-  __shared__ int s_tmp[4];
-  __shared__ uint32_t s_blk[D / 2];
-  const SeqDesc &sd = seqs[seq];
-  const int q = blockIdx.x, h = blockIdx.y, c = threadIdx.x;
-  const int words = D * sd.bits / 8;
-  for (int w = c; w < words; w += D) s_blk[w] = 0;
-  __syncthreads();
-  for (int j = 0; j < 4 && 4 * q + j < n0; ++j) {
-    const int t = 4 * q + j;
-    const int code = kvq_value_token<D>(sd, h, t, v[((size_t)t * Hkv + h) * D + c], cbtab, s_abs, &s_scale, s_tmp);
-    or_quad_code(s_blk, c, j, code, sd.bits);
+__global__ __launch_bounds__(kKvqThreads) void k_kvq_outliers(const SeqDesc *__restrict__ seqs,
+                                                              const int32_t *__restrict__ list,
+                                                              const uint16_t *__restrict__ k, int Hkv) {
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  if (t0 >= n0 || sd.bp <= 0) return;
+  const int l = threadIdx.x % LT, tl = threadIdx.x / LT;
+  const uint16_t *kp = k + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
+  const uint32_t *krow = reinterpret_cast<const uint32_t *>(sd.krow) + h * stride_krow(sd);
+  uint32_t *ko = reinterpret_cast<uint32_t *>(sd.kout) + h * stride_kout(sd);
+  uint4 w[NI];
+  uint32_t at[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int t = min(t0 + i * TPI + tl, n0 - 1);
+    w[i] = gld16h(kp + (size_t)t * Hkv * D);
+    at[i] = gld(krow + t);
   }
-  __syncthreads();
-  store_quad(sd, h, 4 * q, s_blk, D);
+  float tau[8], inv[8];  // (inv unused)
+  load_tau8(sd, h, 8 * l, D, tau, inv);
+  const int bits = sd.bits;
+  const uint8_t *rows = reinterpret_cast<const uint8_t *>(sd.kc) + h * stride_codes(sd);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int t = t0 + i * TPI + tl;
+    float x[8];
+    unpack8(w[i], x);
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m |= fabsf(x[e]) > tau[e] ? 1u << e : 0u;
+    m = t < n0 ? m : 0u;
+    uint32_t *dst = ko + at[i] + lane_group_before<LT>(__popc(m));
+    // the 8 codes of this lane are the 8 * bits bits at byte l * bits of the token's row
+    for (; m != 0; m &= m - 1) {
+      const int e = __builtin_ctz(m), bit = bits * e;
+      const uint8_t *c = rows + (size_t)t * sd.rowbytes + l * bits;
+      const uint32_t lo = gld(c + (bit >> 3)), hi = gld(c + min((bit >> 3) + 1, bits - 1));
+      const int code = (int)((lo | hi << 8) >> (bit & 7)) & ((1 << bits) - 1);
+      gst(dst++, outlier_entry(gld(kp + (size_t)t * Hkv * D + e), t, code, 8 * l + e));
+    }
+  }
+}
+
+// KVQ prompt values: per-token scale (the n_ov-th largest |v|, 0-based), codes in 4-token blocks, and
+// the outliers, whose slots go by ascending channel.  A wave holds whole 4-token blocks: the four
+// tokens' codes of a lane's 8 channels are BITS words of the block, OR-ed across their lanes.
+template <int D>
+__global__ __launch_bounds__(kKvqThreads) void k_kvq_values(const SeqDesc *__restrict__ seqs,
+                                                            const int32_t *__restrict__ list,
+                                                            const uint16_t *__restrict__ v,
+                                                            const float *__restrict__ cbtab, int Hkv) {
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  if (t0 >= n0) return;
+  const int l = threadIdx.x % LT, tl = threadIdx.x / LT, j = tl & 3;
+  const uint16_t *vp = v + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
+  uint4 nx = gld16h(vp + (size_t)min(t0 + tl, n0 - 1) * Hkv * D);
+  const int nov = sd.bp > 0 ? sd.n_ov : 0, slots = sd.nov_slots;
+  const bool outliers = sd.bp > 0;
+  uint8_t *blocks = reinterpret_cast<uint8_t *>(sd.vc) + h * stride_codes(sd);
+  float *scale = reinterpret_cast<float *>(sd.vmeta) + h * stride_slots(sd);
+  uint32_t *vo = reinterpret_cast<uint32_t *>(sd.vout) + h * stride_vout(sd);
+  uint32_t *vd = reinterpret_cast<uint32_t *>(sd.vdel) + h * stride_vout(sd);
+  auto run = [&](auto bits_tag) {
+    constexpr int BITS = decltype(bits_tag)::value, NC = 1 << BITS;
+    const float *cb = cbtab + cb_offset(BITS) + NC, *mid = cbtab + cb_offset(BITS) + 2 * NC + (NC - 1);
+#pragma unroll 1
+    for (int i = 0; i < NI; ++i) {
+      const int t = t0 + i * TPI + tl;
+      const uint4 w = nx;
+      if (i + 1 < NI) nx = gld16h(vp + (size_t)min(t + TPI, n0 - 1) * Hkv * D);
+      const uint32_t valid = t < n0 ? ~0u : 0u;
+      float x[8], ax[8];
+      unpack8(w, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ax[e] = fabsf(x[e]);
+      // the largest values one after another, with their multiplicities, until nov of them lie above
+      float s = 0.f;
+      int above = 0;
+      bool found = false;
+      for (int r = 0; r <= nov && __any(!found); ++r) {
+        float m = -1.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, r == 0 || ax[e] < s ? ax[e] : -1.f);
+        m = lane_group_reduce<LT>(m, [](float a, float b) { return fmaxf(a, b); });
+        int c = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c += ax[e] == m ? 1 : 0;
+        c = lane_group_sum<LT>(c);
+        if (!found) {
+          s = m;
+          above += c;
+          found = above > nov;
+        }
+      }
+      const float inv = s > 0.f ? __fdiv_rn(1.0f, s) : 0.f;
+      int code[8];
+      uint32_t word[BITS] = {}, om = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        code[e] = code_from_mid(__fmul_rn(x[e], inv), mid, NC - 1);
+        om |= ax[e] > s ? 1u << e : 0u;
+        const uint32_t f = (uint32_t)code[e] << (BITS * j);
+        const int bit = 4 * BITS * e, sh = bit & 31;
+        word[bit >> 5] |= f << sh;
+        if (sh + 4 * BITS > 32) word[(bit >> 5) + 1] |= f >> (32 - sh);
+      }
+      if (!outliers) om = 0;
+      om &= valid;
+      uint32_t mine = 0;  // lane group j stores word j of each lane's BITS words
+#pragma unroll
+      for (int b = 0; b < BITS; ++b) {
+        word[b] &= valid;
+        word[b] |= (uint32_t)__shfl_xor((int)word[b], LT);
+        word[b] |= (uint32_t)__shfl_xor((int)word[b], 2 * LT);
+        mine = j == b ? word[b] : mine;
+      }
+      if (j < BITS && t - j < n0)
+        gst(reinterpret_cast<uint32_t *>(blocks + (size_t)(t - j) * sd.rowbytes) + l * BITS + j, mine);
+      const int before = lane_group_before<LT>(__popc(om)), total = lane_group_sum<LT>(__popc(om));
+      if (t < n0) {
+        if (l == 0) gst(scale + t, s);
+        if (om) {
+          // (values and codes re-read, or counted again, for the few outliers only)
+          int r = before;
+          for (uint32_t m = om; m != 0; m &= m - 1, ++r) {
+            const int e = __builtin_ctz(m);
+            if (r >= slots) break;
+            const uint32_t bits = gld(vp + (size_t)t * Hkv * D + e);
+            const float y = h2f(bits);
+            const int c = code_from_mid(__fmul_rn(y, inv), mid, NC - 1);
+            gst(vo + (size_t)r * sd.cap + t, outlier_entry(bits, t, c, 8 * l + e));
+            // the attention's form: the outlier minus the value its code stands for, and the channel
+            gst(vd + (size_t)r * sd.cap + t, vdel_pack(__fsub_rn(y, __fmul_rn(s, gld(cb + c))), 8 * l + e));
+          }
+        }
+        for (int r = total + l; r < slots; r += LT) {
+          gst(vo + (size_t)r * sd.cap + t, kNoOutlier);
+          gst(vd + (size_t)r * sd.cap + t, 0u);
+        }
+      }
+    }
+  };
+  if (sd.bits == 4) run(std::integral_constant<int, 4>{});
+  else if (sd.bits == 3) run(std::integral_constant<int, 3>{});
+  else run(std::integral_constant<int, 2>{});
 }
 
 __global__ void k_prefill_state(const SeqDesc *__restrict__ seqs, int seq, int32_t *state, int Hkv) {
@@ -717,7 +967,8 @@ template <int D>
 hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq, const uint16_t *k,
                         const uint16_t *v, hipStream_t st) {
   const int n0 = hs.n0, Hkv = sh.Hkv;
-  hipLaunchKernelGGL(k_prefill_state, dim3(1), dim3(64 * ((Hkv + 63) / 64)), 0, st, dv.seqs, seq, dv.state, Hkv);
+  if (hs.method != KVQ)  // (the KVQ scan writes it)
+    hipLaunchKernelGGL(k_prefill_state, dim3(1), dim3(64 * ((Hkv + 63) / 64)), 0, st, dv.seqs, seq, dv.state, Hkv);
   switch (hs.method) {
     case FP16:
     case H2O:
@@ -735,14 +986,23 @@ hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &hs, int s
       hipLaunchKernelGGL(k_prefill_uq_values<D>, dim3((n0 + 3) / 4, Hkv), dim3(D), 0, st, dv.seqs, seq, v, Hkv, n0);
       hipLaunchKernelGGL(k_prefill_uq_keys<D>, dim3(n0 / 64 + 1, Hkv), dim3(D), 0, st, dv.seqs, seq, k, Hkv, n0);
       break;
-    case KVQ:
-      hipLaunchKernelGGL(k_kvq_calibrate<D>, dim3(Hkv, D / 64), dim3(kCalibThreads), 0, st, dv.seqs, seq, k, Hkv, n0);
-      hipLaunchKernelGGL(k_kvq_keys<D>, dim3(n0, Hkv), dim3(D), 0, st, dv.seqs, seq, k, dv.cbtab, Hkv, 0);
-      hipLaunchKernelGGL(k_kvq_scan, dim3(Hkv), dim3(256), 0, st, dv.seqs, seq, dv.state, Hkv, n0);
-      hipLaunchKernelGGL(k_kvq_keys<D>, dim3(n0, Hkv), dim3(D), 0, st, dv.seqs, seq, k, dv.cbtab, Hkv, 1);
-      hipLaunchKernelGGL(k_prefill_kvq_values<D>, dim3((n0 + 3) / 4, Hkv), dim3(D), 0, st, dv.seqs, seq, v, dv.cbtab,
-                         Hkv, n0);
+    case KVQ: {
+      const unsigned H = sh.Hkv, blocks = (n0 + kKvqTokens - 1) / kKvqTokens;
+      for (int a = 0; a < dv.of[KVQ].n; a += kMaxGridY) {
+        const unsigned n = std::min(dv.of[KVQ].n - a, kMaxGridY);
+        const int32_t *list = dv.of[KVQ].list + a;
+        hipLaunchKernelGGL(k_kvq_calibrate<D>, dim3(H * (D / kCalibChannels), n), dim3(kCalibThreads), 0, st, dv.seqs,
+                           list, k, Hkv);
+        hipLaunchKernelGGL(k_kvq_keys<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, k, dv.cbtab,
+                           Hkv);
+        hipLaunchKernelGGL(k_kvq_scan, dim3(H, n), dim3(kScanThreads), 0, st, dv.seqs, list, dv.state, Hkv);
+        hipLaunchKernelGGL(k_kvq_outliers<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, k,
+                           Hkv);
+        hipLaunchKernelGGL(k_kvq_values<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, v, dv.cbtab,
+                           Hkv);
+      }
       break;
+    }
     default:
       return hipErrorInvalidValue;
   }

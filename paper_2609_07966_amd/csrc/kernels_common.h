@@ -46,6 +46,14 @@ MKV_DEV uint4 gld16(const void *p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// 16 bytes of a caller's fp16 tensor, which is only known to be aligned to its elements (global memory
+// takes any alignment here; the aligned case costs the same as gld16)
+MKV_DEV uint4 gld16h(const uint16_t *p) {
+  typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));
+  const u32x4h v = *(const MKV_GLOBAL u32x4h *)p;
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // 16 bytes as four scalars (the backend merges the four loads into one 16-byte load); loader
 // state holds plain scalars rather than vector types
 struct U4 {

@@ -171,7 +171,7 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
   L->off_state = take(sizeof(int32_t) * S * Hkv * ST_WORDS);
   L->off_cbtab = take(sizeof(float) * kCbRegionFloats);
   L->seqs.assign(S, SeqDesc{});
-  int q_h2o = 0, q_rk = 0;
+  int q_h2o = 0, q_rk = 0, row0 = 0;
   for (int s = 0; s < S; ++s) {
     SeqDesc &d = L->seqs[s];
     const mkv_config &c = cfg[s];
@@ -180,6 +180,8 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     d.n0 = n0;
     d.bits = c.bits;
     d.bp = c.outlier_bp;
+    d.row0 = row0;
+    row0 += n0;
     const size_t H = Hkv;
     switch (c.method) {
       case FP16:
@@ -668,8 +670,10 @@ mkv_status mkv_append_quantize(mkv_cache *c, const uint16_t *k, const uint16_t *
                     c->hs[s].n0);
     const size_t row = (size_t)c->sh.Hkv * c->sh.D;
     for (int s = 0; s < S; ++s) {
-      hipError_t e = launch_prefill_seq(c->dv, c->sh, c->hs[s], s, k + (size_t)cu_new[s] * row,
-                                        v + (size_t)cu_new[s] * row, hst);
+      const bool all = c->hs[s].method == KVQ;  // one call over the method's sequences
+      if (all && s != c->dv.of[KVQ].longest) continue;
+      const size_t first = all ? 0 : (size_t)cu_new[s] * row;
+      hipError_t e = launch_prefill_seq(c->dv, c->sh, c->hs[s], s, k + first, v + first, hst);
       if (e != hipSuccess) return hip_fail(e, "prefill append");
     }
     c->phase = (c->any_h2o || c->any_rocket) ? PH_PROMPT : PH_READY;

@@ -53,8 +53,9 @@ struct SeqDesc {
   int32_t pool_cap, nblk, w_eff, chunk;   // KVQ outlier pool; UQ blocks; window rows; tile tokens
   int32_t tile_first, tile_count, q_off, cstride;  // partial tiles (per kv head); prompt-q row offset;
                                                    // ROCKET channel-major row stride (cap rounded to 8)
-  int32_t vparts, nseg, seg_rows, spare0;  // H2O: eviction candidates per kv head (one per combine part);
-                                           // prefill scoring: row segments and virtual rows of each
+  int32_t vparts, nseg, seg_rows;  // H2O: eviction candidates per kv head (one per combine part);
+                                   // prefill scoring: row segments and virtual rows of each
+  int32_t row0;                    // first row of the sequence in the prompt batch's k and v
   uint64_t k, v;            // fp16 [cap][d] rows (FP16 / H2O / ROCKET)
   uint64_t kc, vc;          // packed codes [cap][rowbytes] (UQ / KVQ)
   uint64_t kmeta, vmeta;    // UQ: float2 [nblk][d], float2 [cap][d/64]; KVQ: float2 tau/inv [d], float [cap]
@@ -180,6 +181,8 @@ struct LaunchEv {
 // H2O pairs whose last attention pass chose a victim write the token into its slot.
 hipError_t launch_append_decode(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                                 hipStream_t st, LaunchEv ev = {});
+// The prompt append of sequence `seq`, whose rows start at k and v; for KVQ of every KVQ sequence
+// (hs, seq: the one with the longest prompt; k, v: the whole batch's rows).
 hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
                               const uint16_t *k, const uint16_t *v, hipStream_t st);
 hipError_t launch_attention_partial(const Dev &dv, const Shape &sh, const uint16_t *q, hipStream_t st,

@@ -48,3 +48,56 @@ def test_h2o_scores_at_tile_edges(hkv, g, d):
             np.testing.assert_allclose(got, ref, rtol=0, atol=float((6 * x + n) * 2.0 ** -23) * max(1.0, ref.max()),
                                        err_msg=f"sequence {s} (n = {n}) head {h}")
     c.close()
+
+
+@pytest.mark.parametrize("hkv,g,d,bp", [(1, 2, 128, 100), (3, 1, 64, 100), (2, 2, 128, 0), (1, 4, 128, 700), (2, 1, 64, 5000)])
+def test_kvq_prompts_at_block_edges(hkv, g, d, bp):
+    """Ragged KVQuant prompts of all bit widths quantized together: thresholds, codes, outlier sets and
+    value scales bit for bit, with lengths around the 4-token value blocks and the 64-token
+    workgroups, outlier-free, one and many value outliers per token, ties and zero tokens, and inputs
+    that are aligned to their elements only."""
+    import torch
+    from oracle import kvquant
+    from paper_2609_07966_amd.cache import KVCache
+    lens = [1, 2, 4, 7, 63, 64, 65, 130, 257, 300]
+    bits = [2 + s % 3 for s in range(len(lens))]
+    cfgs = [{"method": "kvq", "bits": b, "outlier_bp": bp} for b in bits]
+    r = np.random.default_rng(bp + d)
+    n = sum(lens)
+    k = (r.standard_normal((n, hkv, d)) * np.exp(r.standard_normal((hkv, d)))).astype(np.float16)
+    v = r.standard_normal((n, hkv, d)).astype(np.float16)
+    v[::7] = np.round(v[::7])  # many equal magnitudes in a token
+    v[5] = 0
+    k[::5, :, 3] = k[0, :, 3]
+    books, flat = {}, []
+    for b in (2, 3, 4):
+        half = [np.sort(r.uniform(-1, 1, 1 << b)).astype(np.float16).astype(np.float32) for _ in range(2)]
+        books[b] = half
+        flat += [float(x) for x in np.concatenate(half)]
+
+    def odd(x):  # on the device, 2 bytes past a 16-byte boundary
+        t = torch.empty(x.size + 8, dtype=torch.float16, device="cuda")
+        t[1:1 + x.size] = torch.from_numpy(x.reshape(-1)).cuda()
+        return t[1:]
+    c = KVCache((len(lens), hkv * g, hkv, d, 1), cfgs, lens, codebooks=flat)
+    c.append_prompt(odd(k), odd(v))
+    at = 0
+    for s, (m, b) in enumerate(zip(lens, bits)):
+        for h in range(hkv):
+            kp, vp = k[at:at + m, h], v[at:at + m, h]
+            cbk, cbv = books[b]
+            tau, inv = kvquant.calibrate_keys(kp, bp)
+            ck, ok = kvquant.quantize_keys(kp, tau, inv, cbk, bp)
+            cv, sv, ov = kvquant.quantize_values(vp, cbv, bp)
+            where = f"sequence {s} ({m} tokens, {b} bits) head {h}"
+            np.testing.assert_array_equal(c.export(s, h, "scales_k"), tau, err_msg=where)
+            np.testing.assert_array_equal(c.export(s, h, "codes_k").reshape(m, d), ck, err_msg=where)
+            np.testing.assert_array_equal(c.export(s, h, "codes_v").reshape(m, d), cv, err_msg=where)
+            np.testing.assert_array_equal(c.export(s, h, "scales_v"), sv, err_msg=where)
+            for what, raw, out in (("outliers_k", kp, ok), ("outliers_v", vp, ov)):
+                got = c.export(s, h, what).reshape(m, d)
+                np.testing.assert_array_equal(got >= 0, out, err_msg=where + what)
+                np.testing.assert_array_equal(got[out].astype(np.uint16), raw.view(np.uint16)[out])
+            assert c.counts(s, h) == (m, m, m, m)
+        at += m
+    c.close()
