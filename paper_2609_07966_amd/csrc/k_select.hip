@@ -51,26 +51,10 @@ __global__ __launch_bounds__(kTopkThreads, 8) void k_topk(const SeqDesc *__restr
 // rows or keys and launches per sequence stood before; a library matrix product reaches 1150 here.
 // The column sums are held to 168 registers (three waves per SIMD; 2.90 ms at 220 and two).
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
-typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
-MKV_DEV f4v mfma_k32(const uint4 &a, const uint4 &b, f4v c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, b), c, 0, 0, 0);
-}
 MKV_DEV f16v mfma32(const uint4 &a, const uint4 &b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, b), c, 0, 0, 0);
-}
-
-// Sum and max over the 16 lanes of a row (lanes with the same lq).
-MKV_DEV float row16_max(float x) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
-}
-MKV_DEV float row16_sum(float x) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o);
-  return x;
 }
 
 constexpr int kScoreTile = 64;  // streamed items per LDS stage
@@ -82,6 +66,22 @@ template <int D>
 struct ScoreStage {
   uint4 row[2][kScoreTile][D / 8 + 1];
 };
+
+// Sums over the 32 lanes of each half wave: lane lr gets the total of v[lr].  At step o the lanes with
+// bit o clear keep the even values of each pair and the others the odd ones.
+MKV_DEV float half_wave_sums(float (&v)[32]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1, n = 32; o < 32; o <<= 1, n >>= 1) {
+    const bool odd = lane & o;
+#pragma unroll
+    for (int i = 0; i < n / 2; ++i) {
+      const float keep = odd ? v[2 * i + 1] : v[2 * i], send = odd ? v[2 * i] : v[2 * i + 1];
+      v[i] = keep + __shfl_xor(send, o);
+    }
+  }
+  return v[0];
+}
 
 // Query row of virtual row r (clamped to the prompt) of kv head h, in 16-byte units.
 template <int D>
@@ -290,19 +290,9 @@ __global__ __launch_bounds__(NT, 3) void k_h2o_colsums(const SeqDesc *__restrict
       }
     }
   }
-  // sum over the 32 lanes of a half: at step o the lanes with bit o clear keep the even values of
-  // each pair and the others the odd ones, so lane lr ends with the total of value lr
-#pragma unroll
-  for (int o = 1, n = 32; o < 32; o <<= 1, n >>= 1) {
-    const bool odd = lane & o;
-#pragma unroll
-    for (int i = 0; i < n / 2; ++i) {
-      const float keep = odd ? acc[2 * i + 1] : acc[2 * i], send = odd ? acc[2 * i] : acc[2 * i + 1];
-      acc[i] = keep + __shfl_xor(send, o);
-    }
-  }
+  const float sum = half_wave_sums(acc);
   const int key = key0 + 32 * (lr / 16) + 8 * ((lr / 4) & 3) + 4 * lh + (lr & 3);
-  if (key < n0) gst(reinterpret_cast<float *>(sd.colpart) + ((size_t)h * sd.nseg + seg) * n0 + key, acc[0]);
+  if (key < n0) gst(reinterpret_cast<float *>(sd.colpart) + ((size_t)h * sd.nseg + seg) * n0 + key, sum);
 }
 
 // Scores: the segments' column sums added in ascending order (a key's first segment is the one its
@@ -405,99 +395,125 @@ __global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ s
 
 // ---- SnapKV prefill -------------------------------------------------------------------------------
 // Window row r = i * G + g (query head h*G + g at position n0 - w + i; it attends to keys
-// 0 .. n0 - w + i).  Pass 1: per 256-key chunk and wave, the partial (max, sum of exp2) of every
-// row, from v_mfma_f32_16x16x32_f16 logit tiles.  Pass 2: each row's partials merged.  Pass 3: the
-// votes of a chunk's keys, the logits recomputed on the matrix cores.  Pass 4: max pooling into
-// order-preserving keys.  Pass 5: select, gather the kept rows.
-constexpr int SNAP_CHUNK = 256;  // keys per workgroup: 64 per wave, 4 key tiles of 16
-constexpr int SNAP_ROWS = 64;    // window rows staged in LDS at a time (4 row tiles of 16)
+// 0 .. n0 - w + i).  Pass 1: per 256-key chunk the partial (max, sum of exp2) of every row.  Pass 2:
+// each row's partials merged.  Pass 3: the votes of a chunk's keys, the logits recomputed.  Pass 4: max
+// pooling into order-preserving keys.  Pass 5: the selection; pass 6: the kept rows gathered.  Every
+// pass is one launch over all RocketKV sequences (grid as for H2O).
+//
+// Logit tiles as in the H2O scoring: S^T = K Q^T, a lane owning one row and 16 keys of a 32 x 32 tile.
+// A wave holds 64 keys in registers and takes the window rows from LDS, 64 staged at a time, so K is
+// read once per pass, straight into operands.  4 prompts of 32768 tokens (268 MB of K a pass): row
+// statistics 96 us and votes 81, where per-row shuffles and launches per sequence took 231 and 146.
+constexpr int SNAP_CHUNK = 256;  // keys per workgroup: 64 per wave
+constexpr int SNAP_ROWS = 64;    // window rows staged in LDS at a time
 
 // The window rows [r0, r0 + 64) (clamped to the last row) as fp16 operands in LDS.
 template <int D>
-MKV_DEV void stage_window(uint4 (*sq)[D / 8 + 1], const uint16_t *qw, int h, int G, int Hq, int w, int wfull,
-                          int rows, int r0) {
+MKV_DEV void stage_window(uint4 (*sq)[D / 8 + 1], const uint16_t *qw, const SeqDesc &sd, int h, int lg, int Hq, int rows,
+                          int r0) {
   constexpr int U = D / 8;
   for (int e = threadIdx.x; e < SNAP_ROWS * U; e += NT) {
     const int rr = e / U, u = e % U;
-    const int r = min(r0 + rr, rows - 1), i = r / G, g = r % G;
-    // the last w of the `wfull` window rows
-    sq[rr][u] = gld16(reinterpret_cast<const uint4 *>(qw + ((size_t)(wfull - w + i) * Hq + h * G + g) * D) + u);
+    const int r = min(r0 + rr, rows - 1), i = r >> lg, g = r & ((1 << lg) - 1);
+    // the last w_eff of the `window` rows
+    sq[rr][u] = gld16(reinterpret_cast<const uint4 *>(
+                          qw + ((size_t)(sd.q_off + sd.window - sd.w_eff + i) * Hq + (h << lg) + g) * D) + u);
   }
 }
 
-// A wave's 4 key tiles (16 keys each) of the chunk as matrix operands: key 16 n + lr, channels
-// 8 lq .. 8 lq + 7 of k-step s.
+// A wave's 64 keys as matrix operands: key 32 u + lr, channels 8 lh .. 8 lh + 7 of k-step s.
 template <int D>
-MKV_DEV void snap_key_operands(const uint16_t *ks, int key0, int n0, uint4 (&kop)[4][D / 32]) {
+MKV_DEV void snap_key_operands(const SeqDesc &sd, int h, int key0, uint4 (&ka)[2][D / 16]) {
   constexpr int U = D / 8;
-  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
+                                                    h * stride_stage(sd, D));
+  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int s = 0; s < D / 32; ++s)
-      kop[n][s] = gld16(reinterpret_cast<const uint4 *>(ks) + (size_t)min(key0 + 16 * n + lr, n0 - 1) * U + 4 * s + lq);
+    for (int s = 0; s < D / 16; ++s)
+      ka[u][s] = gld16(ks + (size_t)min(key0 + 32 * u + lr, sd.n0 - 1) * U + 2 * s + lh);
 }
 
 template <int D>
-__global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict__ seqs, int seq,
-                                                      const uint16_t *__restrict__ qw, int Hq, int G,
+MKV_DEV void snap_logits(const uint4 (&ka)[2][D / 16], const uint4 (*sq)[D / 8 + 1], int row, int lh, f16v (&S)[2]) {
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    const uint4 b = sq[row][2 * s + lh];
+    S[0] = mfma32(ka[0][s], b, S[0]);
+    S[1] = mfma32(ka[1][s], b, S[1]);
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict__ seqs,
+                                                      const int32_t *__restrict__ list,
+                                                      const uint16_t *__restrict__ qw, int Hq, int Hkv, int lg,
                                                       float scale2) {
-  constexpr int KS = D / 32;
   __shared__ uint4 sq[SNAP_ROWS][D / 8 + 1];
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0, w = sd.w_eff, wfull = sd.window;
-  const int chunk = blockIdx.x, h = blockIdx.y;
+  __shared__ float2 s_part[NT / 64][SNAP_ROWS];
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, chunk = (int)blockIdx.x / Hkv;
   const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
+  if (chunk >= nchunk || sd.T >= n0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
   const int key0 = chunk * SNAP_CHUNK + 64 * wave;
-  uint4 kop[4][KS];
-  snap_key_operands<D>(reinterpret_cast<const uint16_t *>(sd.stage_k) + h * stride_stage(sd, D), key0, n0, kop);
-  const int rows = w * G;
-  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * rows * nchunk * 4;
+  uint4 ka[2][D / 16];
+  snap_key_operands<D>(sd, h, key0, ka);
+  const int rows = w << lg;
+  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * rows * nchunk;
   for (int r0 = 0; r0 < rows; r0 += SNAP_ROWS) {
-    __syncthreads();
-    stage_window<D>(sq, qw, h, G, Hq, w, wfull, rows, r0);
+    stage_window<D>(sq, qw, sd, h, lg, Hq, rows, r0);
     __syncthreads();
 #pragma unroll 1
-    for (int t = 0; t < SNAP_ROWS / 16 && r0 + 16 * t < rows; ++t) {
-      float v[4][4];
+    for (int t = 0; t < SNAP_ROWS / 32 && r0 + 32 * t < rows; ++t) {
+      f16v S[2] = {};
+      snap_logits<D>(ka, sq, 32 * t + lr, lh, S);
+      if (key0 + 63 > n0 - w) {
+        const int rel = n0 - w + ((r0 + 32 * t + lr) >> lg) - key0 - 4 * lh;  // compared with constants
+        const int end = n0 - 1 - key0 - 4 * lh;
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        f4v S = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) S = mfma_k32(sq[16 * t + lr][4 * s + lq], kop[n][s], S);
-        const int key = key0 + 16 * n + lr;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int r = r0 + 16 * t + 4 * lq + j, posr = n0 - w + r / G;
-          v[n][j] = (key <= posr && key < n0) ? S[j] * scale2 : -INFINITY;
+        for (int i = 0; i < 32; ++i) {
+          const int c = 32 * (i / 16) + 8 * ((i / 4) & 3) + (i & 3);
+          S[i / 16][i % 16] = c <= min(rel, end) ? S[i / 16][i % 16] : -INFINITY;
         }
       }
+      float mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float M = row16_max(fmaxf(fmaxf(v[0][j], v[1][j]), fmaxf(v[2][j], v[3][j])));
-        float e = 0.f;
-        if (M != -INFINITY) {
+      for (int i = 0; i < 32; ++i) mx = fmaxf(mx, S[i / 16][i % 16]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale2;
+      const float ref = mx == -INFINITY ? 0.f : mx;  // no key of the wave's is visible: a sum of 0
+      float l[2] = {0.f, 0.f};
 #pragma unroll
-          for (int n = 0; n < 4; ++n) e += fexp2(v[n][j] - M);  // arguments <= 0
-        }
-        const float L = row16_sum(e);
-        const int r = r0 + 16 * t + 4 * lq + j;
-        if (lr == 0 && r < rows) part[((size_t)r * nchunk + chunk) * 4 + wave] = make_float2(M, L);
+      for (int i = 0; i < 32; ++i) l[i & 1] += fexp2(fmaf(S[i / 16][i % 16], scale2, -ref));
+      l[0] += l[1];
+      l[0] += __shfl_xor(l[0], 32);
+      if (lh == 0) s_part[wave][32 * t + lr] = make_float2(mx, l[0]);
+    }
+    __syncthreads();
+    if (threadIdx.x < SNAP_ROWS && r0 + (int)threadIdx.x < rows) {
+      float M = -INFINITY, L = 0.f;
+#pragma unroll
+      for (int v = 0; v < NT / 64; ++v) M = fmaxf(M, s_part[v][threadIdx.x].x);
+#pragma unroll
+      for (int v = 0; v < NT / 64; ++v) {
+        const float2 p = s_part[v][threadIdx.x];
+        L += p.x == -INFINITY ? 0.f : p.y * fexp2(p.x - M);
       }
+      part[(size_t)(r0 + threadIdx.x) * nchunk + chunk] = make_float2(M, L);
     }
   }
 }
 
-// Merge each window row's 4 nchunk partials (one wave per row); entry 0 of the row then holds
-// (max, sum of exp2) over all its keys.
-template <int D>
-__global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ seqs, int seq, int G) {
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0, rows = sd.w_eff * G, h = blockIdx.y;
-  const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK, np = 4 * nchunk;
-  const int lane = threadIdx.x & 63, r = blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
-  if (r >= rows) return;
+// Merge each window row's partials (one wave per row); entry 0 of the row then holds (max, 1 / sum of
+// exp2) over all its keys.
+__global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                   int Hkv, int lg) {
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, rows = sd.w_eff << lg, h = blockIdx.x % Hkv;
+  const int np = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
+  const int lane = threadIdx.x & 63, r = (int)blockIdx.x / Hkv * (NT / 64) + (threadIdx.x >> 6);
+  if (r >= rows || sd.T >= n0) return;
   float2 *pr = reinterpret_cast<float2 *>(sd.aux1) + ((size_t)h * rows + r) * np;
   float m = -INFINITY, l = 0.f;
   for (int e = lane; e < np; e += 64) {
@@ -509,71 +525,62 @@ __global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ s
   }
   const float M = wave_max(m);
   const float L = wave_sum(m == -INFINITY ? 0.f : l * fexp2(m - M));
-  if (lane == 0) pr[0] = make_float2(M, L);
+  if (lane == 0) pr[0] = make_float2(M, 1.f / L);
 }
 
-// Votes of a chunk's keys: sum over the window rows of exp2(s - M_r) / L_r.
+// Votes of a chunk's keys before the window: sum over the window rows of exp2(s - M_r) / L_r.  (Window
+// keys get sums too, over rows that do not see them; they are not written.)
 template <int D>
-__global__ __launch_bounds__(NT) void k_snap_votes(const SeqDesc *__restrict__ seqs, int seq,
-                                                   const uint16_t *__restrict__ qw, int Hq, int G,
+__global__ __launch_bounds__(NT) void k_snap_votes(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                   const uint16_t *__restrict__ qw, int Hq, int Hkv, int lg,
                                                    float scale2) {
-  constexpr int KS = D / 32;
   __shared__ uint4 sq[SNAP_ROWS][D / 8 + 1];
   __shared__ float2 sml[SNAP_ROWS];  // (M, 1 / L) of the staged rows
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0, w = sd.w_eff, wfull = sd.window;
-  const int chunk = blockIdx.x, h = blockIdx.y;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, chunk = (int)blockIdx.x / Hkv;
   const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
+  if (chunk >= nchunk || sd.T >= n0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
   const int key0 = chunk * SNAP_CHUNK + 64 * wave;
-  uint4 kop[4][KS];
-  snap_key_operands<D>(reinterpret_cast<const uint16_t *>(sd.stage_k) + h * stride_stage(sd, D), key0, n0, kop);
-  const int rows = w * G;
-  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * rows * nchunk * 4;
-  float col[4] = {0.f, 0.f, 0.f, 0.f};
+  uint4 ka[2][D / 16];
+  snap_key_operands<D>(sd, h, key0, ka);
+  const int rows = w << lg;
+  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * rows * nchunk;
+  float acc[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) acc[i] = 0.f;
   for (int r0 = 0; r0 < rows; r0 += SNAP_ROWS) {
     __syncthreads();
-    stage_window<D>(sq, qw, h, G, Hq, w, wfull, rows, r0);
+    stage_window<D>(sq, qw, sd, h, lg, Hq, rows, r0);
     if (threadIdx.x < SNAP_ROWS) {
-      const float *ml = reinterpret_cast<const float *>(part + (size_t)min(r0 + (int)threadIdx.x, rows - 1) * nchunk * 4);
-      sml[threadIdx.x] = make_float2(gld(ml), 1.f / gld(ml + 1));
+      const int r = r0 + (int)threadIdx.x;
+      const float *ml = reinterpret_cast<const float *>(part + (size_t)min(r, rows - 1) * nchunk);
+      const float iL = gld(ml + 1);
+      sml[threadIdx.x] = make_float2(gld(ml), r < rows ? iL : 0.f);
     }
     __syncthreads();
 #pragma unroll 1
-    for (int t = 0; t < SNAP_ROWS / 16 && r0 + 16 * t < rows; ++t) {
+    for (int t = 0; t < SNAP_ROWS / 32 && r0 + 32 * t < rows; ++t) {
+      f16v S[2] = {};
+      snap_logits<D>(ka, sq, 32 * t + lr, lh, S);
+      const float2 mi = sml[32 * t + lr];
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        f4v S = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) S = mfma_k32(sq[16 * t + lr][4 * s + lq], kop[n][s], S);
-        const int key = key0 + 16 * n + lr;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int rr = 16 * t + 4 * lq + j, r = r0 + rr, posr = n0 - w + r / G;
-          // arguments <= 0 wherever the row statistics hold this logit
-          if (r < rows && key <= posr && key < n0) col[n] += fexp2(S[j] * scale2 - sml[rr].x) * sml[rr].y;
-        }
-      }
+      for (int i = 0; i < 32; ++i) acc[i] = fmaf(fexp2(fmaf(S[i / 16][i % 16], scale2, -mi.x)), mi.y, acc[i]);
     }
   }
-  float *votes = reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0;
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    float x = col[n];
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
-    const int key = key0 + 16 * n + lr;
-    if (lq == 0 && key < n0 - w) votes[key] = x;
-  }
+  const float sum = half_wave_sums(acc);
+  const int key = key0 + 32 * (lr / 16) + 8 * ((lr / 4) & 3) + 4 * lh + (lr & 3);
+  if (key < n0 - w) gst(reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0 + key, sum);
 }
 
 // Max pooling of the candidates' votes (odd kernel `pool`, clipped to [0, n0 - w)) into
 // order-preserving keys, one thread per candidate.
-__global__ __launch_bounds__(NT) void k_snap_pool(const SeqDesc *__restrict__ seqs, int seq) {
-  const SeqDesc &sd = seqs[seq];
-  const int n0 = sd.n0, ncand = n0 - sd.w_eff, h = blockIdx.y, half = sd.pool / 2;
-  const int j = blockIdx.x * NT + (int)threadIdx.x;
-  if (j >= ncand) return;
+__global__ __launch_bounds__(NT) void k_snap_pool(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                  int Hkv) {
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, ncand = n0 - sd.w_eff, h = blockIdx.x % Hkv, half = sd.pool / 2;
+  const int j = (int)blockIdx.x / Hkv * NT + (int)threadIdx.x;
+  if (j >= ncand || sd.T >= n0) return;
   const float *votes = reinterpret_cast<const float *>(sd.aux0) + (size_t)h * n0;
   float m = gld(votes + j);
   const int lo = max(0, j - half), hi = min(ncand - 1, j + half);
@@ -582,14 +589,14 @@ __global__ __launch_bounds__(NT) void k_snap_pool(const SeqDesc *__restrict__ se
 }
 
 // Keep the T - w highest pooled votes among the candidates (lower position on a tie) and the w
-// window tokens; gather their rows (and the channel-major key copy) into slots 0..kept-1 in
-// ascending position order.
-template <int D>
-__global__ __launch_bounds__(kTopkThreads) void k_snap_keep(const SeqDesc *__restrict__ seqs, int seq,
-                                                            int32_t *state, int Hkv) {
+// window tokens: their positions into slots 0..kept-1 in ascending order, and the head's state.
+__global__ __launch_bounds__(kTopkThreads) void k_snap_keep(const SeqDesc *__restrict__ seqs,
+                                                            const int32_t *__restrict__ list, int32_t *state,
+                                                            int Hkv) {
   __shared__ SelLds L;
+  const int seq = list[blockIdx.y], h = blockIdx.x;
   const SeqDesc &sd = seqs[seq];
-  const int h = blockIdx.x, n0 = sd.n0, w = sd.w_eff;
+  const int n0 = sd.n0, w = sd.w_eff;
   const bool all = sd.T >= n0;
   const int ncand = n0 - w, want = sd.T - w;
   const int kept = all ? n0 : sd.T;
@@ -603,48 +610,64 @@ __global__ __launch_bounds__(kTopkThreads) void k_snap_keep(const SeqDesc *__res
     }
     for (int i = threadIdx.x; i < w; i += kTopkThreads) pos[want + i] = ncand + i;
   }
-  __syncthreads();
-  // gather: item (16-byte chunk u, slot) with slots consecutive across lanes, so the 2-byte
-  // stores into the channel-major copy are coalesced
+  if (threadIdx.x == 0) {
+    int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
+    st[ST_COUNT] = kept;
+    st[ST_KEPT] = kept;
+  }
+}
+
+// The kept rows and their channel-major key copy, a workgroup per kGatherSlots slots: rows are read
+// and written 16 bytes a lane, the key tile transposed through LDS so that the copy is written 8
+// slots (16 bytes) a lane.  (In the selecting workgroup, one per kv head, with 2-byte stores into the
+// copy, selection and gather of 4 prompts of 32768 tokens took 935 us; 67 apart.)
+template <int D>
+__global__ __launch_bounds__(NT) void k_snap_gather(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
+                                                    int Hkv) {
+  constexpr int U = D / 8, PER = kGatherSlots * U / NT, PITCH = D + 2;  // halves; odd in words
+  __shared__ __attribute__((aligned(16))) uint16_t tile[kGatherSlots * PITCH];
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int h = blockIdx.x % Hkv, s0 = (int)blockIdx.x / Hkv * kGatherSlots, kept = min(sd.T, sd.n0);
+  if (s0 >= kept) return;
+  const int32_t *pos = reinterpret_cast<const int32_t *>(sd.pos) + h * stride_slots(sd);
   const uint16_t *sk = reinterpret_cast<const uint16_t *>(sd.stage_k) + h * stride_stage(sd, D);
   const uint16_t *sv = reinterpret_cast<const uint16_t *>(sd.stage_v) + h * stride_stage(sd, D);
   uint16_t *dk = reinterpret_cast<uint16_t *>(sd.k) + h * stride_rows(sd, D);
   uint16_t *dvv = reinterpret_cast<uint16_t *>(sd.v) + h * stride_rows(sd, D);
   uint16_t *kcm = reinterpret_cast<uint16_t *>(sd.kcm) + h * stride_kcm(sd, D);
-  const int cstride = sd.cstride, total = kept * (D / 8);
-  // batches of kGather items per thread: every position and row load in flight before the stores
-  constexpr int kGather = 8;
-  for (int base = threadIdx.x; base < total; base += kGather * kTopkThreads) {
-    int jj[kGather];
-    uint4 a[kGather], b[kGather];
+  const int u = threadIdx.x % U;
+  int jj[PER];
+  uint4 a[PER], b[PER];
 #pragma unroll
-    for (int q = 0; q < kGather; ++q) {
-      const int it = min(base + q * kTopkThreads, total - 1);
-      jj[q] = gld(pos + it % kept);
-    }
+  for (int k = 0; k < PER; ++k) jj[k] = gld(pos + min(s0 + (int)(threadIdx.x + k * NT) / U, kept - 1));
 #pragma unroll
-    for (int q = 0; q < kGather; ++q) {
-      const int u = min(base + q * kTopkThreads, total - 1) / kept;
-      a[q] = gld16(sk + (size_t)jj[q] * D + 8 * u);
-      b[q] = gld16(sv + (size_t)jj[q] * D + 8 * u);
-    }
-#pragma unroll
-    for (int q = 0; q < kGather; ++q) {
-      const int it = base + q * kTopkThreads;
-      if (it >= total) break;
-      const int u = it / kept, slot = it % kept;
-      *reinterpret_cast<uint4 *>(dk + (size_t)slot * D + 8 * u) = a[q];
-      *reinterpret_cast<uint4 *>(dvv + (size_t)slot * D + 8 * u) = b[q];
-      const uint32_t wv[4] = {a[q].x, a[q].y, a[q].z, a[q].w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        kcm[(size_t)(8 * u + e) * cstride + slot] = (uint16_t)(wv[e / 2] >> (16 * (e & 1)));
-    }
+  for (int k = 0; k < PER; ++k) {
+    a[k] = gld16(sk + (size_t)jj[k] * D + 8 * u);
+    b[k] = gld16(sv + (size_t)jj[k] * D + 8 * u);
   }
-  if (threadIdx.x == 0) {
-    int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
-    st[ST_COUNT] = kept;
-    st[ST_KEPT] = kept;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int rr = (int)(threadIdx.x + k * NT) / U, slot = s0 + rr;
+    uint32_t *t = reinterpret_cast<uint32_t *>(tile + rr * PITCH + 8 * u);
+    t[0] = a[k].x;
+    t[1] = a[k].y;
+    t[2] = a[k].z;
+    t[3] = a[k].w;
+    if (slot >= kept) continue;
+    *reinterpret_cast<uint4 *>(dk + (size_t)slot * D + 8 * u) = a[k];
+    *reinterpret_cast<uint4 *>(dvv + (size_t)slot * D + 8 * u) = b[k];
+  }
+  __syncthreads();
+  // 8 slots of one channel per item, the channels fastest; slots past the kept ones (below the row's
+  // stride, a multiple of 8) repeat the last kept token until an append writes them
+  for (int e = threadIdx.x; e < D * (kGatherSlots / 8); e += NT) {
+    const int c = e % D, o = 8 * (e / D);
+    if (s0 + o >= kept) break;
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      w[i] = (uint32_t)tile[(o + 2 * i) * PITCH + c] | (uint32_t)tile[(o + 2 * i + 1) * PITCH + c] << 16;
+    *reinterpret_cast<uint4 *>(kcm + (size_t)c * sd.cstride + s0 + o) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
@@ -682,20 +705,30 @@ hipError_t h2o_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longe
 }
 
 template <int D>
-hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq, const uint16_t *qw,
+hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *qw,
                              hipStream_t st) {
   const float scale2 = kLog2e / sqrtf((float)D);
-  if (hs.T < hs.n0) {
-    const int nchunk = (hs.n0 + SNAP_CHUNK - 1) / SNAP_CHUNK, rows = hs.w_eff * sh.G;
-    hipLaunchKernelGGL(k_snap_rowstats<D>, dim3(nchunk, sh.Hkv), dim3(NT), 0, st, dv.seqs, seq, qw, sh.Hq, sh.G,
-                       scale2);
-    hipLaunchKernelGGL(k_snap_merge<D>, dim3((rows + NT / 64 - 1) / (NT / 64), sh.Hkv), dim3(NT), 0, st, dv.seqs,
-                       seq, sh.G);
-    hipLaunchKernelGGL(k_snap_votes<D>, dim3(nchunk, sh.Hkv), dim3(NT), 0, st, dv.seqs, seq, qw, sh.Hq, sh.G,
-                       scale2);
-    hipLaunchKernelGGL(k_snap_pool, dim3((hs.n0 - hs.w_eff + NT - 1) / NT, sh.Hkv), dim3(NT), 0, st, dv.seqs, seq);
+  const MethodSeqs &ms = dv.of[ROCKET];
+  const int lg = __builtin_ctz((unsigned)sh.G);
+  const unsigned H = sh.Hkv, chunks = (longest.n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
+  const unsigned rows = (unsigned)ms.max_vote_rows << lg;
+  for (int a = 0; a < ms.n; a += kMaxGridY) {
+    const unsigned n = std::min(ms.n - a, kMaxGridY);
+    const int32_t *list = ms.list + a;
+    if (rows > 0) {  // some sequence keeps less than its prompt
+      hipLaunchKernelGGL(k_snap_rowstats<D>, dim3(H * chunks, n), dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv,
+                         lg, scale2);
+      hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + NT / 64 - 1) / (NT / 64)), n), dim3(NT), 0, st, dv.seqs,
+                         list, sh.Hkv, lg);
+      hipLaunchKernelGGL(k_snap_votes<D>, dim3(H * chunks, n), dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg,
+                         scale2);
+      hipLaunchKernelGGL(k_snap_pool, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list,
+                         sh.Hkv);
+    }
+    hipLaunchKernelGGL(k_snap_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, list, dv.state, sh.Hkv);
+    hipLaunchKernelGGL(k_snap_gather<D>, dim3(H * ((ms.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0,
+                       st, dv.seqs, list, sh.Hkv);
   }
-  hipLaunchKernelGGL(k_snap_keep<D>, dim3(sh.Hkv), dim3(kTopkThreads), 0, st, dv.seqs, seq, dv.state, sh.Hkv);
   return hipGetLastError();
 }
 
@@ -721,10 +754,10 @@ hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc 
   return sh.D == 64 ? h2o_prefill_impl<64>(dv, sh, hs, q_rows, st) : h2o_prefill_impl<128>(dv, sh, hs, q_rows, st);
 }
 
-hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
-                                   const uint16_t *q_window, hipStream_t st) {
-  return sh.D == 64 ? snap_prefill_impl<64>(dv, sh, hs, seq, q_window, st)
-                    : snap_prefill_impl<128>(dv, sh, hs, seq, q_window, st);
+hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *q_window,
+                                   hipStream_t st) {
+  return sh.D == 64 ? snap_prefill_impl<64>(dv, sh, hs, q_window, st)
+                    : snap_prefill_impl<128>(dv, sh, hs, q_window, st);
 }
 
 }  // namespace mkv

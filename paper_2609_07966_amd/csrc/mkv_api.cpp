@@ -262,7 +262,7 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
         d.stage_k = take(H * n0 * D * 2);
         d.stage_v = take(H * n0 * D * 2);
         d.aux0 = take(H * n0 * 4);
-        d.aux1 = take(std::max({H * d.w_eff * G * nchunk * 4 * 8, H * D * 4, H * n0 * 4}));
+        d.aux1 = take(std::max({H * d.w_eff * G * nchunk * 8, H * D * 4, H * n0 * 4}));
         d.q_off = q_rk;
         q_rk += c.window;
         break;
@@ -401,6 +401,7 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
       if (d.method != m) continue;
       L->lists.push_back(s);
       ++ms.n;
+      if (m == ROCKET && d.T < d.n0) ms.max_vote_rows = std::max(ms.max_vote_rows, d.w_eff);
       ms.max_kept = std::max(ms.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
     }
     std::stable_sort(L->lists.end() - ms.n, L->lists.end(),
@@ -715,12 +716,9 @@ mkv_status mkv_snap_prefill_evict(mkv_cache *c, const uint16_t *q_window, void *
     return fail(MKV_ESTATE, "SnapKV prefill eviction runs once, after the prefill append");
   if (!q_window) return fail(MKV_EINVAL, "q_window is NULL");
   hipStream_t hst = static_cast<hipStream_t>(stream);
-  const size_t row = (size_t)c->sh.Hq * c->sh.D;
-  for (int s = 0; s < c->sh.S; ++s) {
-    if (c->hs[s].method != ROCKET) continue;
-    hipError_t e = launch_snap_prefill_seq(c->dv, c->sh, c->hs[s], s, q_window + (size_t)c->hs[s].q_off * row, hst);
-    if (e != hipSuccess) return hip_fail(e, "SnapKV prefill");
-  }
+  const int longest = c->dv.of[ROCKET].longest;
+  hipError_t e = launch_snap_prefill_seq(c->dv, c->sh, c->hs[longest], longest, q_window, hst);
+  if (e != hipSuccess) return hip_fail(e, "SnapKV prefill");
   c->snap_done = true;
   if (!c->any_h2o || c->h2o_done) c->phase = PH_READY;
   return MKV_OK;

@@ -70,7 +70,7 @@ struct SeqDesc {
   uint64_t kcm;             // ROCKET: fp16 [d][cap] channel-major keys
   uint64_t sel, akeys;      // ROCKET: int32 [topk] selected slots; u32 [cap] score keys
   uint64_t aux0, aux1;      // prefill scratch: H2O float [n0] scores, float2 [G][n0] row stats;
-                            // ROCKET float [n0] votes, float2 [G*w][nchunk] partial row stats
+                            // ROCKET float [n0] votes, float2 [w*G][nchunk] partial row stats
   uint64_t colpart;         // H2O prefill scratch: float [nseg][n0] column sums per row segment
 };
 
@@ -147,11 +147,11 @@ constexpr int kScoreSegs = 8;
 // Sequences of one launch over a method's sequences (the grid's y extent).
 constexpr int kMaxGridY = 32768;
 
-// The sequences of one method, longest prompt first, and the most tokens one of them keeps after
-// prefill.
+// The sequences of one method, longest prompt first, the most tokens one of them keeps after prefill,
+// and the most window positions one votes with (0: every one keeps its whole prompt).
 struct MethodSeqs {
   const int32_t *list = nullptr;  // device
-  int n = 0, longest = -1, max_kept = 0;
+  int n = 0, longest = -1, max_kept = 0, max_vote_rows = 0;
 };
 
 // Kernel launchers (defined in the .hip files).  All enqueue on `st`.
@@ -208,6 +208,7 @@ hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *
 // prompt; q_rows: the prompt queries of all of them, in sequence order.
 hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
                                   const uint16_t *q_rows, hipStream_t st);
+// SnapKV of every RocketKV sequence, likewise; q_window: their window queries in sequence order.
 hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
                                    const uint16_t *q_window, hipStream_t st);
 hipError_t launch_init_state(const Dev &dv, const Shape &sh, hipStream_t st);
