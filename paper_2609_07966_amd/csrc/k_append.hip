@@ -489,68 +489,52 @@ __global__ __launch_bounds__(kTopkThreads) void k_rocket_select(const SeqDesc *_
   }
 }
 
-// ---- prefill -----------------------------------------------------------------------------------
+// ---- prefill: every sequence of a method in one launch per stage ---------------------------------
+// Grid: x = kv head (fastest) x blocks of the longest prompt, y = sequence (longest first);
+// workgroups past a shorter prompt's end leave at once.  Launches per sequence left the chip idle
+// between them: a 20-sequence batch of 100-700 tokens enqueued about 100 of them, most under 5 us.
 
-// Copy prompt rows [n0][Hkv][D] (input layout) into per-head rows [Hkv][n0 or cap][D].
+// The state of (seq, h) after the append of an n0-token prompt; `count` tokens are held (0 until a
+// prefill selection has chosen them).
+MKV_DEV void write_prompt_state(int32_t *state, int seq, int h, int Hkv, int n0, int count) {
+  int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
+  st[ST_COUNT] = count;
+  st[ST_NEXT_POS] = n0;
+  st[ST_FREE_SLOT] = 0;
+  st[ST_KEPT] = n0;
+}
+
+// Copy prompt rows [n0][Hkv][D] (input layout) into per-head rows: a sequence's cache (FP16) or its
+// staging (H2O, RocketKV).
 template <int D>
-__global__ void k_prefill_copy(const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
-                               uint16_t *dk, uint16_t *dv, int64_t head_stride, int n0, int Hkv) {
+__global__ __launch_bounds__(256) void k_prefill_copy(const SeqDesc *__restrict__ seqs,
+                                                      const int32_t *__restrict__ list, int32_t *state,
+                                                      const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+                                                      int Hkv) {
+  const int seq = list[blockIdx.y];
+  const SeqDesc &sd = seqs[seq];
+  const int n0 = sd.n0;
+  const bool staged = sd.method != FP16;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // one 16-byte chunk
   const int64_t total = (int64_t)n0 * Hkv * (D / 8);
   if (i >= total) return;
   const int ch = (int)(i % (D / 8));
   const int h = (int)((i / (D / 8)) % Hkv);
   const int64_t t = i / ((D / 8) * Hkv);
-  const uint4 a = reinterpret_cast<const uint4 *>(k)[i];
-  const uint4 b = reinterpret_cast<const uint4 *>(v)[i];
-  *reinterpret_cast<uint4 *>(dk + h * head_stride + t * D + ch * 8) = a;
-  *reinterpret_cast<uint4 *>(dv + h * head_stride + t * D + ch * 8) = b;
+  if (t == 0 && ch == 0) write_prompt_state(state, seq, h, Hkv, n0, staged ? 0 : n0);
+  const int64_t first = (int64_t)sd.row0 * Hkv * (D / 8);
+  const uint4 a = reinterpret_cast<const uint4 *>(k)[first + i];
+  const uint4 b = reinterpret_cast<const uint4 *>(v)[first + i];
+  const int64_t at = h * (staged ? stride_stage(sd, D) : stride_rows(sd, D)) + t * D + ch * 8;
+  *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(staged ? sd.stage_k : sd.k) + at) = a;
+  *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(staged ? sd.stage_v : sd.v) + at) = b;
 }
 
-// UQ prompt values: one workgroup per (4-token block, kv head).
-template <int D>
-__global__ __launch_bounds__(128) void k_prefill_uq_values(const SeqDesc *__restrict__ seqs, int seq,
-                                                          const uint16_t *__restrict__ v, int Hkv, int n0) {
-  __shared__ uint32_t s_blk[D / 2];
-  const SeqDesc &sd = seqs[seq];
-  const int q = blockIdx.x, h = blockIdx.y, c = threadIdx.x;
-  for (int w = c; w < D / 2; w += D) s_blk[w] = 0;
-  __syncthreads();
-  for (int j = 0; j < 4 && 4 * q + j < n0; ++j) {
-    const int t = 4 * q + j;
-    const int code = uq_value_token<D>(sd, h, t, v[((size_t)t * Hkv + h) * D + c]);
-    or_uq_code(s_blk, c, j, code, D);
-  }
-  __syncthreads();
-  store_block<D>(reinterpret_cast<uint8_t *>(sd.vc), (int)stride_codes(sd), h, 4 * q, sd.rowbytes, s_blk, D / 2);
-}
-
-template <int D>
-__global__ __launch_bounds__(128) void k_prefill_uq_keys(const SeqDesc *__restrict__ seqs, int seq,
-                                                        const uint16_t *__restrict__ k, int Hkv, int n0) {
-  const SeqDesc &sd = seqs[seq];
-  const int blk = blockIdx.x, h = blockIdx.y, c = threadIdx.x;
-  const int nfull = n0 / 64;
-  if (blk < nfull) {
-    uq_key_block<D>(sd, h, blk, [&](int t) { return (uint32_t)k[((size_t)(blk * 64 + t) * Hkv + h) * D + c]; });
-  } else {
-    uint16_t *res = reinterpret_cast<uint16_t *>(sd.kres) + (size_t)h * 64 * D;
-    for (int t = nfull * 64; t < n0; ++t) res[(size_t)(t & 63) * D + c] = k[((size_t)t * Hkv + h) * D + c];
-  }
-}
-
-// ---- KVQ prompts: every KVQ sequence in one launch per stage ------------------------------------
-// Grid: x = kv head (fastest) x blocks of the longest prompt, y = sequence (longest first);
-// workgroups past a shorter prompt's end leave at once.  Lanes take 8 consecutive channels of a token
-// (one 16-byte load), LT = D / 8 lanes a token, so that reductions over a token's channels are 3 or 4
-// DPP steps for 4 or 8 tokens at once and codes pack within a lane.  8 prompts of 3000-6000 tokens
-// (8 kv heads x 128), where launches per sequence, one workgroup per token (keys) or 4-token block
-// (values) and 16 workgroups per calibration stood before: thresholds 1176 -> 58 us, key codes and
-// outliers 364 -> 54, values 201 -> 57, scan 72 -> 5.  Reading K or V once takes 15 us here; the
-// codes' compares bound the quantizing kernels, LDS atomics and load latency the calibration.
-
-constexpr int kKvqThreads = 256;
-constexpr int kKvqTokens = 64;  // tokens per workgroup of the quantizing kernels
+// In the quantizing kernels lanes take 8 consecutive channels of a token (one 16-byte load), LT = D / 8
+// lanes a token, so that reductions over a token's channels are 3 or 4 DPP steps for 4 or 8 tokens at
+// once and codes pack within a lane.
+constexpr int kQuantThreads = 256;
+constexpr int kQuantTokens = 64;  // tokens per workgroup
 
 template <int LT, typename Op>
 MKV_DEV float lane_group_reduce(float x, Op op) {  // over aligned groups of LT (8 or 16) lanes
@@ -580,6 +564,158 @@ MKV_DEV int lane_group_before(int x) {
   }
   return inc - x;
 }
+
+// ---- uniform 4-bit prompts ------------------------------------------------------------------------
+// 6 prompts of 1.6-23 thousand tokens (8 kv heads x 128; 230 MB of K and V): 66 + 40 us, against
+// 176 + 138 with launches per sequence, one 128-thread workgroup per 4-token value block and key blocks
+// read twice at 2 bytes a lane.
+
+// The clamped 4-bit code of x in a group of minimum mn.
+MKV_DEV int uq_code(float x, float mn, float inv) {
+  return (int)fminf(fmaxf(rintf(__fmul_rn(__fsub_rn(x, mn), inv)), 0.f), 15.f);
+}
+
+// Key blocks of 64 tokens, a workgroup each: per-channel (min, step) over the block's tokens (in the
+// lane, across the wave's lane groups, then the waves), codes of a lane's 8 channels as one word of the
+// token's row.  The last workgroup of a head copies the incomplete block's rows and writes the state.
+template <int D>
+__global__ __launch_bounds__(kQuantThreads) void k_uq_keys(const SeqDesc *__restrict__ seqs,
+                                                           const int32_t *__restrict__ list, int32_t *state,
+                                                           const uint16_t *__restrict__ k, int Hkv) {
+  constexpr int LT = D / 8, NW = kQuantThreads / 64, TPI = kQuantThreads / LT, NI = kQuantTokens / TPI;
+  __shared__ float2 s_mm[NW][D];
+  const int seq = list[blockIdx.y];
+  const SeqDesc &sd = seqs[seq];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, blk = (int)blockIdx.x / Hkv, nfull = n0 / 64;
+  if (blk > nfull) return;
+  const int l = threadIdx.x % LT, tl = threadIdx.x / LT, wave = threadIdx.x >> 6;
+  const uint16_t *kp = k + ((size_t)(sd.row0 + 64 * blk) * Hkv + h) * D + 8 * l;
+  if (blk == nfull) {
+    uint16_t *res = reinterpret_cast<uint16_t *>(sd.kres) + (size_t)h * 64 * D;
+    for (int t = tl; t < n0 - 64 * nfull; t += TPI)
+      *reinterpret_cast<uint4 *>(res + t * D + 8 * l) = gld16h(kp + (size_t)t * Hkv * D);
+    if (threadIdx.x == 0) write_prompt_state(state, seq, h, Hkv, n0, n0);
+    return;
+  }
+  uint4 w[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) w[i] = gld16h(kp + (size_t)(i * TPI + tl) * Hkv * D);
+  float mn[8], mx[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    mn[e] = INFINITY;
+    mx[e] = -INFINITY;
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    float x[8];
+    unpack8(w[i], x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      mn[e] = fminf(mn[e], x[e]);
+      mx[e] = fmaxf(mx[e], x[e]);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+#pragma unroll
+    for (int o = LT; o < 64; o <<= 1) {
+      mn[e] = fminf(mn[e], __shfl_xor(mn[e], o));
+      mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], o));
+    }
+    if ((int)(threadIdx.x & 63) < LT) s_mm[wave][8 * l + e] = make_float2(mn[e], mx[e]);
+  }
+  __syncthreads();
+  float inv[8];
+  float2 *meta = reinterpret_cast<float2 *>(sd.kmeta) + h * stride_uq_kmeta(sd, D) + (size_t)blk * D;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float2 m = s_mm[0][8 * l + e];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) {
+      const float2 o = s_mm[v][8 * l + e];
+      m = make_float2(fminf(m.x, o.x), fmaxf(m.y, o.y));
+    }
+    const float r = __fsub_rn(m.y, m.x);
+    mn[e] = m.x;
+    inv[e] = r > 0.f ? __fdiv_rn(15.0f, r) : 0.f;
+    if (tl == 0) meta[8 * l + e] = make_float2(m.x, __fdiv_rn(r, 15.0f));
+  }
+  uint8_t *rows = reinterpret_cast<uint8_t *>(sd.kc) + h * stride_codes(sd) + (size_t)blk * 64 * (D / 2);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    float x[8];
+    unpack8(w[i], x);
+    uint32_t word = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) word |= (uint32_t)uq_code(x[e], mn[e], inv[e]) << (4 * e);
+    gst(reinterpret_cast<uint32_t *>(rows + (size_t)(i * TPI + tl) * (D / 2)) + l, word);
+  }
+}
+
+// Values: 64-channel groups (8 lanes), codes in 4-token blocks in the attention's operand order
+// (uq_vbit): a lane's 8 channels are two words of each of two segments, the four tokens' nibbles OR-ed
+// across their lanes.
+template <int D>
+__global__ __launch_bounds__(kQuantThreads) void k_uq_values(const SeqDesc *__restrict__ seqs,
+                                                             const int32_t *__restrict__ list,
+                                                             const uint16_t *__restrict__ v, int Hkv) {
+  constexpr int LT = D / 8, TPI = kQuantThreads / LT, NI = kQuantTokens / TPI;
+  const SeqDesc &sd = seqs[list[blockIdx.y]];
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kQuantTokens * (int)(blockIdx.x / Hkv);
+  if (t0 >= n0) return;
+  const int l = threadIdx.x % LT, tl = threadIdx.x / LT, j = tl & 3, gr = l / 8;
+  const uint16_t *vp = v + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
+  uint8_t *blocks = reinterpret_cast<uint8_t *>(sd.vc) + h * stride_codes(sd);
+  float2 *meta = reinterpret_cast<float2 *>(sd.vmeta) + h * stride_uq_vmeta(sd, D);
+  uint4 nx = gld16h(vp + (size_t)min(t0 + tl, n0 - 1) * Hkv * D);
+#pragma unroll 1
+  for (int i = 0; i < NI; ++i) {
+    const int t = t0 + i * TPI + tl;
+    const uint4 w = nx;
+    if (i + 1 < NI) nx = gld16h(vp + (size_t)min(t + TPI, n0 - 1) * Hkv * D);
+    float x[8];
+    unpack8(w, x);
+    float mn = x[0], mx = x[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) {
+      mn = fminf(mn, x[e]);
+      mx = fmaxf(mx, x[e]);
+    }
+    mn = lane_group_reduce<8>(mn, [](float a, float b) { return fminf(a, b); });
+    mx = lane_group_reduce<8>(mx, [](float a, float b) { return fmaxf(a, b); });
+    const float r = __fsub_rn(mx, mn);
+    const float inv = r > 0.f ? __fdiv_rn(15.0f, r) : 0.f;
+    // channels 8 l .. 8 l + 3 and + 4 .. + 7: segments 2 (l % 8) and + 1, words 2 gr and + 1 of each;
+    // token j's nibble of channel parity b is 2 b + 4 (j % 2) + j / 2
+    const int sh = 4 * (4 * (j & 1) + (j >> 1));
+    uint32_t word[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t c0 = (uint32_t)uq_code(x[2 * q], mn, inv), c1 = (uint32_t)uq_code(x[2 * q + 1], mn, inv);
+      word[q] = t < n0 ? (c0 | c1 << 8) << sh : 0u;
+    }
+    uint32_t mine = 0;  // lane group j stores word j
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      word[q] |= (uint32_t)__shfl_xor((int)word[q], LT);
+      word[q] |= (uint32_t)__shfl_xor((int)word[q], 2 * LT);
+      mine = j == q ? word[q] : mine;
+    }
+    if (t - j < n0)
+      gst(reinterpret_cast<uint32_t *>(blocks + (size_t)(t - j) * sd.rowbytes) + (2 * (l % 8) + (j >> 1)) * (D / 32) +
+              2 * gr + (j & 1),
+          mine);
+    if (t < n0 && l % 8 == 0) meta[(size_t)t * (D / 64) + gr] = make_float2(mn, __fdiv_rn(r, 15.0f));
+  }
+}
+
+// ---- KVQ prompts ----------------------------------------------------------------------------------
+// 8 prompts of 3000-6000 tokens (8 kv heads x 128), where launches per sequence, one workgroup per
+// token (keys) or 4-token block (values) and 16 workgroups per calibration stood before: thresholds
+// 1176 -> 58 us, key codes and outliers 364 -> 54, values 201 -> 57, scan 72 -> 5.  Reading K or V once
+// takes 15 us here; the codes' compares bound the quantizing kernels, LDS atomics and load latency the
+// calibration.
 
 // KVQ key thresholds: the n_o-th largest |k| (0-based) of every channel over the prompt, by a
 // two-pass radix select on the 15-bit fp16 magnitude.  A workgroup takes 32 channels of one kv head;
@@ -693,13 +829,13 @@ MKV_DEV void load_tau8(const SeqDesc &sd, int h, int c, int D, float (&tau)[8], 
 
 // KVQ prompt keys: codes, and each token's outlier count into krow[t + 1].
 template <int D>
-__global__ __launch_bounds__(kKvqThreads) void k_kvq_keys(const SeqDesc *__restrict__ seqs,
+__global__ __launch_bounds__(kQuantThreads) void k_kvq_keys(const SeqDesc *__restrict__ seqs,
                                                           const int32_t *__restrict__ list,
                                                           const uint16_t *__restrict__ k,
                                                           const float *__restrict__ cbtab, int Hkv) {
-  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kQuantThreads / 64, NI = kQuantTokens / TPI;
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kQuantTokens * (int)(blockIdx.x / Hkv);
   if (t0 >= n0) return;
   const int l = threadIdx.x % LT, tl = threadIdx.x / LT;
   const uint16_t *kp = k + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
@@ -767,23 +903,20 @@ __global__ __launch_bounds__(kScanThreads) void k_kvq_scan(const SeqDesc *__rest
   }
   if (threadIdx.x == 0) {
     krow[0] = 0;
-    int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
-    st[ST_KOUT_FILL] = run;
-    st[ST_COUNT] = n0;
-    st[ST_NEXT_POS] = n0;
-    st[ST_KEPT] = n0;
+    write_prompt_state(state, seq, h, Hkv, n0, n0);
+    state[((size_t)seq * Hkv + h) * ST_WORDS + ST_KOUT_FILL] = run;
   }
 }
 
 // KVQ prompt keys: the outlier entries at their CSR offsets, ascending channels; codes come from the
 // rows that k_kvq_keys wrote.
 template <int D>
-__global__ __launch_bounds__(kKvqThreads) void k_kvq_outliers(const SeqDesc *__restrict__ seqs,
+__global__ __launch_bounds__(kQuantThreads) void k_kvq_outliers(const SeqDesc *__restrict__ seqs,
                                                               const int32_t *__restrict__ list,
                                                               const uint16_t *__restrict__ k, int Hkv) {
-  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kQuantThreads / 64, NI = kQuantTokens / TPI;
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kQuantTokens * (int)(blockIdx.x / Hkv);
   if (t0 >= n0 || sd.bp <= 0) return;
   const int l = threadIdx.x % LT, tl = threadIdx.x / LT;
   const uint16_t *kp = k + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
@@ -826,13 +959,13 @@ __global__ __launch_bounds__(kKvqThreads) void k_kvq_outliers(const SeqDesc *__r
 // the outliers, whose slots go by ascending channel.  A wave holds whole 4-token blocks: the four
 // tokens' codes of a lane's 8 channels are BITS words of the block, OR-ed across their lanes.
 template <int D>
-__global__ __launch_bounds__(kKvqThreads) void k_kvq_values(const SeqDesc *__restrict__ seqs,
+__global__ __launch_bounds__(kQuantThreads) void k_kvq_values(const SeqDesc *__restrict__ seqs,
                                                             const int32_t *__restrict__ list,
                                                             const uint16_t *__restrict__ v,
                                                             const float *__restrict__ cbtab, int Hkv) {
-  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kKvqThreads / 64, NI = kKvqTokens / TPI;
+  constexpr int LT = D / 8, TPW = 64 / LT, TPI = TPW * kQuantThreads / 64, NI = kQuantTokens / TPI;
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kKvqTokens * (int)(blockIdx.x / Hkv);
+  const int n0 = sd.n0, h = blockIdx.x % Hkv, t0 = kQuantTokens * (int)(blockIdx.x / Hkv);
   if (t0 >= n0) return;
   const int l = threadIdx.x % LT, tl = threadIdx.x / LT, j = tl & 3;
   const uint16_t *vp = v + ((size_t)sd.row0 * Hkv + h) * D + 8 * l;
@@ -928,18 +1061,6 @@ __global__ __launch_bounds__(kKvqThreads) void k_kvq_values(const SeqDesc *__res
   else run(std::integral_constant<int, 2>{});
 }
 
-__global__ void k_prefill_state(const SeqDesc *__restrict__ seqs, int seq, int32_t *state, int Hkv) {
-  const SeqDesc &sd = seqs[seq];
-  const int h = threadIdx.x;
-  if (h >= Hkv) return;
-  int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
-  const bool staged = sd.method == H2O || sd.method == ROCKET;
-  st[ST_COUNT] = staged ? 0 : sd.n0;
-  st[ST_NEXT_POS] = sd.n0;
-  st[ST_FREE_SLOT] = 0;
-  st[ST_KEPT] = sd.n0;
-}
-
 __global__ void k_init_state(int32_t *state, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) state[i] = 0;
@@ -964,47 +1085,41 @@ hipError_t append_select_impl(const Dev &dv, const Shape &sh, const uint16_t *k,
 }
 
 template <int D>
-hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq, const uint16_t *k,
-                        const uint16_t *v, hipStream_t st) {
-  const int n0 = hs.n0, Hkv = sh.Hkv;
-  if (hs.method != KVQ)  // (the KVQ scan writes it)
-    hipLaunchKernelGGL(k_prefill_state, dim3(1), dim3(64 * ((Hkv + 63) / 64)), 0, st, dv.seqs, seq, dv.state, Hkv);
-  switch (hs.method) {
-    case FP16:
-    case H2O:
-    case ROCKET: {
-      const bool staged = hs.method != FP16;
-      uint16_t *dk = reinterpret_cast<uint16_t *>(staged ? hs.stage_k : hs.k);
-      uint16_t *dvp = reinterpret_cast<uint16_t *>(staged ? hs.stage_v : hs.v);
-      const int64_t hstride = staged ? stride_stage(hs, D) : stride_rows(hs, D);
-      const int64_t chunks = (int64_t)n0 * Hkv * (D / 8);
-      hipLaunchKernelGGL(k_prefill_copy<D>, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, k, v,
-                         dk, dvp, hstride, n0, Hkv);
-      break;
-    }
-    case UQ:
-      hipLaunchKernelGGL(k_prefill_uq_values<D>, dim3((n0 + 3) / 4, Hkv), dim3(D), 0, st, dv.seqs, seq, v, Hkv, n0);
-      hipLaunchKernelGGL(k_prefill_uq_keys<D>, dim3(n0 / 64 + 1, Hkv), dim3(D), 0, st, dv.seqs, seq, k, Hkv, n0);
-      break;
-    case KVQ: {
-      const unsigned H = sh.Hkv, blocks = (n0 + kKvqTokens - 1) / kKvqTokens;
-      for (int a = 0; a < dv.of[KVQ].n; a += kMaxGridY) {
-        const unsigned n = std::min(dv.of[KVQ].n - a, kMaxGridY);
-        const int32_t *list = dv.of[KVQ].list + a;
+hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *k, const uint16_t *v,
+                        hipStream_t st) {
+  const int Hkv = sh.Hkv;
+  const unsigned H = Hkv, blocks = (longest.n0 + kQuantTokens - 1) / kQuantTokens;
+  const MethodSeqs &ms = dv.of[longest.method];
+  for (int a = 0; a < ms.n; a += kMaxGridY) {
+    const unsigned n = std::min(ms.n - a, kMaxGridY);
+    const int32_t *list = ms.list + a;
+    switch (longest.method) {
+      case FP16:
+      case H2O:
+      case ROCKET: {
+        const int64_t chunks = (int64_t)longest.n0 * Hkv * (D / 8);
+        hipLaunchKernelGGL(k_prefill_copy<D>, dim3((unsigned)((chunks + 255) / 256), n), dim3(256), 0, st, dv.seqs,
+                           list, dv.state, k, v, Hkv);
+        break;
+      }
+      case UQ:
+        hipLaunchKernelGGL(k_uq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, v, Hkv);
+        hipLaunchKernelGGL(k_uq_keys<D>, dim3(H * (longest.n0 / 64 + 1), n), dim3(kQuantThreads), 0, st, dv.seqs,
+                           list, dv.state, k, Hkv);
+        break;
+      case KVQ:
         hipLaunchKernelGGL(k_kvq_calibrate<D>, dim3(H * (D / kCalibChannels), n), dim3(kCalibThreads), 0, st, dv.seqs,
                            list, k, Hkv);
-        hipLaunchKernelGGL(k_kvq_keys<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, k, dv.cbtab,
+        hipLaunchKernelGGL(k_kvq_keys<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, k, dv.cbtab,
                            Hkv);
         hipLaunchKernelGGL(k_kvq_scan, dim3(H, n), dim3(kScanThreads), 0, st, dv.seqs, list, dv.state, Hkv);
-        hipLaunchKernelGGL(k_kvq_outliers<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, k,
-                           Hkv);
-        hipLaunchKernelGGL(k_kvq_values<D>, dim3(H * blocks, n), dim3(kKvqThreads), 0, st, dv.seqs, list, v, dv.cbtab,
-                           Hkv);
-      }
-      break;
+        hipLaunchKernelGGL(k_kvq_outliers<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, k, Hkv);
+        hipLaunchKernelGGL(k_kvq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, v,
+                           dv.cbtab, Hkv);
+        break;
+      default:
+        return hipErrorInvalidValue;
     }
-    default:
-      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -1031,9 +1146,9 @@ hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *
   }
 }
 
-hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq, const uint16_t *k,
+hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *k,
                               const uint16_t *v, hipStream_t st) {
-  return sh.D == 64 ? prefill_impl<64>(dv, sh, hs, seq, k, v, st) : prefill_impl<128>(dv, sh, hs, seq, k, v, st);
+  return sh.D == 64 ? prefill_impl<64>(dv, sh, hs, k, v, st) : prefill_impl<128>(dv, sh, hs, k, v, st);
 }
 
 hipError_t launch_init_state(const Dev &dv, const Shape &sh, hipStream_t st) {

@@ -669,12 +669,9 @@ mkv_status mkv_append_quantize(mkv_cache *c, const uint16_t *k, const uint16_t *
       if (cu_new[s + 1] - cu_new[s] != c->hs[s].n0)
         return fail(MKV_EINVAL, "prefill: seq %d appends %d rows, prompt_len is %d", s, cu_new[s + 1] - cu_new[s],
                     c->hs[s].n0);
-    const size_t row = (size_t)c->sh.Hkv * c->sh.D;
-    for (int s = 0; s < S; ++s) {
-      const bool all = c->hs[s].method == KVQ;  // one call over the method's sequences
-      if (all && s != c->dv.of[KVQ].longest) continue;
-      const size_t first = all ? 0 : (size_t)cu_new[s] * row;
-      hipError_t e = launch_prefill_seq(c->dv, c->sh, c->hs[s], s, k + first, v + first, hst);
+    for (const MethodSeqs &ms : c->dv.of) {
+      if (ms.n == 0) continue;
+      hipError_t e = launch_prefill_seq(c->dv, c->sh, c->hs[ms.longest], ms.longest, k, v, hst);
       if (e != hipSuccess) return hip_fail(e, "prefill append");
     }
     c->phase = (c->any_h2o || c->any_rocket) ? PH_PROMPT : PH_READY;

@@ -181,8 +181,8 @@ struct LaunchEv {
 // H2O pairs whose last attention pass chose a victim write the token into its slot.
 hipError_t launch_append_decode(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                                 hipStream_t st, LaunchEv ev = {});
-// The prompt append of sequence `seq`, whose rows start at k and v; for KVQ of every KVQ sequence
-// (hs, seq: the one with the longest prompt; k, v: the whole batch's rows).
+// The prompt append of every sequence of one method, one launch per stage; hs, seq: the method's
+// sequence with the longest prompt; k, v: the whole batch's rows.
 hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
                               const uint16_t *k, const uint16_t *v, hipStream_t st);
 hipError_t launch_attention_partial(const Dev &dv, const Shape &sh, const uint16_t *q, hipStream_t st,

@@ -158,3 +158,62 @@ def test_snap_prompts_at_chunk_edges(hkv, g, d, window, pool):
             assert np.abs(out[s, hq] - ref).max() <= TOL * rms, where
         at += m
     c.close()
+
+
+@pytest.mark.parametrize("hkv,g,d", [(1, 2, 128), (3, 4, 64), (2, 1, 128)])
+def test_uniform_prompts_at_block_edges(hkv, g, d):
+    """Ragged uniform 4-bit prompts beside fp16 ones, quantized together: codes and (min, step) pairs bit
+    for bit, with lengths around the 4-token value blocks and the 64-token key blocks, constant groups
+   ; then a decode step over the incomplete blocks' rows."""
+    import torch
+    from gpu_harness import TOL
+    from oracle import uniform
+    from paper_2609_07966_amd.cache import KVCache
+    lens = [1, 3, 63, 64, 65, 100, 128, 190, 257]
+    cfgs = [{"method": "uq", "bits": 4, "group": 64} if s % 4 else {"method": "fp16"} for s in range(len(lens))]
+    r = np.random.default_rng(d + g)
+    n, S = sum(lens), len(lens)
+    k = (r.standard_normal((n, hkv, d)) * np.exp(r.standard_normal((hkv, d)))).astype(np.float16)
+    v = r.standard_normal((n, hkv, d)).astype(np.float16)
+    k[:, :, 5] = 0.25
+    v[2::9] = -1.5
+
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    c = KVCache((S, hkv * g, hkv, d, 1), cfgs, lens)
+    c.append_prompt(dev(k), dev(v))
+    at = 0
+    for s, m in enumerate(lens):
+        for h in range(hkv):
+            assert c.counts(s, h) == (m, m, m, m)
+            if cfgs[s]["method"] != "uq":
+                continue
+            kp, vp, where = k[at:at + m, h], v[at:at + m, h], f"sequence {s} ({m} tokens) head {h}"
+            cv, mn, rng = uniform.quantize_value_rows(vp, 4)
+            np.testing.assert_array_equal(c.export(s, h, "codes_v").reshape(m, d), cv, err_msg=where)
+            sv = c.export(s, h, "scales_v").reshape(m, d // 64, 2)
+            np.testing.assert_array_equal(sv[..., 0], mn, err_msg=where)
+            np.testing.assert_array_equal(sv[..., 1], (rng / np.float32(15)).astype(np.float32), err_msg=where)
+            nb = m // 64
+            gk = c.export(s, h, "codes_k").reshape(-1, d)
+            assert gk.shape[0] == 64 * nb
+            if nb:
+                ck, mn, rng = uniform.quantize_key_blocks(kp, 4)
+                np.testing.assert_array_equal(gk, ck, err_msg=where)
+                sk = c.export(s, h, "scales_k").reshape(nb, d, 2)
+                np.testing.assert_array_equal(sk[..., 0], mn, err_msg=where)
+                np.testing.assert_array_equal(sk[..., 1], (rng / np.float32(15)).astype(np.float32), err_msg=where)
+        at += m
+    kn, vn = (r.standard_normal((S, hkv, d)).astype(np.float16) for _ in range(2))
+    q = r.standard_normal((S, hkv * g, d)).astype(np.float16)
+    out = torch.empty((S, hkv * g, d), dtype=torch.float32, device="cuda")
+    c.step(dev(kn), dev(vn), dev(q), out)
+    out = out.cpu().numpy()
+    from oracle.sequence import Sequence
+    at = 0
+    for s, m in enumerate(lens):
+        seq = Sequence(cfgs[s], k[at:at + m], v[at:at + m], hkv * g)
+        ref, _ = seq.step(kn[s], vn[s], q[s])
+        rms = np.sqrt(np.mean(v[at:at + m].astype(np.float64) ** 2))
+        assert np.abs(out[s] - ref).max() <= TOL * max(rms, 1.0), f"sequence {s} ({m} tokens)"
+        at += m
+    c.close()
