@@ -106,7 +106,6 @@ struct MG {
   static constexpr int NM = D / 16;   // MFMAs per 16-token step, for q.k and for p.v
   static constexpr int CPL = D / 4;   // key channels per lane
   static constexpr int VPL = D / 16;  // value channels per lane
-  static constexpr int NS = 2;        // 16-token steps per batch
 };
 
 template <int G>
@@ -127,9 +126,6 @@ struct QB {
 template <int D, int G, bool GATHER>
 struct MRows {
   static constexpr int NM = MG<D>::NM, CPL = MG<D>::CPL, VPL = MG<D>::VPL;
-  static constexpr int NS = MG<D>::NS;
-  static constexpr bool kSplit = false;   // q and p enter as single fp16 parts
-  static constexpr bool kScaled = false;  // logits still need the log2(e)/sqrt(d) factor
   const uint16_t *K, *V;
   const int32_t *sel;
   int lr, lq;
@@ -137,22 +133,7 @@ struct MRows {
     uint32_t kw[CPL / 2];
     uint32_t vw[4][VPL / 2];
   };
-  struct Batch {};
-  // Gather: the slots of the next batch, loaded one batch ahead so that row loads never wait
-  // for their index loads
-  struct Carry {
-    int ks[MG<D>::NS], vs[MG<D>::NS][4];
-  };
   MKV_DEV int slot_of(int t) const { return GATHER ? gld(sel + t) : t; }
-  MKV_DEV void carry(int base, int b, Carry &cy) const {
-    if (!GATHER) return;
-#pragma unroll
-    for (int s = 0; s < MG<D>::NS; ++s) {
-      cy.ks[s] = gld(sel + min(base + 16 * s + lr, b - 1));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cy.vs[s][j] = gld(sel + min(base + 16 * s + 4 * lq + j, b - 1));
-    }
-  }
   MKV_DEV void load_rows(int ks, const int (&vs)[4], Raw &r) const {
     // 16-byte pieces at channels 32 i + 8 lq (i < D / 32)
     const uint32_t *kp = reinterpret_cast<const uint32_t *>(K + (size_t)ks * D + 8 * lq);
@@ -173,36 +154,12 @@ struct MRows {
 #pragma unroll
     for (int j = 0; j < 4; ++j) vs[j] = slot_of(min(base + 4 * lq + j, b - 1));
   }
-  // step s: FULL: all 16 tokens of the step exist; otherwise indices past the end re-read the
-  // last one
-  template <bool FULL>
-  MKV_DEV void fetch(int base, int b, int s, const Carry &cy, Raw &r) const {
-    int ks, vs[4];
-    if (GATHER) {
-      ks = cy.ks[s];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) vs[j] = cy.vs[s][j];
-    } else {
-      ks = FULL ? base + lr : min(base + lr, b - 1);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) vs[j] = FULL ? base + 4 * lq + j : min(base + 4 * lq + j, b - 1);
-    }
-    load_rows(ks, vs, r);
-  }
-  MKV_DEV void batch_fetch(const Carry &, Batch &) const {}
-  MKV_DEV void batch_fix(const Batch &) const {}
-  // slot of this lane's token j of the step at `base` (rows only: the logit store of H2O)
-  MKV_DEV int slot(int base, const Raw &, int j) const { return base + 4 * lq + j; }
   MKV_DEV void qk(const Raw &r, const QB<D> &qb, f4v &S) const {
 #pragma unroll
     for (int m = 0; m < NM; ++m) S = mfma16(mk_h4(r.kw[2 * m], r.kw[2 * m + 1]), qb.b[m], S);
   }
-  MKV_DEV void kfix(int, float (&)[4]) const {}
-  MKV_DEV float vscale(const Raw &, int) const { return 1.f; }
-  MKV_DEV void vfix(const Raw &, const float (&)[4], const float (&)[4], int) const {}
-  MKV_DEV void prep(int, QB<D> &) {}
   MKV_DEV void rescale(float) const {}
-  MKV_DEV void pv(const Raw &r, const float (&)[4], const float (&pp)[4], int, f4v (&O)[NM]) const {
+  MKV_DEV void pv(const Raw &r, const float (&pp)[4], f4v (&O)[NM]) const {
     const h4v P = mk_h4(pk_f16(pp[0], pp[1]), pk_f16(pp[2], pp[3]));
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
@@ -224,8 +181,6 @@ template <int D, int G, int BITS>
 struct MKVQ {
   static constexpr int NM = MG<D>::NM, CPL = MG<D>::CPL, VPL = MG<D>::VPL;
   static constexpr int NS = 2;           // 32-token batches (the key-outlier tags are slot mod 32)
-  static constexpr bool kSplit = true;   // fp16 residual of q' in columns G..2G-1
-  static constexpr bool kScaled = true;  // q' carries log2(e)/sqrt(d)
   static constexpr int SEG = CPL * BITS;  // bits per lane segment (keys; values alike)
   // words per segment: a segment starts at bit SEG * lane_index, which is word aligned unless
   // SEG = 48 (d = 64, 3 bits), where it starts at bit 0 or 16 of a word and still spans 2 words
@@ -312,7 +267,7 @@ struct MKVQ {
     r.vd[3] = e.w;
   }
   // lane l takes entry l of the batch's key-outlier range
-  MKV_DEV void batch_fetch(const Carry &cy, Batch &bt) const {
+  MKV_DEV void batch_fetch(int, const Carry &cy, Batch &bt) const {
     bt.kr = cy.kr;
     const uint32_t e0 = __builtin_amdgcn_readlane(cy.kr, 0), e1 = __builtin_amdgcn_readlane(cy.kr, 32);
     const uint32_t e = e0 + (threadIdx.x & 63);
@@ -358,7 +313,6 @@ struct MKVQ {
       for (int g = 0; g < G; ++g) kcorr[g * KCS + lane] = acc[g];
     }
   }
-  MKV_DEV int slot(int, const Raw &r, int j) const { return r.t0 + j; }
   MKV_DEV void qk(const Raw &r, const QB<D> &qb, f4v &S) const {
 #pragma unroll
     for (int m = 0; m < NM; ++m) S = mfma16(operand(lutk, r.kw, m), qb.b[m], S);
@@ -452,8 +406,6 @@ struct MUQ {
   static constexpr int NGRP = D / 64;     // value groups
   static constexpr int KW = RES ? CPL / 2 : CPL / 8;  // key words per lane and step
   static constexpr int NS = RES ? 1 : 2;  // the fp16 block (at most 63 tokens) in 16-token batches
-  static constexpr bool kSplit = true;    // fp16 residual of q'' in columns G..2G-1
-  static constexpr bool kScaled = true;   // q'' carries log2(e)/sqrt(d)
   const uint8_t *kc, *vc;
   const float *kmeta, *vmeta;             // float2 pairs (min, step)
   const uint16_t *kres;
@@ -480,9 +432,9 @@ struct MUQ {
   // the batch's value (min, step) pairs, one per lane (slot base + l / NGRP, group l % NGRP),
   // staged in LDS for the p.v step (slots past the end re-read the last one)
   int bbase, bend;
-  MKV_DEV void batch_fetch(const Carry &, Batch &bt) const {
+  MKV_DEV void batch_fetch(int base, const Carry &, Batch &bt) const {
     const int l = threadIdx.x & 63;
-    const int t = min(bbase + l / NGRP, bend - 1);
+    const int t = min(base + l / NGRP, bend - 1);
     const float *mp = vmeta + ((size_t)t * NGRP + l % NGRP) * 2;
     bt.mn = l < 16 * NS * NGRP ? gld(mp) : 0.f;
     bt.st = l < 16 * NS * NGRP ? gld(mp + 1) : 0.f;
@@ -491,9 +443,14 @@ struct MUQ {
     const int l = threadIdx.x & 63;
     if (l < 16 * NS * NGRP) vm[l] = make_float2(bt.mn, bt.st);
   }
-  MKV_DEV int slot(int, const Raw &, int) const { return 0; }
   // offset, from the lane's first key channel CPL*lq, of element j of key operand m
   static constexpr int kofs(int m, int j) { return 8 * (m >> 1) + ((m & 1) ? 2 : 0) + ((j & 1) ? 4 : 0) + (j >> 1); }
+  // the (min, step) pairs of the first block of a range (prep loads the later ones a block ahead)
+  MKV_DEV void first_block(int base) {
+    const int l = threadIdx.x & 63;
+    next_blk = base >> 6;
+    if (l < D / 2) next_km = gld16u(kmeta + ((size_t)next_blk * D + 2 * l) * 2);
+  }
   // rebuild the key operand B (and sum q mn) when the batch enters a new block
   MKV_DEV void prep(int base, QB<D> &qb) {
     bbase = base;
@@ -502,11 +459,10 @@ struct MUQ {
     cur_blk = blk;
     if (!RES) {
       // stage the block's (min, step) pairs, lane l taking channels 2l and 2l + 1 (loaded one
-      // block ahead, the first on demand), then load the next block's (the last complete block
-      // of the range at most)
+      // block ahead), then load the next block's (the last complete block of the range at most)
       const int l = threadIdx.x & 63;
       if (l < D / 2) {
-        const U4 u = next_blk == blk ? next_km : gld16u(kmeta + ((size_t)blk * D + 2 * l) * 2);
+        const U4 u = next_km;
         next_blk = min(blk + 1, (bend - 1) >> 6);
         next_km = gld16u(kmeta + ((size_t)next_blk * D + 2 * l) * 2);
         float4 *dst = reinterpret_cast<float4 *>(km + 4 * l);
@@ -658,10 +614,12 @@ MKV_DEV void rescale_to(L &ld, float mx, float &m_run, float &l_part, f4v (&O)[N
   mx = fmaxf(mx, __shfl_xor(mx, 32));
   const bool up = mx > m_run;
   const float corr = up ? fexp2(m_run - mx) : 1.f;  // factor 1 for the heads whose max held
-  l_part *= corr;
+  if (__any(m_run != -INFINITY)) {  // (a wave's first move finds empty sums)
+    l_part *= corr;
 #pragma unroll
-  for (int m = 0; m < NM; ++m) O[m] *= corr;
-  ld.rescale(corr);
+    for (int m = 0; m < NM; ++m) O[m] *= corr;
+    ld.rescale(corr);
+  }
   if (up) m_run = mx;
 }
 
@@ -692,14 +650,18 @@ MKV_DEV void rows_step(const MRows<D, G, GATHER> &ld, const typename MRows<D, G,
     pp[j] = fexp2(sc[j] - m_run);  // 0 for a masked token
     l_part += pp[j];
   }
-  ld.pv(r, pp, pp, 0xF, O);
+  ld.pv(r, pp, O);
 }
 
 // fp16 rows (FP16, H2O; gathered for RocketKV) over tokens [a, b) in 16-token steps, the row
 // loads of step i + 1 issued before step i is computed (and, when gathering, the slot indices
 // one step further ahead).
-template <int D, int G, bool GATHER>
-MKV_DEV void wave_rows(const MRows<D, G, GATHER> &ld, int a, int b, const QB<D> &qb, float qscale, float &m_run,
+//
+// `operand()` makes the q.k operand from its own loads, issued before: the first step's row loads go
+// out between the two, so that a tile waits once for both (it waited 1.5-2.4 us for q alone before
+// its first row load otherwise: a third of a short tile).
+template <int D, int G, bool GATHER, class Q>
+MKV_DEV void wave_rows(const MRows<D, G, GATHER> &ld, int a, int b, Q operand, float qscale, float &m_run,
                        float &l_part, f4v (&O)[MG<D>::NM], float *logit_out) {
   if (a >= b) return;
   typename MRows<D, G, GATHER>::Raw r0, r1;
@@ -707,6 +669,8 @@ MKV_DEV void wave_rows(const MRows<D, G, GATHER> &ld, int a, int b, const QB<D> 
   ld.index(a, b, ks, vs);
   ld.load_rows(ks, vs, r0);
   ld.index(a + 16, b, ks, vs);
+  QB<D> qb;
+  operand(qb);
   for (int base = a; base < b; base += 32) {
     const bool more1 = base + 16 < b;
     if (more1) {
@@ -723,45 +687,47 @@ MKV_DEV void wave_rows(const MRows<D, G, GATHER> &ld, int a, int b, const QB<D> 
   }
 }
 
-// One 32-token batch of a wave.  FULL: all 32 tokens exist (no clamping, no masks).
-template <bool FULL, int D, int G, class L>
-MKV_DEV void mfma_batch(L &ld, int base, int b, typename L::Carry &cy, QB<D> &qb, float qscale,
-                        float &m_run, float &l_part, f4v (&O)[MG<D>::NM], float *logit_out) {
-  constexpr int NS = L::NS;
-  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
-  typename L::Raw raw[NS];
+// A wave's current batch of the quantized paths.
+template <class L>
+struct Batch {
+  typename L::Raw raw[L::NS];
   typename L::Batch bt;
-  ld.prep(base, qb);
-  // issue order: loads that depend on the carried indices first, then this batch's rows or
-  // codes, then the next batch's indices
-  ld.batch_fetch(cy, bt);
+  typename L::Carry cy;
+};
+
+// Issue the loads of the batch at `base`, whose carried indices are there already: first those that
+// depend on the carried indices, then this batch's codes, then the next batch's indices.  FULL: all
+// its tokens exist (no clamping).
+template <bool FULL, class L>
+MKV_DEV void load_batch(const L &ld, int base, int b, Batch<L> &x) {
+  ld.batch_fetch(base, x.cy, x.bt);
 #pragma unroll
-  for (int s = 0; s < NS; ++s) ld.template fetch<FULL>(base + 16 * s, b, s, cy, raw[s]);
-  ld.carry(base + 16 * NS, b, cy);
-  ld.batch_fix(bt);
+  for (int s = 0; s < L::NS; ++s) ld.template fetch<FULL>(base + 16 * s, b, s, x.cy, x.raw[s]);
+  ld.carry(base + 16 * L::NS, b, x.cy);
+}
+
+// One batch of a wave, its loads issued.  FULL: all its tokens exist (no masks).
+template <bool FULL, int D, int G, class L>
+MKV_DEV void mfma_batch(L &ld, int base, int b, const Batch<L> &x, QB<D> &qb, float &m_run, float &l_part,
+                        f4v (&O)[MG<D>::NM]) {
+  constexpr int NS = L::NS;
+  const int lane = threadIdx.x & 63, lq = lane >> 4;
+  ld.prep(base, qb);
+  ld.batch_fix(x.bt);
   float sc[NS][4];
   float mx = -INFINITY;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     f4v S = {0.f, 0.f, 0.f, 0.f};
-    ld.qk(raw[s], qb, S);
-    float x[4] = {S[0], S[1], S[2], S[3]};
-    ld.kfix(s, x);
+    ld.qk(x.raw[s], qb, S);
+    float v[4] = {S[0], S[1], S[2], S[3]};
+    ld.kfix(s, v);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (L::kSplit) x[j] += mirror_cols<G>(x[j]);
-      float v = L::kScaled ? x[j] : x[j] * qscale;
-      if (!FULL) v = base + 16 * s + 4 * lq + j < b ? v : -INFINITY;
-      sc[s][j] = v;
-      mx = fmaxf(mx, v);
+      v[j] += mirror_cols<G>(v[j]);  // the residual columns (q'' carries log2(e)/sqrt(d))
+      sc[s][j] = FULL || base + 16 * s + 4 * lq + j < b ? v[j] : -INFINITY;
+      mx = fmaxf(mx, sc[s][j]);
     }
-  }
-  if (logit_out != nullptr && lr < G) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (FULL || sc[s][j] != -INFINITY) gst(logit_out + (size_t)ld.slot(base + 16 * s, raw[s], j) * G + lr, sc[s][j]);
   }
   if (__any(mx > m_run + kLazyMax)) rescale_to(ld, mx, m_run, l_part, O);
 #pragma unroll
@@ -772,7 +738,7 @@ MKV_DEV void mfma_batch(L &ld, int base, int b, typename L::Carry &cy, QB<D> &qb
     for (int j = 0; j < 4; ++j) {
       p[j] = fexp2(sc[s][j] - m_run);  // 0 for a masked token
       l_part += p[j];
-      pp[j] = p[j] * ld.vscale(raw[s], j);
+      pp[j] = p[j] * ld.vscale(x.raw[s], j);
       if (!FULL) {
         // slots past the count may hold any bits: their scale must not reach the product
         const bool ok = sc[s][j] != -INFINITY;
@@ -780,24 +746,25 @@ MKV_DEV void mfma_batch(L &ld, int base, int b, typename L::Carry &cy, QB<D> &qb
         valid_mask &= ~((ok ? 0 : 1) << j);
       }
     }
-    ld.vfix(raw[s], p, pp, valid_mask);
-    ld.pv(raw[s], p, pp, valid_mask, O);
+    ld.vfix(x.raw[s], p, pp, valid_mask);
+    ld.pv(x.raw[s], p, pp, valid_mask, O);
   }
 }
 
-// One wave over tokens [a, b) of its tile.  m_run / l_part belong to this lane's query head
-// (column lr); O holds this lane's part of O^T.
+// One wave over tokens [a, b) of its tile, the first batch's carried indices loaded.  m_run / l_part
+// belong to this lane's query head (column lr); O holds this lane's part of O^T.
 template <int D, int G, class L>
-MKV_DEV void wave_mfma(L &ld, int a, int b, QB<D> &qb, float qscale, float &m_run, float &l_part,
-                       f4v (&O)[MG<D>::NM], float *logit_out) {
-  if (a >= b) return;
-  typename L::Carry cy;
-  ld.carry(a, b, cy);
-  for (int base = a; base < b; base += 16 * L::NS) {
-    if (base + 16 * L::NS <= b)
-      mfma_batch<true, D, G>(ld, base, b, cy, qb, qscale, m_run, l_part, O, logit_out);
-    else
-      mfma_batch<false, D, G>(ld, base, b, cy, qb, qscale, m_run, l_part, O, logit_out);
+MKV_DEV void wave_mfma(L &ld, int a, int b, Batch<L> &x, QB<D> &qb, float &m_run, float &l_part,
+                       f4v (&O)[MG<D>::NM]) {
+  constexpr int T = 16 * L::NS;
+  for (int base = a; base < b; base += T) {
+    if (base + T <= b) {
+      load_batch<true>(ld, base, b, x);
+      mfma_batch<true, D, G>(ld, base, b, x, qb, m_run, l_part, O);
+    } else {
+      load_batch<false>(ld, base, b, x);
+      mfma_batch<false, D, G>(ld, base, b, x, qb, m_run, l_part, O);
+    }
   }
 }
 
@@ -808,9 +775,9 @@ MKV_DEV void wave_mfma(L &ld, int a, int b, QB<D> &qb, float qscale, float &m_ru
 struct WaveRange {
   int a, b;
 };
-MKV_DEV WaveRange wave_range(int t0, int t1, int wave, int nw) {
+MKV_DEV WaveRange wave_range(int t0, int t1, int wave, int nw, int step) {
   const int end = max(t1, t0);
-  const int span = ((end - t0 + nw - 1) / nw + 31) & ~31;
+  const int span = ((end - t0 + nw - 1) / nw + step - 1) & -step;
   const int a = min(t0 + wave * span, end);
   return {a, min(a + span, end)};
 }
@@ -873,96 +840,33 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int Hq = Hkv * G;
   const uint16_t *qh = q + ((size_t)seq * Hq + h * G) * D;
-  const WaveRange wr = wave_range(tile.z, min(tile.w, n_act), wave, NW);
+  const WaveRange wr = wave_range(tile.z, min(tile.w, n_act), wave, NW, method == KVQ || method == UQ ? 32 : 16);
   const int lr = lane & 15, lq = lane >> 4;
-  const bool kvq = method == KVQ;
   const bool uq = method == UQ;
-  // Set-up: every global read of the tile's set-up is issued before any of it is used (the
-  // reads are independent, so the tile waits for one round trip, not one per read).
+  // Set-up: every global read of the tile's set-up, and the first batch's loads behind them, are
+  // issued before any of it is used (the reads are independent, so the tile waits for one round trip,
+  // not one per read).
   constexpr int kQI = (G * D + kTileThreads - 1) / kTileThreads;  // q elements per thread
   // both lookup tables of a codebook take at most 256 uint4 (the 2-bit quad tables)
   static_assert(kTileThreads >= 256, "one uint4 of the lookup tables per thread");
-  if (uq || kvq) {
-    uint16_t qv[kQI];
-    float tv[kQI];
-#pragma unroll
-    for (int i = 0; i < kQI; ++i) {
-      const int e = min((int)threadIdx.x + i * kTileThreads, G * D - 1);
-      qv[i] = qh[(size_t)(e / D) * D + e % D];
-    }
-    uint4 lv = make_uint4(0u, 0u, 0u, 0u);
-    int nlut = 0;
-    float cbv = 0.f;
-    if (kvq) {
-      // tau per channel, the codebook's lookup tables (copied as built on the host) and the key
-      // codebook
-      const float *tau = reinterpret_cast<const float *>(sd.kmeta) + (size_t)h * D * 2;
-#pragma unroll
-      for (int i = 0; i < kQI; ++i) tv[i] = gld(tau + 2 * ((threadIdx.x + i * kTileThreads) % D));
-      const int bits = sd.bits, nc = 1 << bits;
-      const uint32_t *lut = reinterpret_cast<const uint32_t *>(cbtab + kLutBase) + lut_offset(bits);
-      nlut = lut_half_words(bits) / 2;
-      if ((int)threadIdx.x < nlut) lv = gld16(lut + 4 * threadIdx.x);
-      if (threadIdx.x < 16 && (int)threadIdx.x < nc) cbv = cbtab[cb_offset(bits) + threadIdx.x];
-      // cleared per-wave outlier rows
-      float4 *vz = reinterpret_cast<float4 *>(&s_wave[wave][0]);
-      for (int e = lane; e < kWaveFloats / 4; e += 64) vz[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-      float4 *kz = reinterpret_cast<float4 *>(&s_kc[wave][0][0]);
-      for (int e = lane; e < (G + 1) * 36 / 4; e += 64) kz[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if ((int)threadIdx.x < nlut) reinterpret_cast<uint4 *>(s_lut)[threadIdx.x] = lv;
-      if (threadIdx.x < 16) s_cbk[threadIdx.x] = cbv;
-    }
-    // q of each head (scaled), and for KVQuant q * tau
-#pragma unroll
-    for (int i = 0; i < kQI; ++i) {
-      const int e = threadIdx.x + i * kTileThreads;
-      if (e < G * D) {
-        const int g = e / D, c = e % D;
-        const float qx = h2f(qv[i]) * qscale;
-        s_q[c][g] = qx;
-        if (kvq) s_q[c][G + g] = qx * tv[i];
-      }
-    }
-  }
-  __syncthreads();
-  // q.k operand B: query head lr, channels CPL*lq + 4m .. +3 (KVQuant: fp16 part of the scaled
-  // q' in columns g < G, its residual in columns 2G-1-g)
-  QB<D> qb;
-  if (kvq) {
-    const int g = lr < G ? lr : lr < 2 * G ? 2 * G - 1 - lr : 0;
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      const int c = CPL * lq + 4 * m;
-      uint32_t w[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const float x0 = s_q[c + 2 * j][G + g], x1 = s_q[c + 2 * j + 1][G + g];
-        const float h0 = (float)(_Float16)x0, h1 = (float)(_Float16)x1;
-        w[j] = lr < G ? pk_f16(h0, h1) : lr < 2 * G ? pk_f16(x0 - h0, x1 - h1) : 0u;
-      }
-      qb.b[m] = mk_h4(w[0], w[1]);
-    }
-  } else {
-    uint32_t w[NM][2];
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      const int c = 32 * (m / 2) + 8 * lq + 4 * (m % 2);
-      const uint32_t *qp = reinterpret_cast<const uint32_t *>(qh + (size_t)min(lr, G - 1) * D + c);
-      w[m][0] = gld(qp);  // lanes lr >= G read head G - 1 and drop it
-      w[m][1] = gld(qp + 1);
-    }
-#pragma unroll
-    for (int m = 0; m < NM; ++m) qb.b[m] = lr < G ? mk_h4(w[m][0], w[m][1]) : mk_h4(0u, 0u);
-  }
   float m_run = -INFINITY, l_part = 0.f;
   float uq_om[D / 64];  // uniform 4-bit: sum p mn per value group (summed over the lane quads)
   f4v O[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) O[m] = f4v{0.f, 0.f, 0.f, 0.f};
+  // q of each head (quantized paths), staged scaled in LDS by stage_q
+  uint16_t qv[kQI];
+  auto load_q = [&]() {
+#pragma unroll
+    for (int i = 0; i < kQI; ++i) {
+      const int e = min((int)threadIdx.x + i * kTileThreads, G * D - 1);
+      qv[i] = gld(qh + (size_t)(e / D) * D + e % D);
+    }
+  };
   auto run_uq = [&]() {
     // the complete 64-token blocks, then the incomplete block's fp16 keys (a batch never spans
     // both: ranges start at multiples of 32)
-    const int full = (st[ST_COUNT] / 64) * 64;
+    const int full = (n_cnt / 64) * 64;
     auto init = [&](auto &ld) {
       ld.kc = reinterpret_cast<const uint8_t *>(sd.kc) + h * stride_codes(sd);
       ld.vc = reinterpret_cast<const uint8_t *>(sd.vc) + h * stride_codes(sd);
@@ -977,21 +881,31 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
       ld.lq = lq;
       ld.prole = lr < G ? 0 : lr < 2 * G ? 1 : 2;
       ld.cur_blk = -1;
-      ld.next_blk = -1;
       ld.kbias = 0.f;
     };
+    load_q();
     MUQ<D, G, false> lq_;
     init(lq_);
     lq_.bend = min(wr.b, full);
 #pragma unroll
     for (int gr = 0; gr < D / 64; ++gr) lq_.om[gr] = 0.f;
-    wave_mfma<D, G>(lq_, wr.a, min(wr.b, full), qb, qscale, m_run, l_part, O, nullptr);
+    Batch<MUQ<D, G, false>> x;
+    if (wr.a < lq_.bend) lq_.first_block(wr.a);
+#pragma unroll
+    for (int i = 0; i < kQI; ++i) {
+      const int e = threadIdx.x + i * kTileThreads;
+      if (e < G * D) s_q[e % D][e / D] = h2f(qv[i]) * qscale;
+    }
+    __syncthreads();
+    QB<D> qb;
+    wave_mfma<D, G>(lq_, wr.a, lq_.bend, x, qb, m_run, l_part, O);
     MUQ<D, G, true> lr_;
     init(lr_);
     lr_.bend = wr.b;
 #pragma unroll
     for (int gr = 0; gr < D / 64; ++gr) lr_.om[gr] = lq_.om[gr];
-    wave_mfma<D, G>(lr_, max(wr.a, full), wr.b, qb, qscale, m_run, l_part, O, nullptr);
+    Batch<MUQ<D, G, true>> y;
+    wave_mfma<D, G>(lr_, max(wr.a, full), wr.b, y, qb, m_run, l_part, O);
 #pragma unroll
     for (int gr = 0; gr < D / 64; ++gr) {
       float v = lr_.om[gr];
@@ -1000,61 +914,122 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
       uq_om[gr] = v;
     }
   };
+  auto run_kvq = [&](auto bits_tag) {
+    constexpr int BITS = decltype(bits_tag)::value;
+    MKVQ<D, G, BITS> ld;
+    ld.kc = reinterpret_cast<const uint8_t *>(sd.kc) + h * stride_codes(sd);
+    ld.vc = reinterpret_cast<const uint8_t *>(sd.vc) + h * stride_codes(sd);
+    ld.krow = reinterpret_cast<const uint32_t *>(sd.krow) + h * stride_krow(sd);
+    ld.kout = reinterpret_cast<const uint32_t *>(sd.kout) + h * stride_kout(sd);
+    ld.vdel = reinterpret_cast<const uint32_t *>(sd.vdel) + h * stride_vout(sd);
+    ld.vsc = reinterpret_cast<const float *>(sd.vmeta) + h * stride_slots(sd);
+    ld.lutk = s_lut;
+    ld.lutv = s_lut + lut_half_words(BITS);
+    ld.cbk = s_cbk;
+    ld.qq = &s_q[0][0];
+    ld.kcorr = &s_kc[wave][0][0];
+    ld.kterm = s_kt[wave];
+    ld.vacc = &s_wave[wave][0];
+    ld.lr = lr;
+    ld.lq = lq;
+    ld.rowbytes = sd.rowbytes;
+    ld.nov = sd.nov_slots;
+    ld.cap = sd.cap;
+    // q, tau per channel, the codebook's lookup tables (copied as built on the host) and the key
+    // codebook
+    load_q();
+    float tv[kQI];
+    const float *tau = reinterpret_cast<const float *>(sd.kmeta) + (size_t)h * D * 2;
+#pragma unroll
+    for (int i = 0; i < kQI; ++i) tv[i] = gld(tau + 2 * ((threadIdx.x + i * kTileThreads) % D));
+    const int nlut = lut_half_words(BITS) / 2;
+    uint4 lv = make_uint4(0u, 0u, 0u, 0u);
+    if ((int)threadIdx.x < nlut)
+      lv = gld16(reinterpret_cast<const uint32_t *>(cbtab + kLutBase) + lut_offset(BITS) + 4 * threadIdx.x);
+    float cbv = 0.f;
+    if ((int)threadIdx.x < (1 << BITS)) cbv = gld(cbtab + cb_offset(BITS) + threadIdx.x);
+    Batch<MKVQ<D, G, BITS>> x;
+    if (wr.a < wr.b) ld.carry(wr.a, wr.b, x.cy);
+    // cleared per-wave outlier rows
+    float4 *vz = reinterpret_cast<float4 *>(&s_wave[wave][0]);
+    for (int e = lane; e < kWaveFloats / 4; e += 64) vz[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 *kz = reinterpret_cast<float4 *>(&s_kc[wave][0][0]);
+    for (int e = lane; e < (G + 1) * 36 / 4; e += 64) kz[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    // q scaled, and q * tau
+#pragma unroll
+    for (int i = 0; i < kQI; ++i) {
+      const int e = threadIdx.x + i * kTileThreads;
+      if (e < G * D) {
+        const float qx = h2f(qv[i]) * qscale;
+        s_q[e % D][e / D] = qx;
+        s_q[e % D][G + e / D] = qx * tv[i];
+      }
+    }
+    if ((int)threadIdx.x < nlut) reinterpret_cast<uint4 *>(s_lut)[threadIdx.x] = lv;
+    if (threadIdx.x < 16) s_cbk[threadIdx.x] = cbv;
+    __syncthreads();
+    // q.k operand B: query head lr, channels CPL*lq + 4m .. +3: the fp16 part of the scaled q' in
+    // columns g < G, its residual in columns 2G-1-g
+    QB<D> qb;
+    const int g = lr < G ? lr : lr < 2 * G ? 2 * G - 1 - lr : 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const int c = CPL * lq + 4 * m;
+      uint32_t w[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float x0 = s_q[c + 2 * j][G + g], x1 = s_q[c + 2 * j + 1][G + g];
+        const float h0 = (float)(_Float16)x0, h1 = (float)(_Float16)x1;
+        w[j] = lr < G ? pk_f16(h0, h1) : lr < 2 * G ? pk_f16(x0 - h0, x1 - h1) : 0u;
+      }
+      qb.b[m] = mk_h4(w[0], w[1]);
+    }
+    wave_mfma<D, G>(ld, wr.a, wr.b, x, qb, m_run, l_part, O);
+    // fold the value-outlier terms of head lr into this lane's channels (the wave's LDS
+    // accesses complete in order, so the merge may reuse the region afterwards)
+    if (lr < G) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) O[m][i] += s_wave[wave][lr * (D + 4) + VPL * (4 * lq + i) + m];
+      }
+    }
+  };
+  // fp16 rows: query head lr, channels as in the row loads
+  auto run_rows = [&](auto gather_tag) {
+    constexpr bool GATHER = decltype(gather_tag)::value;
+    MRows<D, G, GATHER> ld;
+    ld.K = reinterpret_cast<const uint16_t *>(sd.k) + h * stride_rows(sd, D);
+    ld.V = reinterpret_cast<const uint16_t *>(sd.v) + h * stride_rows(sd, D);
+    ld.sel = GATHER ? reinterpret_cast<const int32_t *>(sd.sel) + h * stride_sel(sd) : nullptr;
+    ld.lr = lr;
+    ld.lq = lq;
+    float *lg = method == H2O ? reinterpret_cast<float *>(sd.logits) + h * stride_logits(sd, G) : nullptr;
+    uint32_t w[NM][2];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const int c = 32 * (m / 2) + 8 * lq + 4 * (m % 2);
+      const uint32_t *qp = reinterpret_cast<const uint32_t *>(qh + (size_t)min(lr, G - 1) * D + c);
+      w[m][0] = gld(qp);  // lanes lr >= G read head G - 1 and drop it
+      w[m][1] = gld(qp + 1);
+    }
+    auto operand = [&](QB<D> &qb) {
+#pragma unroll
+      for (int m = 0; m < NM; ++m) qb.b[m] = lr < G ? mk_h4(w[m][0], w[m][1]) : mk_h4(0u, 0u);
+    };
+    wave_rows<D, G, GATHER>(ld, wr.a, wr.b, operand, qscale, m_run, l_part, O, lg);
+  };
   if (uq) {
     run_uq();
-  } else if (method == FP16 || method == H2O) {
-    MRows<D, G, false> ld;
-    ld.K = reinterpret_cast<const uint16_t *>(sd.k) + h * stride_rows(sd, D);
-    ld.V = reinterpret_cast<const uint16_t *>(sd.v) + h * stride_rows(sd, D);
-    ld.sel = nullptr;
-    ld.lr = lr;
-    ld.lq = lq;
-    float *lg = (method == H2O) ? reinterpret_cast<float *>(sd.logits) + h * stride_logits(sd, G) : nullptr;
-    wave_rows<D, G, false>(ld, wr.a, wr.b, qb, qscale, m_run, l_part, O, lg);
+  } else if (method == KVQ) {
+    const int bits = sd.bits;
+    if (bits == 4) run_kvq(std::integral_constant<int, 4>{});
+    else if (bits == 3) run_kvq(std::integral_constant<int, 3>{});
+    else run_kvq(std::integral_constant<int, 2>{});
   } else if (method == ROCKET) {
-    MRows<D, G, true> ld;
-    ld.K = reinterpret_cast<const uint16_t *>(sd.k) + h * stride_rows(sd, D);
-    ld.V = reinterpret_cast<const uint16_t *>(sd.v) + h * stride_rows(sd, D);
-    ld.sel = reinterpret_cast<const int32_t *>(sd.sel) + h * stride_sel(sd);
-    ld.lr = lr;
-    ld.lq = lq;
-    wave_rows<D, G, true>(ld, wr.a, wr.b, qb, qscale, m_run, l_part, O, nullptr);
-  } else if (kvq) {
-    auto run = [&](auto bits_tag) {
-      constexpr int BITS = decltype(bits_tag)::value;
-      MKVQ<D, G, BITS> ld;
-      ld.kc = reinterpret_cast<const uint8_t *>(sd.kc) + h * stride_codes(sd);
-      ld.vc = reinterpret_cast<const uint8_t *>(sd.vc) + h * stride_codes(sd);
-      ld.krow = reinterpret_cast<const uint32_t *>(sd.krow) + h * stride_krow(sd);
-      ld.kout = reinterpret_cast<const uint32_t *>(sd.kout) + h * stride_kout(sd);
-      ld.vdel = reinterpret_cast<const uint32_t *>(sd.vdel) + h * stride_vout(sd);
-      ld.vsc = reinterpret_cast<const float *>(sd.vmeta) + h * stride_slots(sd);
-      ld.lutk = s_lut;
-      ld.lutv = s_lut + lut_half_words(BITS);
-      ld.cbk = s_cbk;
-      ld.qq = &s_q[0][0];
-      ld.kcorr = &s_kc[wave][0][0];
-      ld.kterm = s_kt[wave];
-      ld.vacc = &s_wave[wave][0];
-      ld.lr = lr;
-      ld.lq = lq;
-      ld.rowbytes = sd.rowbytes;
-      ld.nov = sd.nov_slots;
-      ld.cap = sd.cap;
-      wave_mfma<D, G>(ld, wr.a, wr.b, qb, qscale, m_run, l_part, O, nullptr);
-      // fold the value-outlier terms of head lr into this lane's channels (the wave's LDS
-      // accesses complete in order, so the merge may reuse the region afterwards)
-      if (lr < G) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-          for (int m = 0; m < NM; ++m) O[m][i] += s_wave[wave][lr * (D + 4) + VPL * (4 * lq + i) + m];
-        }
-      }
-    };
-    if (sd.bits == 4) run(std::integral_constant<int, 4>{});
-    else if (sd.bits == 3) run(std::integral_constant<int, 3>{});
-    else run(std::integral_constant<int, 2>{});
+    run_rows(std::integral_constant<bool, true>{});
+  } else {
+    run_rows(std::integral_constant<bool, false>{});
   }
   if (uq) {
 #pragma unroll

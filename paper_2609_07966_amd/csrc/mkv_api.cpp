@@ -83,19 +83,20 @@ double token_bytes(const SeqDesc &s, int D) {
   }
 }
 
-// Tokens per attention tile for a tile of about `tile_bytes` (a multiple of 64: tiles of 32-token
-// granularity, which filled the slots of small launches more finely, were measured slower on the
-// FP16, uniform 4-bit, H2O and RocketKV per-configuration launches).
-int tile_tokens(const SeqDesc &s, int D, double tile_bytes) {
-  const int t = (int)(tile_bytes / token_bytes(s, D)) & ~63;
-  return std::max(64, std::min(t, 4096));
+// What a token of a quantized sequence costs a wave, in the same unit (KVQ at 4 bits: its bytes): tiles
+// of a short launch all start together, so equal times balance it, not equal bytes (clock stamps per
+// 32-token batch: uniform 4-bit 2.0 us, KVQ at 2, 3 and 4 bits 2.3, 3.0 and 3.5).
+double token_cost(const SeqDesc &s, int D) {
+  const double c = s.method == UQ ? 80 : s.bits == 2 ? 92 : s.bits == 3 ? 120 : 140;
+  return c * D / 128;
 }
 
 // Tile size: large tiles amortise each workgroup's set-up, but a launch needs several
 // workgroups per slot (256 CUs x 3 resident workgroups) to balance: about 4 rounds, within
 // 64 to 192 KiB (measured best for batches of ~40 MB and ~600 MB per step); then adjusted to
 // whole rounds (below).
-constexpr int kTileSlots = 256 * 3;  // resident attention workgroups (3 per CU)
+constexpr int kCus = 256;
+constexpr int kTileSlots = kCus * 3;  // resident attention workgroups (3 per CU)
 double tile_bytes_for(double total_bytes) {
   constexpr double kRounds = 4;
   return std::min(196608.0, std::max(65536.0, total_bytes / (kTileSlots * kRounds)));
@@ -279,18 +280,12 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     const SeqDesc &d = L->seqs[s];
     total += (double)Hkv * (d.method == ROCKET ? d.topk : d.cap) * token_bytes(d, D);
   }
-  // a sequence's tokens per tile and tile count at a given tile size
-  // In launches of three or more rounds of workgroups, fp16-row tiles (FP16, H2O) take twice the
-  // bytes: they are bandwidth-bound, and each tile a CU starts costs a dispatch gap (a median
-  // 2 us from one tile's end to the next one's start on that CU, measured with clock stamps), so
-  // fewer, longer row tiles leave the slots busier (mixed batch: 134.0-135.1 against 135.8-136.3
-  // us per partial launch; 1.5x and 2.5-3x no better, 0.75x 6 us slower).  Shorter launches keep
-  // them (H2O-40 alone: 32.7 against 30.3 us with doubled row tiles, half a round left over).
-  bool long_rows = false;
-  auto split = [&](const SeqDesc &d, double tb, int *chunk) {
+  int n_quant = 0;
+  for (const SeqDesc &d : L->seqs) n_quant += d.method == UQ || d.method == KVQ;
+  // a sequence's tokens per tile (a multiple of `gran`) and tile count for tiles of `unit` tokens
+  auto split = [&](const SeqDesc &d, double unit, int gran, int *chunk) {
     const int amax = d.method == ROCKET ? d.topk : d.cap;
-    if (long_rows && (d.method == FP16 || d.method == H2O)) tb *= 2;
-    int c = tile_tokens(d, D, tb), n = std::max(1, (amax + c - 1) / c);
+    int c = std::max(gran, std::min((int)unit & -gran, 4096)), n = std::max(1, (amax + c - 1) / c);
     if (n > kMaxTiles) {  // long sequences: fewer, larger tiles keep the combine short
       c = (((amax + kMaxTiles - 1) / kMaxTiles) + 63) & ~63;
       n = (amax + c - 1) / c;
@@ -298,25 +293,93 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     *chunk = c;
     return n;
   };
-  auto count_at = [&](double tb) {
+  // Tiles are multiples of 64 tokens (of 32, which filled the slots of small launches more finely,
+  // measured slower), quantized ones of 128 in short launches: the 4 waves of a workgroup take 32-token
+  // batches, so other sizes leave waves idle for the last one (a 320-token tile takes as long as a
+  // 384-token one).  In launches of three or more rounds of workgroups, fp16-row tiles (FP16, H2O)
+  // take twice the bytes: they are bandwidth-bound, and each tile a CU starts costs a dispatch gap (a
+  // median 2 us from one tile's end to the next one's start on that CU, measured with clock stamps), so
+  // fewer, longer row tiles leave the slots busier (mixed batch: 134.0-135.1 against 135.8-136.3
+  // us per partial launch; 1.5x and 2.5-3x no better, 0.75x 6 us slower).
+  bool long_launch = false, fine = true;
+  auto by_bytes = [&](const SeqDesc &d, double tb, int *chunk) {
+    if (long_launch && (d.method == FP16 || d.method == H2O)) tb *= 2;
+    return split(d, tb / token_bytes(d, D), fine || (d.method != UQ && d.method != KVQ) ? 64 : 128, chunk);
+  };
+  auto by_time = [&](const SeqDesc &d, double cost, int *chunk) { return split(d, cost / token_cost(d, D), 128, chunk); };
+  auto count_at = [&](double size, auto rule) {
     long long n = 0;
     int c;
-    for (int s = 0; s < S; ++s) n += (long long)Hkv * split(L->seqs[s], tb, &c);
+    for (int s = 0; s < S; ++s) n += (long long)Hkv * rule(L->seqs[s], size, &c);
     return n;
   };
   // whole rounds of resident workgroups: when the size rule leaves the last round partly idle,
   // smaller tiles (down to 16 KiB) fill it, the smallest size whose count still fits in the
-  // rounds begun.  (Fewer, larger tiles to drop a nearly empty last round were measured worse:
-  // H2O-40 alone 32.3 against 29.5 us.)
+  // rounds begun.
+  auto fill_rounds = [&]() {
+    const double most = tile_bytes_for(total);
+    const long long cap = (count_at(most, by_bytes) + kTileSlots - 1) / kTileSlots * kTileSlots;
+    for (double tb = 16384.0; tb < most; tb *= 1.02)
+      if (count_at(tb, by_bytes) <= cap) return tb;
+    return most;
+  };
   double tile_bytes = tile_bytes_for(total);
-  long_rows = count_at(tile_bytes) >= 3 * kTileSlots;
-  {
-    const long long cap = (count_at(tile_bytes) + kTileSlots - 1) / kTileSlots * kTileSlots;
-    for (double tb = 16384.0; tb < tile_bytes; tb *= 1.02)
-      if (count_at(tb) <= cap) {
-        tile_bytes = tb;
-        break;
+  long_launch = fine = count_at(tile_bytes, by_bytes) >= 3 * kTileSlots;
+  enum { BY_BYTES, BY_TIME, BY_ROWS } rule = BY_BYTES;
+  if (!long_launch && n_quant == 0) {
+    // Short launches of fp16 rows alone: every workgroup starts at once, tile i on CU i mod 256, so the
+    // fullest CU sets the time: its bytes, a set-up worth about 44 d = 128 rows per tile, and a rate that
+    // drops with fewer than 3 workgroups on a CU.  The size with the least is taken.  (Sweeps of four
+    // layers: 8 x 8192 tokens under H2O-20 117, 113, 116, 118, 116 us at 832, 448, 576, 384, 256 tiles;
+    // H2O-40 162, 159, 159, 156, 167 at 1664, 1152, 704, 512, 448; 8 x 4096 FP16 145, 154, 144, 146 at
+    // 1408, 1088, 704, 512.  The model puts each of these in order.)
+    rule = BY_ROWS;
+    double best = -1.0;
+    std::vector<double> load(kCus);
+    for (int c = 64; c <= 1024; c += 64) {
+      const double bytes = c * 4.0 * D;
+      const long long n = count_at(bytes, by_bytes);
+      if (n > 3 * kTileSlots && c < 1024) continue;
+      std::fill(load.begin(), load.end(), 0.0);
+      int i = 0;
+      for (int rocket = 0; rocket < 2; ++rocket)
+        for (const SeqDesc &d : L->seqs) {
+          if ((d.method == ROCKET) != (rocket == 1)) continue;
+          int chunk;
+          const int amax = d.method == ROCKET ? d.topk : d.cap, tiles = by_bytes(d, bytes, &chunk);
+          for (int h = 0; h < Hkv; ++h)
+            for (int t = 0; t < tiles; ++t) load[i++ % kCus] += 44 * 512.0 + std::min(chunk, amax - t * chunk) * 4.0 * D;
+        }
+      // (a d = 64 workgroup has half the bytes in flight)
+      const long long busy = (n + kCus - 1) / kCus * D / 64;
+      const double cost = *std::max_element(load.begin(), load.end()) *
+                          (busy <= 2 ? 1.3 : busy == 3 ? 1.1 : busy == 4 ? 1.04 : 1.0);
+      if (best < 0.0 || cost < best) {
+        best = cost;
+        tile_bytes = bytes;
       }
+    }
+  } else {
+    // One round: quantized tiles alone, bound by the latency of their batches, are best all resident at once
+    // (8 x 8192 tokens, three layers: uniform 4-bit 93 us at 704 tiles of 768 tokens against 105 at
+    // 1408 of 384, KVQ at 4 bits 144 against 156; 16 ragged sequences of three kinds, two layers, 101
+    // against 116): the smallest size that allows it, by time, up to 8 times the default.
+    if (!long_launch && n_quant == S)
+      for (double c = 4096.0; c < 8 * tile_bytes && rule == BY_BYTES; c *= 1.03)
+        if (count_at(c, by_time) <= kTileSlots) {
+          tile_bytes = c;
+          rule = BY_TIME;
+        }
+    if (rule == BY_BYTES) tile_bytes = fill_rounds();
+  }
+  // (a layout that mkv_decode_attention_noalloc has room for under the general rule keeps it)
+  if (rule != BY_BYTES || !fine) {
+    const long long n = rule == BY_TIME ? count_at(tile_bytes, by_time) : count_at(tile_bytes, by_bytes);
+    if (n * G * (D + 2) * sizeof(float) > kStaticScratchBytes) {
+      rule = BY_BYTES;
+      fine = true;
+      tile_bytes = fill_rounds();
+    }
   }
   for (int pass = 0; pass < 2; ++pass)
   for (int s = 0; s < S; ++s) {
@@ -324,7 +387,7 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     const int grp = d.method == ROCKET ? 1 : 0;
     if (grp != pass) continue;
     const int amax = d.method == ROCKET ? d.topk : d.cap;
-    d.tile_count = split(d, tile_bytes, &d.chunk);
+    d.tile_count = rule == BY_TIME ? by_time(d, tile_bytes, &d.chunk) : by_bytes(d, tile_bytes, &d.chunk);
     d.tile_first = (int)L->tiles.size();
     for (int h = 0; h < Hkv; ++h)
       for (int t = 0; t < d.tile_count; ++t)
