@@ -27,12 +27,13 @@ class KVCache:
         self.S, self.Hq, self.Hkv, self.D, self.max_new = self.shape
         self.cfgs = [dict(c) for c in cfgs]
         self.prompt_lens = [int(x) for x in prompt_lens]
-        self.nbytes = L.mkv_cache_bytes(self.shape, self.cfgs, self.prompt_lens)
+        rows = [L.make_config(c) for c in self.cfgs]
+        self.nbytes = L.mkv_cache_bytes(self.shape, rows, self.prompt_lens)
         self.arena = torch.empty(self.nbytes + 256, dtype=torch.uint8, device=device)
         base = self.arena.data_ptr()
         self.arena_ptr = (base + 255) & ~255
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.arena.device)
-        self.h = L.mkv_cache_create(self.shape, self.cfgs, self.prompt_lens, codebooks, self.arena_ptr,
+        self.h = L.mkv_cache_create(self.shape, rows, self.prompt_lens, codebooks, self.arena_ptr,
                                     self.nbytes, self.stream.cuda_stream)
 
     def close(self):

@@ -1061,11 +1061,6 @@ __global__ __launch_bounds__(kQuantThreads) void k_kvq_values(const SeqDesc *__r
   else run(std::integral_constant<int, 2>{});
 }
 
-__global__ void k_init_state(int32_t *state, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) state[i] = 0;
-}
-
 template <int D>
 hipError_t append_decode_impl(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                               hipStream_t st, LaunchEv ev) {
@@ -1149,12 +1144,6 @@ hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *
 hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *k,
                               const uint16_t *v, hipStream_t st) {
   return sh.D == 64 ? prefill_impl<64>(dv, sh, hs, k, v, st) : prefill_impl<128>(dv, sh, hs, k, v, st);
-}
-
-hipError_t launch_init_state(const Dev &dv, const Shape &sh, hipStream_t st) {
-  const int n = sh.S * sh.Hkv * ST_WORDS;
-  hipLaunchKernelGGL(k_init_state, dim3((n + 255) / 256), dim3(256), 0, st, dv.state, n);
-  return hipGetLastError();
 }
 
 }  // namespace mkv

@@ -48,10 +48,13 @@ constexpr int kProfKinds = 5;
 
 struct Layout {
   std::vector<SeqDesc> seqs;  // offsets (relative to the arena) in the pointer fields
-  size_t off_seqs = 0, off_state = 0, off_tiles = 0, off_cbtab = 0, off_partials = 0, total = 0;
-  size_t off_prep = 0, off_rk_pairs = 0, off_comb = 0, off_lists = 0;
+  // [off_tables, tables_end) holds everything that the host writes at creation, in one copy: the
+  // descriptors, the state words (zero), the lists below and the codebook region
+  size_t off_tables = 0, tables_end = 0, off_partials = 0, total = 0;
+  size_t off_seqs = 0, off_state = 0, off_tiles = 0, off_prep = 0, off_comb = 0, off_rk_pairs = 0, off_lists = 0,
+         off_cbtab = 0;
   int n_tiles = 0, n_tiles_uq = 0, n_tiles_rk = 0;
-  std::vector<int4> tiles;
+  std::vector<int4> tiles;     // attention tiles in launch order
   std::vector<int4> prep;      // decode-step append / scoring work list
   std::vector<int2> rk_pairs;  // RocketKV (seq, kv head) pairs
   std::vector<int4> comb;      // combine work list
@@ -153,7 +156,92 @@ mkv_status check_config(const mkv_config &c, int n0, int D, int s) {
   }
 }
 
-mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_t *plen, Layout *L) {
+// RocketKV scoring workgroups of a decode step per kv head.
+int score_parts(const SeqDesc &d) { return (d.cap + kScoreTokensPerPart - 1) / kScoreTokensPerPart; }
+
+// The work lists of a layout whose sizes are set.
+void fill_lists(Layout *L, int Hkv) {
+  const int S = (int)L->seqs.size();
+  // Attention tiles in launch order (a tile's partial slot is tile_first + h tile_count + z / chunk,
+  // whatever its place): the quantized tiles, the longest-running per byte, spread evenly over the
+  // first 3/4 of the fp16-row and quantized tiles, the fp16-row tiles evenly over all of them, RocketKV
+  // tiles last.  Long tiles then start early enough to end with the rest, while issue-bound and
+  // bandwidth-bound tiles still share the chip throughout (measured on the mixed batch: 136-137
+  // against 140-141 us per partial launch for the sequence order; spreading the quantized tiles
+  // over 60 %, 90 % or all of the list, or putting them all first, did less or worse).
+  {
+    constexpr double kQuantSpan = 0.75;
+    std::vector<int4> of[2];  // fp16-row and quantized tiles in sequence order
+    std::vector<int> at[2];   // their places in the sequence order
+    std::vector<int4> rocket;
+    int place = 0;
+    for (int s = 0; s < S; ++s) {
+      const SeqDesc &d = L->seqs[s];
+      const int amax = d.method == ROCKET ? d.topk : d.cap, q = d.method == KVQ || d.method == UQ;
+      for (int h = 0; h < Hkv; ++h)
+        for (int t = 0; t < d.tile_count; ++t) {
+          const int4 tile = make_int4(s, h, t * d.chunk, std::min(amax, (t + 1) * d.chunk));
+          if (d.method == ROCKET) {
+            rocket.push_back(tile);
+          } else {
+            of[q].push_back(tile);
+            at[q].push_back(place++);
+          }
+        }
+    }
+    // the two in the order of their places in the list, in units of its length, the earlier one in the
+    // sequence order where they coincide
+    const double nr = (double)of[0].size(), nq = (double)of[1].size();
+    size_t ir = 0, iq = 0;
+    L->tiles.reserve(L->n_tiles);
+    while (ir < of[0].size() || iq < of[1].size()) {
+      const double r = ir < of[0].size() ? (ir + 0.5) / nr : 2.0, q = iq < of[1].size() ? (iq + 0.5) / nq * kQuantSpan : 2.0;
+      if (q < r || (q == r && at[1][iq] < at[0][ir])) L->tiles.push_back(of[1][iq++]);
+      else L->tiles.push_back(of[0][ir++]);
+    }
+    L->tiles.insert(L->tiles.end(), rocket.begin(), rocket.end());
+  }
+  // a decode step's append and scoring work: RocketKV scoring parts (one per kScoreTokens tokens
+  // of the largest retained set) first, then the plain appends
+  for (int s = 0; s < S; ++s) {
+    const SeqDesc &d = L->seqs[s];
+    if (d.method != ROCKET) continue;
+    const int parts = score_parts(d);
+    for (int h = 0; h < Hkv; ++h) {
+      L->rk_pairs.push_back(make_int2(s, h));
+      for (int p = 0; p < parts; ++p) L->prep.push_back(make_int4(s, h, p, parts));
+    }
+  }
+  for (int s = 0; s < S; ++s)
+    if (L->seqs[s].method != ROCKET)
+      for (int h = 0; h < Hkv; ++h) L->prep.push_back(make_int4(s, h, -1, 0));
+  // the combine: H2O kv heads' parts (one per kCombineSlots slots) first, then one item per pair
+  for (int pass = 0; pass < 2; ++pass)
+    for (int s = 0; s < S; ++s) {
+      const SeqDesc &d = L->seqs[s];
+      if ((d.method == H2O) != (pass == 0)) continue;
+      const int parts = d.method == H2O ? d.vparts : 1;
+      for (int h = 0; h < Hkv; ++h)
+        for (int p = 0; p < parts; ++p) L->comb.push_back(make_int4(s, h, p, parts));
+    }
+  for (int m = 0; m < kMethods; ++m) {
+    MethodSeqs &ms = L->of[m];
+    for (int s = 0; s < S; ++s) {
+      const SeqDesc &d = L->seqs[s];
+      if (d.method != m) continue;
+      L->lists.push_back(s);
+      ++ms.n;
+      if (m == ROCKET && d.T < d.n0) ms.max_vote_rows = std::max(ms.max_vote_rows, d.w_eff);
+      ms.max_kept = std::max(ms.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
+    }
+    std::stable_sort(L->lists.end() - ms.n, L->lists.end(),
+                     [&](int32_t a, int32_t b) { return L->seqs[a].n0 > L->seqs[b].n0; });
+    if (ms.n > 0) ms.longest = L->lists[L->lists.size() - ms.n];
+  }
+}
+
+// `lists`: fill the lists too (the sizes and offsets do not need them).
+mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_t *plen, Layout *L, bool lists) {
   mkv_status st = check_shape(shp);
   if (st != MKV_OK) return st;
   if (!cfg || !plen) return fail(MKV_EINVAL, "cfg and prompt_len must be non-NULL");
@@ -168,9 +256,7 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     off = align256(off + std::max<size_t>(bytes, 1));
     return (uint64_t)o;
   };
-  L->off_seqs = take(sizeof(SeqDesc) * S);
-  L->off_state = take(sizeof(int32_t) * S * Hkv * ST_WORDS);
-  L->off_cbtab = take(sizeof(float) * kCbRegionFloats);
+  take(1);  // no region at offset 0: a zero offset marks one the method lacks
   L->seqs.assign(S, SeqDesc{});
   int q_h2o = 0, q_rk = 0, row0 = 0;
   for (int s = 0; s < S; ++s) {
@@ -272,9 +358,6 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
   }
   // attention tiles: per sequence and kv head, ranges of `chunk` tokens over its largest active set;
   // one launch covers them all, RocketKV sequences last (their gathered tiles are the shortest)
-  L->tiles.clear();
-  L->n_tiles_uq = 0;
-  L->n_tiles_rk = 0;
   double total = 0.0;
   for (int s = 0; s < S; ++s) {
     const SeqDesc &d = L->seqs[s];
@@ -313,15 +396,24 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     for (int s = 0; s < S; ++s) n += (long long)Hkv * rule(L->seqs[s], size, &c);
     return n;
   };
+  // the smallest size lo f^i below `hi` with at most `most` tiles, by bisection (the count falls with
+  // the size); `hi` if there is none
+  auto smallest = [&](double lo, double hi, double f, long long most, auto rule) {
+    int a = 0, b = std::max(0, (int)std::ceil(std::log(hi / lo) / std::log(f)));
+    while (a < b) {
+      const int m = (a + b) / 2;
+      if (count_at(lo * std::pow(f, m), rule) <= most) b = m;
+      else a = m + 1;
+    }
+    return std::min(hi, lo * std::pow(f, a));
+  };
   // whole rounds of resident workgroups: when the size rule leaves the last round partly idle,
   // smaller tiles (down to 16 KiB) fill it, the smallest size whose count still fits in the
   // rounds begun.
   auto fill_rounds = [&]() {
     const double most = tile_bytes_for(total);
     const long long cap = (count_at(most, by_bytes) + kTileSlots - 1) / kTileSlots * kTileSlots;
-    for (double tb = 16384.0; tb < most; tb *= 1.02)
-      if (count_at(tb, by_bytes) <= cap) return tb;
-    return most;
+    return smallest(16384.0, most, 1.02, cap, by_bytes);
   };
   double tile_bytes = tile_bytes_for(total);
   long_launch = fine = count_at(tile_bytes, by_bytes) >= 3 * kTileSlots;
@@ -335,24 +427,27 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     // 1408, 1088, 704, 512.  The model puts each of these in order.)
     rule = BY_ROWS;
     double best = -1.0;
-    std::vector<double> load(kCus);
+    float load[kCus];
     for (int c = 64; c <= 1024; c += 64) {
       const double bytes = c * 4.0 * D;
       const long long n = count_at(bytes, by_bytes);
       if (n > 3 * kTileSlots && c < 1024) continue;
-      std::fill(load.begin(), load.end(), 0.0);
-      int i = 0;
+      std::fill(load, load + kCus, 0.f);
+      unsigned i = 0;
       for (int rocket = 0; rocket < 2; ++rocket)
         for (const SeqDesc &d : L->seqs) {
           if ((d.method == ROCKET) != (rocket == 1)) continue;
           int chunk;
           const int amax = d.method == ROCKET ? d.topk : d.cap, tiles = by_bytes(d, bytes, &chunk);
-          for (int h = 0; h < Hkv; ++h)
-            for (int t = 0; t < tiles; ++t) load[i++ % kCus] += 44 * 512.0 + std::min(chunk, amax - t * chunk) * 4.0 * D;
+          const float full = 44 * 512.f + chunk * 4.f * D, last = 44 * 512.f + (amax - (tiles - 1) * chunk) * 4.f * D;
+          for (int h = 0; h < Hkv; ++h) {
+            for (int t = 0; t + 1 < tiles; ++t) load[i++ % kCus] += full;
+            load[i++ % kCus] += last;
+          }
         }
       // (a d = 64 workgroup has half the bytes in flight)
       const long long busy = (n + kCus - 1) / kCus * D / 64;
-      const double cost = *std::max_element(load.begin(), load.end()) *
+      const double cost = *std::max_element(load, load + kCus) *
                           (busy <= 2 ? 1.3 : busy == 3 ? 1.1 : busy == 4 ? 1.04 : 1.0);
       if (best < 0.0 || cost < best) {
         best = cost;
@@ -364,12 +459,13 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     // (8 x 8192 tokens, three layers: uniform 4-bit 93 us at 704 tiles of 768 tokens against 105 at
     // 1408 of 384, KVQ at 4 bits 144 against 156; 16 ragged sequences of three kinds, two layers, 101
     // against 116): the smallest size that allows it, by time, up to 8 times the default.
-    if (!long_launch && n_quant == S)
-      for (double c = 4096.0; c < 8 * tile_bytes && rule == BY_BYTES; c *= 1.03)
-        if (count_at(c, by_time) <= kTileSlots) {
-          tile_bytes = c;
-          rule = BY_TIME;
-        }
+    if (!long_launch && n_quant == S) {
+      const double c = smallest(4096.0, 8 * tile_bytes, 1.03, kTileSlots, by_time);
+      if (count_at(c, by_time) <= kTileSlots) {
+        tile_bytes = c;
+        rule = BY_TIME;
+      }
+    }
     if (rule == BY_BYTES) tile_bytes = fill_rounds();
   }
   // (a layout that mkv_decode_attention_noalloc has room for under the general rule keeps it)
@@ -381,99 +477,32 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
       tile_bytes = fill_rounds();
     }
   }
+  int n_prep = 0, n_pairs = 0, n_comb = 0;
   for (int pass = 0; pass < 2; ++pass)
-  for (int s = 0; s < S; ++s) {
-    SeqDesc &d = L->seqs[s];
-    const int grp = d.method == ROCKET ? 1 : 0;
-    if (grp != pass) continue;
-    const int amax = d.method == ROCKET ? d.topk : d.cap;
-    d.tile_count = rule == BY_TIME ? by_time(d, tile_bytes, &d.chunk) : by_bytes(d, tile_bytes, &d.chunk);
-    d.tile_first = (int)L->tiles.size();
-    for (int h = 0; h < Hkv; ++h)
-      for (int t = 0; t < d.tile_count; ++t)
-        L->tiles.push_back(make_int4(s, h, t * d.chunk, std::min(amax, (t + 1) * d.chunk)));
-    if (d.method == UQ) L->n_tiles_uq += Hkv * d.tile_count;
-    if (pass == 1) L->n_tiles_rk += Hkv * d.tile_count;
-  }
-  L->n_tiles = (int)L->tiles.size();
-  // Launch order (a tile's partial slot stays tile_first + h tile_count + z / chunk, whatever its
-  // place): the quantized tiles, the longest-running per byte, spread evenly over the first 3/4 of
-  // the fp16-row and quantized tiles, the fp16-row tiles evenly over all of them, RocketKV tiles
-  // last.  Long tiles then start early enough to end with the rest, while issue-bound and
-  // bandwidth-bound tiles still share the chip throughout (measured on the mixed batch: 136-137
-  // against 140-141 us per partial launch for the sequence order; spreading the quantized tiles
-  // over 60 %, 90 % or all of the list, or putting them all first, did less or worse).
-  {
-    constexpr double kQuantSpan = 0.75;
-    auto quant = [&](const int4 &t) { const int m = L->seqs[t.x].method; return m == KVQ || m == UQ; };
-    double nq = 0, nr = 0;
-    for (const int4 &t : L->tiles)
-      if (L->seqs[t.x].method != ROCKET) (quant(t) ? nq : nr) += 1;
-    std::vector<std::pair<double, int>> key;
-    key.reserve(L->tiles.size());
-    double iq = 0, ir = 0;
-    for (int i = 0; i < (int)L->tiles.size(); ++i) {
-      const int4 &t = L->tiles[i];
-      const double v = L->seqs[t.x].method == ROCKET ? 2.0 : quant(t) ? (iq++ + 0.5) / nq * kQuantSpan : (ir++ + 0.5) / nr;
-      key.push_back({v, i});
+    for (SeqDesc &d : L->seqs) {
+      if ((d.method == ROCKET) != (pass == 1)) continue;
+      d.tile_count = rule == BY_TIME ? by_time(d, tile_bytes, &d.chunk) : by_bytes(d, tile_bytes, &d.chunk);
+      d.tile_first = L->n_tiles;
+      L->n_tiles += Hkv * d.tile_count;
+      if (d.method == UQ) L->n_tiles_uq += Hkv * d.tile_count;
+      if (pass == 1) L->n_tiles_rk += Hkv * d.tile_count;
+      n_prep += Hkv * (pass == 1 ? score_parts(d) : 1);
+      n_pairs += pass == 1 ? Hkv : 0;
+      n_comb += Hkv * (d.method == H2O ? d.vparts : 1);
     }
-    std::stable_sort(key.begin(), key.end(), [](const std::pair<double, int> &a, const std::pair<double, int> &b) {
-      return a.first < b.first;
-    });
-    std::vector<int4> ordered;
-    ordered.reserve(L->tiles.size());
-    for (const auto &kv : key) ordered.push_back(L->tiles[kv.second]);
-    L->tiles.swap(ordered);
-  }
+  L->off_tables = off;
+  L->off_seqs = take(sizeof(SeqDesc) * S);
+  L->off_state = take(sizeof(int32_t) * S * Hkv * ST_WORDS);
   L->off_tiles = take(sizeof(int4) * L->n_tiles);
-  // a decode step's append and scoring work: RocketKV scoring parts (one per kScoreTokens tokens
-  // of the largest retained set) first, then the plain appends
-  L->prep.clear();
-  L->rk_pairs.clear();
-  for (int s = 0; s < S; ++s) {
-    const SeqDesc &d = L->seqs[s];
-    if (d.method != ROCKET) continue;
-    const int parts = (d.cap + kScoreTokensPerPart - 1) / kScoreTokensPerPart;
-    for (int h = 0; h < Hkv; ++h) {
-      L->rk_pairs.push_back(make_int2(s, h));
-      for (int p = 0; p < parts; ++p) L->prep.push_back(make_int4(s, h, p, parts));
-    }
-  }
-  for (int s = 0; s < S; ++s)
-    if (L->seqs[s].method != ROCKET)
-      for (int h = 0; h < Hkv; ++h) L->prep.push_back(make_int4(s, h, -1, 0));
-  L->off_prep = take(sizeof(int4) * L->prep.size());
-  // the combine: H2O kv heads' parts (one per kCombineSlots slots) first, then one item per pair
-  L->comb.clear();
-  for (int pass = 0; pass < 2; ++pass)
-    for (int s = 0; s < S; ++s) {
-      const SeqDesc &d = L->seqs[s];
-      if ((d.method == H2O) != (pass == 0)) continue;
-      const int parts = d.method == H2O ? d.vparts : 1;
-      for (int h = 0; h < Hkv; ++h)
-        for (int p = 0; p < parts; ++p) L->comb.push_back(make_int4(s, h, p, parts));
-    }
-  L->off_comb = take(sizeof(int4) * L->comb.size());
-  L->off_rk_pairs = take(sizeof(int2) * std::max<size_t>(1, L->rk_pairs.size()));
-  L->lists.clear();
-  for (int m = 0; m < kMethods; ++m) {
-    MethodSeqs &ms = L->of[m];
-    ms = MethodSeqs{};
-    for (int s = 0; s < S; ++s) {
-      const SeqDesc &d = L->seqs[s];
-      if (d.method != m) continue;
-      L->lists.push_back(s);
-      ++ms.n;
-      if (m == ROCKET && d.T < d.n0) ms.max_vote_rows = std::max(ms.max_vote_rows, d.w_eff);
-      ms.max_kept = std::max(ms.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
-    }
-    std::stable_sort(L->lists.end() - ms.n, L->lists.end(),
-                     [&](int32_t a, int32_t b) { return L->seqs[a].n0 > L->seqs[b].n0; });
-    if (ms.n > 0) ms.longest = L->lists[L->lists.size() - ms.n];
-  }
-  L->off_lists = take(sizeof(int32_t) * L->lists.size());
+  L->off_prep = take(sizeof(int4) * n_prep);
+  L->off_comb = take(sizeof(int4) * n_comb);
+  L->off_rk_pairs = take(sizeof(int2) * n_pairs);
+  L->off_lists = take(sizeof(int32_t) * S);
+  L->off_cbtab = take(sizeof(float) * kCbRegionFloats);
+  L->tables_end = off;
   L->off_partials = take(sizeof(float) * (size_t)L->n_tiles * G * (D + 2));
   L->total = off;
+  if (lists) fill_lists(L, Hkv);
   return MKV_OK;
 }
 
@@ -483,7 +512,6 @@ struct mkv_cache {
   Shape sh{};
   std::vector<mkv_config> cfg;
   std::vector<SeqDesc> hs;  // absolute device pointers
-  Layout L;
   char *arena = nullptr;
   Dev dv{};
   Phase phase = PH_CREATED;
@@ -521,7 +549,7 @@ namespace mkv {
 mkv_status layout_tiles(const mkv_shape *shape, const mkv_config *cfg, const int32_t *prompt_len,
                         std::vector<int4> *tiles, std::vector<SeqDesc> *seqs) {
   Layout L;
-  const mkv_status st = make_layout(shape, cfg, prompt_len, &L);
+  const mkv_status st = make_layout(shape, cfg, prompt_len, &L, true);
   if (st != MKV_OK) return st;
   *tiles = L.tiles;
   *seqs = L.seqs;
@@ -550,7 +578,7 @@ mkv_status mkv_cache_bytes(const mkv_shape *shape, const mkv_config *cfg, const 
                            size_t *arena_bytes) {
   if (!arena_bytes) return fail(MKV_EINVAL, "arena_bytes is NULL");
   Layout L;
-  mkv_status st = make_layout(shape, cfg, prompt_len, &L);
+  mkv_status st = make_layout(shape, cfg, prompt_len, &L, false);
   if (st != MKV_OK) return st;
   *arena_bytes = L.total;
   return MKV_OK;
@@ -562,7 +590,7 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
   if (!out) return fail(MKV_EINVAL, "out is NULL");
   *out = nullptr;
   Layout L;
-  mkv_status st = make_layout(shape, cfg, prompt_len, &L);
+  mkv_status st = make_layout(shape, cfg, prompt_len, &L, true);
   if (st != MKV_OK) return st;
   if (!arena) return fail(MKV_EINVAL, "arena is NULL");
   if (((uintptr_t)arena & 255) != 0) return fail(MKV_EINVAL, "arena must be 256-byte aligned");
@@ -616,11 +644,9 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
                 shape->n_q_heads / shape->n_kv_heads, shape->max_new_tokens};
   c->cfg.assign(cfg, cfg + shape->n_seqs);
   c->arena = static_cast<char *>(arena);
-  c->L = L;
   const uint64_t base = (uint64_t)(uintptr_t)arena;
-  c->hs = L.seqs;
+  c->hs = std::move(L.seqs);
   for (auto &d : c->hs) {
-    // offset 0 holds the descriptor table, so a zero offset marks a region the method lacks
     for (uint64_t SeqDesc::*f : kRegionFields)
       if (d.*f) d.*f += base;
     if (d.method == H2O) {
@@ -654,24 +680,19 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
     list += L.of[m].n;
   }
   hipStream_t hst = static_cast<hipStream_t>(stream);
-  hipError_t e = hipMemcpyAsync(c->arena + L.off_seqs, c->hs.data(), sizeof(SeqDesc) * c->hs.size(),
-                                hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->arena + L.off_tiles, L.tiles.data(), sizeof(int4) * L.tiles.size(),
-                       hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->arena + L.off_prep, L.prep.data(), sizeof(int4) * L.prep.size(), hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->arena + L.off_comb, L.comb.data(), sizeof(int4) * L.comb.size(), hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess && !L.rk_pairs.empty())
-    e = hipMemcpyAsync(c->arena + L.off_rk_pairs, L.rk_pairs.data(), sizeof(int2) * L.rk_pairs.size(),
-                       hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->arena + L.off_lists, L.lists.data(), sizeof(int32_t) * L.lists.size(), hipMemcpyHostToDevice,
-                       hst);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->arena + L.off_cbtab, table, sizeof table, hipMemcpyHostToDevice, hst);
-  if (e == hipSuccess) e = launch_init_state(c->dv, c->sh, hst);
+  // the tables in one copy (each copy from pageable memory costs the host several microseconds)
+  std::vector<char> tables(L.tables_end - L.off_tables);  // zero: the state words start so
+  auto put = [&](size_t at, const void *src, size_t bytes) {
+    if (bytes > 0) std::memcpy(tables.data() + (at - L.off_tables), src, bytes);
+  };
+  put(L.off_seqs, c->hs.data(), sizeof(SeqDesc) * c->hs.size());
+  put(L.off_tiles, L.tiles.data(), sizeof(int4) * L.tiles.size());
+  put(L.off_prep, L.prep.data(), sizeof(int4) * L.prep.size());
+  put(L.off_comb, L.comb.data(), sizeof(int4) * L.comb.size());
+  put(L.off_rk_pairs, L.rk_pairs.data(), sizeof(int2) * L.rk_pairs.size());
+  put(L.off_lists, L.lists.data(), sizeof(int32_t) * L.lists.size());
+  put(L.off_cbtab, table, sizeof table);
+  hipError_t e = hipMemcpyAsync(c->arena + L.off_tables, tables.data(), tables.size(), hipMemcpyHostToDevice, hst);
   if (e == hipSuccess) e = hipStreamSynchronize(hst);
   if (e != hipSuccess) {
     mkv_cache_destroy(c);
