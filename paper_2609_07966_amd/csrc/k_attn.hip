@@ -6,7 +6,8 @@
 // takes one tile = (sequence, kv head, token range) and runs the loop for that sequence's method;
 // the 4 waves of a workgroup split the tile's tokens into contiguous ranges.  Tiles launch in an
 // order chosen on the host (quantized tiles early, RocketKV's last), so a tile writes its partial
-// to the slot its sequence, kv head and range give, not to its launch index.
+// to the slot its sequence, kv head and range give, not to its launch index.  In a step without RocketKV
+// sequences the tile that owns the new token's slot appends it first.
 //
 // Matrix path (fp16 rows, gathered rows, KVQuant): a wave handles 16 tokens per step with
 // v_mfma_f32_16x16x16_f16.  q.k is S^T = K Q^T (tokens x query heads; channels permuted so a
@@ -32,7 +33,7 @@
 // of a 32-token batch before computing any of it.
 #include <mutex>
 
-#include "kernels_common.h"
+#include "append_dev.h"
 
 // Split-K workspace of mkv_decode_attention_noalloc, for callers that cannot allocate: the
 // partial (max, sum, output) of every attention tile lives here instead of in the cache arena.
@@ -809,11 +810,11 @@ MKV_DEV void merge_waves(const float *red, int wstride, float *dst) {
   }
 }
 
-template <int D, int G>
+template <int D, int G, bool APPEND>
 __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
-    const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ state, const int4 *__restrict__ tiles,
+    const SeqDesc *__restrict__ seqs, int32_t *__restrict__ state, const int4 *__restrict__ tiles,
     const uint16_t *__restrict__ q, float *__restrict__ partials, const float *__restrict__ cbtab,
-    int Hkv, float qscale) {
+    const uint16_t *__restrict__ k_new, const uint16_t *__restrict__ v_new, int Hkv, float qscale) {
   constexpr int NW = kTileThreads / 64, NM = MG<D>::NM, CPL = MG<D>::CPL, VPL = MG<D>::VPL;
   // per wave: KVQuant value-outlier terms [G][D] while the wave runs; then the wave's (max,
   // sum, o) for the merge
@@ -833,9 +834,33 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
   const int seq = tile.x, h = tile.y;
   const SeqDesc &sd = seqs[seq];
   const int method = sd.method;
-  const int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
+  int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
   // both counts are read alongside the descriptor (not after it), then chosen by method
-  const int n_cnt = st[ST_COUNT], n_sel = st[ST_SEL_COUNT];
+  int n_cnt = st[ST_COUNT];
+  const int n_sel = st[ST_SEL_COUNT];
+  if constexpr (APPEND) {
+    // The step's token is appended here, by the tile that owns its slot: a launch of its own costs
+    // about 4.5 us, an owner's append 1-3 us while the other tiles run (8 x 4096 tokens, per layer:
+    // FP16 35.8 -> 33.4 us, uniform 4-bit 23.5 -> 20.9; 8 x 8192 under H2O-20 27.9 -> 25.0).  No other
+    // tile reads what it writes (a key block and a 4-token value block lie within a tile), and the
+    // counts that all tiles read stay until the combine launch.
+    static_assert(sizeof(AppendLds<D>) <= sizeof(s_wave), "the append's LDS fits the wave regions");
+    int victim;
+    const int pos = st[ST_NEXT_POS], at = append_slot(sd, h, n_cnt, &victim);
+    AppendLds<D> &al = *reinterpret_cast<AppendLds<D> *>(&s_wave[0][0]);
+    if (at >= tile.z && at < tile.w &&
+        append_pair<D, kTileThreads>(sd, st, load_token<D, kTileThreads>(sd, st, seq, h, Hkv, k_new, v_new, cbtab, al),
+                                     h, n_cnt, pos, at, victim, al)) {
+      // the stores have reached the CU's cache before any wave reads them
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      n_cnt += victim < 0 ? 1 : 0;
+      if (threadIdx.x == 0) {
+        st[ST_STEP_COUNT] = n_cnt;
+        st[ST_STEP_POS] = pos + 1;
+      }
+    }
+  }
   const int n_act = (method == ROCKET) ? n_sel : n_cnt;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int Hq = Hkv * G;
@@ -1072,9 +1097,9 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
 constexpr int kMaxTilesPerPair = 64;
 constexpr int kCombineThreads = 512;
 
-template <int D, int G>
+template <int D, int G, bool COMMIT>
 __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc *__restrict__ seqs,
-                                                                  const int32_t *__restrict__ state,
+                                                                  int32_t *__restrict__ state,
                                                                   const int4 *__restrict__ items,
                                                                   const float *__restrict__ partials,
                                                                   float *__restrict__ out, int Hkv) {
@@ -1095,7 +1120,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc 
   const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
   const bool merge = part == 0;
   const bool h2o = sd.method == H2O;
-  const int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
+  int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
   const float *lg = reinterpret_cast<const float *>(sd.logits) + h * stride_logits(sd, G);
   float *score = reinterpret_cast<float *>(sd.score) + h * stride_slots(sd);
   const int32_t *pos = reinterpret_cast<const int32_t *>(sd.pos) + h * stride_slots(sd);
@@ -1123,8 +1148,8 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc 
   float lgv[kU][G], scv[kU];
   int pv[kU];
   if (h2o) {
-    count = st[ST_COUNT];
-    limit = st[ST_NEXT_POS] - 1 - sd.R + 1;
+    count = st[COMMIT ? ST_STEP_COUNT : ST_COUNT];
+    limit = st[COMMIT ? ST_STEP_POS : ST_NEXT_POS] - 1 - sd.R + 1;
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int j = min(j0 + u * kCombineThreads, sd.cap - 1);
@@ -1145,6 +1170,10 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc 
   }
   __syncthreads();
   if (merge) {
+    if (COMMIT && threadIdx.x == 0) {  // the step is done (an H2O head's other parts read only the step's words)
+      st[ST_COUNT] = st[ST_STEP_COUNT];
+      st[ST_NEXT_POS] = st[ST_STEP_POS];
+    }
     const int Hq = Hkv * G;
 #pragma unroll
     for (int i = 0; i < kE; ++i) {
@@ -1217,16 +1246,18 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc 
 template <int D, int G>
 hipError_t partial_impl(const Dev &dv, const Shape &sh, const uint16_t *q, hipStream_t st, LaunchEv ev) {
   const float qscale = kLog2e / sqrtf((float)D);
+  auto kernel = dv.k_new ? k_attn_partial_mx<D, G, true> : k_attn_partial_mx<D, G, false>;
   if (dv.n_tiles > 0)
-    hipExtLaunchKernelGGL((k_attn_partial_mx<D, G>), dim3(dv.n_tiles), dim3(kTileThreads), 0, st, ev.start, ev.stop,
-                          0, dv.seqs, dv.state, dv.tiles, q, dv.partials, dv.cbtab, sh.Hkv, qscale);
+    hipExtLaunchKernelGGL(kernel, dim3(dv.n_tiles), dim3(kTileThreads), 0, st, ev.start, ev.stop, 0, dv.seqs,
+                          dv.state, dv.tiles, q, dv.partials, dv.cbtab, dv.k_new, dv.v_new, sh.Hkv, qscale);
   return hipGetLastError();
 }
 
 template <int D, int G>
 hipError_t combine_impl(const Dev &dv, const Shape &sh, float *out, hipStream_t st, LaunchEv ev) {
-  hipExtLaunchKernelGGL((k_attn_combine<D, G>), dim3(dv.n_comb), dim3(kCombineThreads), 0, st, ev.start,
-                        ev.stop, 0, dv.seqs, dv.state, dv.comb, dv.partials, out, sh.Hkv);
+  auto kernel = dv.k_new ? k_attn_combine<D, G, true> : k_attn_combine<D, G, false>;
+  hipExtLaunchKernelGGL(kernel, dim3(dv.n_comb), dim3(kCombineThreads), 0, st, ev.start, ev.stop, 0, dv.seqs,
+                        dv.state, dv.comb, dv.partials, out, sh.Hkv);
   return hipGetLastError();
 }
 

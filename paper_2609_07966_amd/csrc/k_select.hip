@@ -348,8 +348,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__rest
   }
   if (threadIdx.x == 0) {
     int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
-    st[ST_COUNT] = kept;
-    st[ST_FREE_SLOT] = kept;
+    set_counts(st, kept, n0);
     st[ST_KEPT] = kept;
   }
 }
@@ -612,7 +611,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_snap_keep(const SeqDesc *__res
   }
   if (threadIdx.x == 0) {
     int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
-    st[ST_COUNT] = kept;
+    set_counts(st, kept, n0);
     st[ST_KEPT] = kept;
   }
 }

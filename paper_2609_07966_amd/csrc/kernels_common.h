@@ -70,6 +70,14 @@ MKV_DEV void unpack8(const U4 &u, float *f) {
   f[6] = h2f(u.w); f[7] = h2f(u.w >> 16);
 }
 
+// The counts of a (sequence, kv head) and those its append of the current step leaves, alike between
+// steps.
+MKV_DEV void set_counts(int32_t *st, int count, int next_pos) {
+  static_assert(ST_COUNT == 0 && ST_NEXT_POS == 1 && ST_STEP_COUNT == 6 && ST_STEP_POS == 7, "pairs of words");
+  reinterpret_cast<int2 *>(st)[0] = make_int2(count, next_pos);
+  reinterpret_cast<int2 *>(st)[3] = make_int2(count, next_pos);
+}
+
 // 2^x on the hardware exponential unit (inputs here are <= 0; -inf gives 0)
 MKV_DEV float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

@@ -23,10 +23,12 @@ constexpr int kMethods = 5;
 enum StateWord : int32_t {
   ST_COUNT = 0,      // tokens held in the decode region (slots 0..count-1 are valid at attention time)
   ST_NEXT_POS = 1,   // position the next appended token gets
-  ST_FREE_SLOT = 2,  // H2O: slot the next token is written to
   ST_KOUT_FILL = 3,  // KVQ: entries used in the key-outlier pool
   ST_SEL_COUNT = 4,  // ROCKET: tokens selected by the last top-k
   ST_KEPT = 5,       // tokens kept after prefill (H2O / ROCKET), prompt length otherwise
+  ST_STEP_COUNT = 6,  // ST_COUNT and ST_NEXT_POS with the token of the step in progress: an
+  ST_STEP_POS = 7,    // attention launch that appends it sets them, while its other tiles still read
+                      // the former, and its combine launch copies them there
   ST_WORDS = 8
 };
 
@@ -169,6 +171,8 @@ struct Dev {
   const int2 *rk_pairs;  // device [n_rk_pairs]: the RocketKV (seq, kv head) pairs
   const int4 *comb;      // device [n_comb]: combine work (seq, kv head, part, parts)
   int n_prep, n_rk_pairs, n_comb;
+  // the step's tokens, when the attention partial launch is to append them itself (else nullptr)
+  const uint16_t *k_new = nullptr, *v_new = nullptr;
   MethodSeqs of[kMethods];
 };
 

@@ -1,0 +1,116 @@
+"""Decode steps at the edges of their tiles: appends inside the attention launch, and tile sizes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+METHODS = {
+    "fp16": {"method": "fp16"}, "uq": {"method": "uq", "bits": 4, "group": 64},
+    "kvq2": {"method": "kvq", "bits": 2, "outlier_bp": 100}, "kvq3": {"method": "kvq", "bits": 3, "outlier_bp": 100},
+    "kvq4": {"method": "kvq", "bits": 4, "outlier_bp": 0}, "h2o": {"method": "h2o", "budget_pct": 50},
+    "h2o_all": {"method": "h2o", "budget_pct": 100},
+}
+
+
+def _cache(names, lens, hkv, g, d, steps, first=0):
+    """A prefilled cache, and the prompt's rows (those of sequence s of a stream that begins at `first`)."""
+    import torch
+    from oracle import kvquant
+    from paper_2609_07966_amd.cache import KVCache
+    rows = []
+    for s, n in enumerate(lens):
+        r = np.random.default_rng(1000 + first + s)
+        rows.append([r.standard_normal((n, h, d)).astype(np.float16) for h in (hkv, hkv, hkv * g)])
+    k, v, q = (torch.from_numpy(np.concatenate([x[i] for x in rows])).cuda() for i in range(3))
+    r = np.random.default_rng(5)
+    books = [float(x) for b in (2, 3, 4) for _ in range(2)
+             for x in np.sort(r.uniform(-1, 1, 1 << b)).astype(np.float16)]
+    c = KVCache((len(lens), hkv * g, hkv, d, steps), [METHODS[m] for m in names], lens, books)
+    c.append_prompt(k, v)
+    if any(m.startswith("h2o") for m in names):
+        c.h2o_prefill(q)
+    return c, rows
+
+
+def _token(S, hkv, g, d, t):
+    import torch
+    r = np.random.default_rng(77 + t)
+    odd = lambda x: torch.from_numpy(np.concatenate([[0], x.ravel()]).astype(np.float16)).cuda()[1:].view(x.shape)
+    return tuple(odd(r.standard_normal((S, h, d))) for h in (hkv, hkv, hkv * g))
+
+
+@pytest.mark.parametrize("hkv,g,d", [(1, 1, 64), (2, 4, 128), (1, 8, 128), (3, 2, 64)])
+def test_step_appends_in_the_attention_launch(hkv, g, d):
+    """mkv_decode_step, whose attention launch appends, leaves the same codes, rows, positions, scores
+    and outputs as the separate calls, over 70 steps from lengths around the 4-token value
+    blocks, the 64-token key blocks and the tile edges (tokens that begin and end a tile)."""
+    import torch
+    from paper_2609_07966_amd._lib import MkvError
+    names = list(METHODS) * 2
+    lens = [1, 2, 3, 4, 61, 63, 64, 65, 100, 127, 128, 191, 255, 257]
+    S, steps = len(lens), 70
+    a, _ = _cache(names, lens, hkv, g, d, steps)
+    b, _ = _cache(names, lens, hkv, g, d, steps)
+    oa, ob = (torch.full((S, hkv * g, d), float("nan"), device="cuda") for _ in range(2))
+    for t in range(steps):
+        k, v, q = _token(S, hkv, g, d, t)
+        a.step(k, v, q, oa)
+        b.append(k, v)
+        b.attention(q, ob)
+        b.evict()
+        # the same tiles in the same order: only the order of atomic additions of value-outlier terms
+        # may differ, 128 of them at most a row and each a rounding of 2^-24
+        torch.testing.assert_close(oa, ob, rtol=0, atol=float(ob.abs().max()) * 2.0 ** -16, msg=f"step {t}")
+        if t % 23 and t != steps - 1:
+            continue
+        for s, m in enumerate(names):
+            for h in range(hkv):
+                assert a.counts(s, h) == b.counts(s, h), (t, s, h)
+                what = {"f": [], "u": ["codes_k", "codes_v", "scales_k", "scales_v"],
+                        "k": ["codes_k", "codes_v", "scales_k", "scales_v", "outliers_k", "outliers_v"],
+                        "h": ["positions", "scores"]}[m[0]]
+                for w in what:
+                    np.testing.assert_array_equal(a.export(s, h, w), b.export(s, h, w), err_msg=f"{w} {m} step {t}")
+    with pytest.raises(MkvError):
+        a.step(k, v, q, oa)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("name", list(METHODS))
+@pytest.mark.parametrize("hkv,g,d", [(2, 4, 128), (1, 2, 64)])
+def test_tile_sizes_do_not_change_results(name, hkv, g, d):
+    """A launch's tile sizes follow from its sequences: each of these lengths (around the 16-row and
+    32-token wave steps and the 64-token tiles) alone, in a batch of its method and beside fp16 rows
+    gives the same output up to the order of the sums; fp16 rows also match a float64 reference."""
+    import torch
+    lens = [2, 14, 15, 16, 31, 32, 127, 128, 700, 2500]
+    S = len(lens)
+    k, v, q = _token(2 * S, hkv, g, d, 0)
+
+    def run(names, lens, pick):
+        c, rows = _cache(names, lens, hkv, g, d, 1, pick[0])
+        out = torch.full((len(lens), hkv * g, d), float("nan"), device="cuda")
+        c.step(k[pick].clone(), v[pick].clone(), q[pick].clone(), out)
+        c.close()
+        return out.cpu().numpy(), rows
+
+    own, rows = run([name] * S, lens, list(range(S)))
+    mixed, _ = run([name] * S + ["fp16"] * S, lens + [4000 + 64 * s for s in range(S)], list(range(2 * S)))
+    # probabilities enter the second product in fp16, relative to a maximum that depends on the
+    # tiles: each off by at most 2^-11 of itself, so an output by 2^-11 of the largest value (below
+    # 2^3 here; quantized values lie below their rows' largest), on either side
+    tol = dict(rtol=0, atol=2.0 ** -7)
+    np.testing.assert_allclose(own, mixed[:S], **tol)
+    for s in (0, 3, S - 1):
+        alone, _ = run([name], lens[s:s + 1], [s])
+        np.testing.assert_allclose(alone[0], own[s], **tol)
+    if name != "fp16":
+        return
+    for s, (kp, vp, _) in enumerate(rows):
+        kk = np.concatenate([kp, k[s:s + 1].cpu().numpy()]).astype(np.float64)
+        vv = np.concatenate([vp, v[s:s + 1].cpu().numpy()]).astype(np.float64)
+        for e in range(hkv * g):
+            x = kk[:, e // g] @ q[s, e].cpu().numpy().astype(np.float64) / np.sqrt(d)
+            p = np.exp(x - x.max())
+            np.testing.assert_allclose(own[s, e], p @ vv[:, e // g] / p.sum(), rtol=0, atol=2.0 ** -8)
