@@ -39,11 +39,33 @@ __global__ __launch_bounds__(128) void k_append_decode(const SeqDesc *__restrict
 // other waves leave at once; a barrier waits only for waves that have not ended).  A RocketKV pair
 // has ceil(cap / kScoreTokens) parts: part 0 appends its token (rows, channel-major copy,
 // position) and every part picks the channels and scores its kScoreTokens tokens, the new one
-// from the key it holds in LDS.  The state of a RocketKV pair is left to the selecting launch.
+// from the key it holds in LDS.  The state of a RocketKV pair is left to the selecting launch.  Where
+// every pair has one part (SELECT: caps up to kScoreTokens tokens), that workgroup selects from the
+// keys it has in LDS and there is no selecting launch.
 //
 // k_rocket_select, one workgroup of kTopkThreads threads per RocketKV pair (int2: seq, kv head):
 // the top-k of the scores, then the pair's state (count, next position, selection count).
-template <int D, int G>
+// The selection of a pair with n tokens (the new one included, if there was room for it) from the keys
+// src(j), and the pair's state after the step; count and pos are those before it, read by every thread
+// before a barrier.
+template <int NTH, int KR, typename Src>
+MKV_DEV void rocket_select(const SeqDesc &sd, int32_t *st, int h, int n, bool room, int count, int pos, Src src,
+                           SelLds &L) {
+  const int k = sd.topk;
+  int32_t *sel = reinterpret_cast<int32_t *>(sd.sel) + h * stride_sel(sd);
+  if (k >= n) {
+    for (int j = threadIdx.x; j < n; j += NTH) sel[j] = j;
+  } else {
+    select_keys<NTH, KR>(n, k, src, sel, L);
+  }
+  __syncthreads();  // every thread has read the state
+  if (threadIdx.x == 0) {
+    st[ST_SEL_COUNT] = min(k, n);
+    if (room) set_counts(st, count + 1, pos + 1);
+  }
+}
+
+template <int D, int G, bool SELECT>
 __global__ __launch_bounds__(kScoreThreads) void k_append_score(const SeqDesc *__restrict__ seqs, int32_t *state,
                                                                 const int4 *__restrict__ items,
                                                                 const uint16_t *__restrict__ k,
@@ -54,6 +76,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_append_score(const SeqDesc *_
     AppendLds<D> a;
     ChanLds<D, kScoreThreads> c;
   } L;
+  __shared__ SelLds s_sel;
+  __shared__ uint32_t s_keys[SELECT ? kScoreTokens : 1];
   const int4 it = items[blockIdx.x];
   const int seq = it.x, h = it.y, part = it.z, c = threadIdx.x;
   const SeqDesc &sd = seqs[seq];
@@ -66,22 +90,32 @@ __global__ __launch_bounds__(kScoreThreads) void k_append_score(const SeqDesc *_
   // the query channels first: their address needs only the work item
   uint16_t qr[G];
   load_qcol<D, G>(q + ((size_t)seq * Hkv * G + h * G) * D, qr);
-  const int count = st[ST_COUNT];
+  const size_t at = ((size_t)seq * Hkv + h) * D + min(c, D - 1);
+  const uint16_t kb = k[at], vb = part == 0 ? v[at] : (uint16_t)0;
+  const int count = st[ST_COUNT], pos = st[ST_NEXT_POS];
   // a full region (reachable only by replaying a captured decode step past max_new_tokens) drops
   // the token, as the separate append does
   const bool room = count < sd.cap;
   if (room && c < D) {
-    const uint16_t kb = k[((size_t)seq * Hkv + h) * D + c];
     L.c.knew[c] = kb;
     if (part == 0) {
-      const uint16_t vb = v[((size_t)seq * Hkv + h) * D + c];
       (reinterpret_cast<uint16_t *>(sd.k) + h * stride_rows(sd, D))[(size_t)count * D + c] = kb;
       (reinterpret_cast<uint16_t *>(sd.v) + h * stride_rows(sd, D))[(size_t)count * D + c] = vb;
       (reinterpret_cast<uint16_t *>(sd.kcm) + h * stride_kcm(sd, D))[(size_t)c * sd.cstride + count] = kb;
-      if (c == 0) (reinterpret_cast<int32_t *>(sd.pos) + h * stride_slots(sd))[count] = st[ST_NEXT_POS];
+      if (c == 0) (reinterpret_cast<int32_t *>(sd.pos) + h * stride_slots(sd))[count] = pos;
     }
   }
-  score_part<D, G>(sd, h, room ? count + 1 : count, part, room, qr, L.c);
+  const int n = room ? count + 1 : count;
+  uint32_t *akeys = reinterpret_cast<uint32_t *>(sd.akeys) + h * stride_slots(sd);
+  score_part<D, G>(sd, h, n, part, room, qr, L.c, [&](int j, uint32_t key) {
+    if constexpr (SELECT) s_keys[j] = key;
+    else gst(akeys + j, key);
+  });
+  if constexpr (SELECT) {
+    __syncthreads();
+    rocket_select<kScoreThreads, kScoreTokens / kScoreThreads>(
+        sd, st, h, n, room, count, pos, [&](int j) { return s_keys[j]; }, s_sel);
+  }
 }
 
 template <int D>
@@ -89,24 +123,14 @@ __global__ __launch_bounds__(kTopkThreads) void k_rocket_select(const SeqDesc *_
                                                                 const int2 *__restrict__ pairs, int Hkv) {
   __shared__ SelLds L;
   const int2 pr = pairs[blockIdx.x];
-  const int seq = pr.x, h = pr.y, tid = threadIdx.x;
+  const int seq = pr.x, h = pr.y;
   const SeqDesc &sd = seqs[seq];
   int32_t *st = state + ((size_t)seq * Hkv + h) * ST_WORDS;
   const int count = st[ST_COUNT], pos = st[ST_NEXT_POS];
   const bool room = count < sd.cap;
-  const int n = room ? count + 1 : count, k = sd.topk;
-  int32_t *sel = reinterpret_cast<int32_t *>(sd.sel) + h * stride_sel(sd);
-  if (k >= n) {
-    for (int j = tid; j < n; j += kTopkThreads) sel[j] = j;
-  } else {
-    const uint32_t *akeys = reinterpret_cast<const uint32_t *>(sd.akeys) + h * stride_slots(sd);
-    select_keys<kTopkThreads>(n, k, [&](int j) { return gld(akeys + j); }, sel, L);
-  }
-  __syncthreads();  // every thread has read the state
-  if (tid == 0) {
-    st[ST_SEL_COUNT] = min(k, n);
-    if (room) set_counts(st, count + 1, pos + 1);
-  }
+  const uint32_t *akeys = reinterpret_cast<const uint32_t *>(sd.akeys) + h * stride_slots(sd);
+  rocket_select<kTopkThreads, kRegKeys>(
+      sd, st, h, room ? count + 1 : count, room, count, pos, [&](int j) { return gld(akeys + j); }, L);
 }
 
 // ---- prefill: every sequence of a method in one launch per stage ---------------------------------
@@ -690,8 +714,15 @@ hipError_t append_decode_impl(const Dev &dv, const Shape &sh, const uint16_t *k,
 template <int D, int G>
 hipError_t append_select_impl(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                               const uint16_t *q, hipStream_t st, LaunchEv ev_score, LaunchEv ev_select) {
-  hipExtLaunchKernelGGL((k_append_score<D, G>), dim3(dv.n_prep), dim3(kScoreThreads), 0, st, ev_score.start,
-                        ev_score.stop, 0, dv.seqs, dv.state, dv.prep, k, v, q, dv.cbtab, sh.Hkv);
+  // one item per (sequence, kv head): every RocketKV pair has one part, which selects (unless the
+  // selections are timed).  Per step, 8 kv heads, keeping an eighth: one sequence of 300 tokens 19.9 us
+  // with the second launch, 16.7 without; 48 of 500 tokens 25.5 and 20.7.  Pairs of more parts would
+  // wait for all of them, or score over 1024 tokens on one CU.
+  const bool fused = dv.n_prep == sh.S * sh.Hkv && ev_select.start == nullptr;
+  auto kernel = fused ? k_append_score<D, G, true> : k_append_score<D, G, false>;
+  hipExtLaunchKernelGGL(kernel, dim3(dv.n_prep), dim3(kScoreThreads), 0, st, ev_score.start, ev_score.stop, 0,
+                        dv.seqs, dv.state, dv.prep, k, v, q, dv.cbtab, sh.Hkv);
+  if (fused) return hipGetLastError();
   hipExtLaunchKernelGGL(k_rocket_select<D>, dim3(dv.n_rk_pairs), dim3(kTopkThreads), 0, st, ev_select.start,
                         ev_select.stop, 0, dv.seqs, dv.state, dv.rk_pairs, sh.Hkv);
   return hipGetLastError();

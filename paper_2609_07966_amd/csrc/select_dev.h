@@ -169,7 +169,7 @@ MKV_DEV void score_tokens(const uint16_t *kcm, int cstride, int j0, int nch, con
 // radix passes of 8 bits: digit counts go to kTopkHists LDS histograms by atomics (one per run of
 // equal digits in a thread's keys), and wave 0
 // finds the digit by a scan over lanes while the other waves clear the next pass's histogram set
-// (2 barriers per pass).  Then counts of keys above and equal to the threshold before each run,
+// (2 barriers per pass; the passes end when all keys with the prefix so far are taken).  Then counts of keys above and equal to the threshold before each run,
 // by one block scan, place every thread's selected indices.  Keys written by other threads of the
 // workgroup must be visible on entry.
 template <int NTH, int KR = kRegKeys, typename Src>
@@ -233,6 +233,7 @@ MKV_DEV void select_keys(int n, int k, Src src, int32_t *sel, SelLds &L) {
         if (above < remaining && remaining <= above + cnt[i]) {
           L.s3[0] = 255 - (4 * lane + i);
           L.s3[1] = remaining - above;
+          L.s3[2] = remaining - above == cnt[i];
         }
         above += cnt[i];
       }
@@ -243,13 +244,19 @@ MKV_DEV void select_keys(int n, int k, Src src, int32_t *sel, SelLds &L) {
     prefix |= (uint32_t)L.s3[0] << shift;
     mask |= 255u << shift;
     remaining = L.s3[1];
+    // every key with this prefix is taken: its other digits decide nothing (mostly after three
+    // passes, whose 24 bits leave few equal keys)
+    if (L.s3[2]) break;
   }
+  // the threshold: keys above it are taken, and the first `need` of those equal to it (after an early
+  // end all of those with its leading digits)
   const uint32_t kth = prefix;
   const int need = remaining;  // keys equal to kth that are taken (the lowest indices)
   int gt = 0, eq = 0;
   each([&](int, uint32_t key) {
-    gt += key > kth ? 1 : 0;
-    eq += key == kth ? 1 : 0;
+    const uint32_t lead = key & mask;
+    gt += lead > kth ? 1 : 0;
+    eq += lead == kth ? 1 : 0;
   });
   // one scan of both counts when n < 2^15 keeps them apart in the two halves of a word
   int tot, gt_before, eq_run;
@@ -263,8 +270,9 @@ MKV_DEV void select_keys(int n, int k, Src src, int32_t *sel, SelLds &L) {
   }
   int slot = gt_before + min(eq_run, need);
   each([&](int u, uint32_t key) {
-    const bool take = key > kth || (key == kth && eq_run < need);
-    eq_run += key == kth ? 1 : 0;
+    const uint32_t lead = key & mask;
+    const bool take = lead > kth || (lead == kth && eq_run < need);
+    eq_run += lead == kth ? 1 : 0;
     if (take && slot < k) gst(sel + slot, ja + u);
     slot += take ? 1 : 0;
   });
@@ -273,26 +281,24 @@ MKV_DEV void select_keys(int n, int k, Src src, int32_t *sel, SelLds &L) {
 // ---- a decode step's scoring workgroups -----------------------------------------------------------
 // Part `part` of a RocketKV (sequence, kv head) with n retained tokens (the new one included):
 // the channel pick (every part makes it, from the query channels qr; part 0 also writes it out)
-// and the scores of tokens [part kScoreTokens, (part + 1) kScoreTokens), as keys into the
-// head's global key array.
+// and the scores of tokens [part kScoreTokens, (part + 1) kScoreTokens): put(token, key).
 // L.knew must hold the new token's key (token n - 1) when `has_new`; the pick's barriers publish it.
-template <int D, int G>
+template <int D, int G, typename Put>
 MKV_DEV void score_part(const SeqDesc &sd, int h, int n, int part, bool has_new, const uint16_t (&qr)[G],
-                        ChanLds<D, kScoreThreads> &L) {
+                        ChanLds<D, kScoreThreads> &L, Put put) {
   const int tid = threadIdx.x;
   const int nch = channel_pick<D, G, kScoreThreads>(sd, qr, L);
   if (part == 0)
     for (int i = tid; i < nch; i += kScoreThreads) (reinterpret_cast<int32_t *>(sd.aux1) + (size_t)h * D)[i] = L.sel_ch[i];
   if (sd.topk >= n) return;  // every token is selected; no scores needed
   const uint16_t *kcm = reinterpret_cast<const uint16_t *>(sd.kcm) + h * stride_kcm(sd, D);
-  uint32_t *akeys = reinterpret_cast<uint32_t *>(sd.akeys) + h * stride_slots(sd);
   const int j0 = part * kScoreTokens + 4 * tid;
   if (j0 >= n) return;
   float acc[4];
   score_tokens<4, 32>(kcm, sd.cstride, j0, nch, L.sel_ch, L.sel_qb, has_new ? n - 1 : -1, L.knew, acc);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
-    if (j0 + r < n) gst(akeys + j0 + r, float_key(acc[r]));
+    if (j0 + r < n) put(j0 + r, float_key(acc[r]));
 }
 
 // ---- the stand-alone top-k: one workgroup of kTopkThreads threads per (sequence, kv head) -------

@@ -114,3 +114,41 @@ def test_tile_sizes_do_not_change_results(name, hkv, g, d):
             x = kk[:, e // g] @ q[s, e].cpu().numpy().astype(np.float64) / np.sqrt(d)
             p = np.exp(x - x.max())
             np.testing.assert_allclose(own[s, e], p @ vv[:, e // g] / p.sum(), rtol=0, atol=2.0 ** -8)
+
+
+@pytest.mark.parametrize("longest", [1021, 1023, 1500])
+@pytest.mark.parametrize("hkv,g,d", [(2, 4, 128), (1, 1, 64)])
+def test_selections_with_ties(hkv, g, d, longest):
+    """RocketKV steps whose top-k is chosen in the scoring launch (no pair holds over 1024 tokens) and in a
+    launch of its own (longest = 1500): the exact top-k of the approximate scores, with keys of
+    few values so that equal scores cross the threshold, with all keys equal, and with all kept."""
+    import torch
+    from oracle import rocketkv
+    from paper_2609_07966_amd.cache import KVCache
+    lens, topk, nch, steps = [40, 130, 255, 600, 900, longest], [7, 64, 255, 299, 1, 512], 16, 3
+    cfgs = [{"method": "rocket", "keep_tokens": 4096, "window": 32, "pool": 7, "topk": t, "n_channels": nch} for t in topk]
+    r = np.random.default_rng(d + longest)
+    S, at = len(lens), np.concatenate([[0], np.cumsum(lens)])
+    k = r.integers(-2, 3, (at[-1], hkv, d)).astype(np.float16)
+    k[at[3]:at[4]] = 1.0
+    k[at[5]:] = r.standard_normal((longest, hkv, d)).astype(np.float16)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    c = KVCache((S, hkv * g, hkv, d, steps), cfgs, lens)
+    c.append_prompt(dev(k), dev(k))
+    c.snap_prefill(dev(r.standard_normal((32 * S, hkv * g, d)).astype(np.float16)))
+    out = torch.empty((S, hkv * g, d), dtype=torch.float32, device="cuda")
+    rows = [k[at[s]:at[s + 1]] for s in range(S)]
+    for t in range(steps):
+        kn = r.integers(-2, 3, (S, hkv, d)).astype(np.float16)
+        q = r.integers(-3, 4, (S, hkv * g, d)).astype(np.float16)
+        c.step(dev(kn), dev(kn), dev(q), out)
+        for s in range(S):
+            rows[s] = np.concatenate([rows[s], kn[s][None]])
+            for h in range(hkv):
+                hq = q[s, h * g:(h + 1) * g]
+                scores = rocketkv.approx_scores(hq, rows[s][:, h], rocketkv.select_channels(hq, nch))
+                np.testing.assert_array_equal(c.export(s, h, "topk"), rocketkv.topk_indices(scores, topk[s]),
+                                              err_msg=f"sequence {s} head {h} step {t}")
+                n = lens[s] + t + 1
+                assert c.counts(s, h) == (n, n, min(topk[s], n), lens[s])
+    c.close()
