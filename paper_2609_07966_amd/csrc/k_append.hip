@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_append_score(const SeqDesc *_
   if constexpr (SELECT) {
     __syncthreads();
     rocket_select<kScoreThreads, kScoreTokens / kScoreThreads>(
-        sd, st, h, n, room, count, pos, [&](int j) { return s_keys[j]; }, s_sel);
+        sd, st, h, n, room, count, pos, LdsKeys{s_keys}, s_sel);
   }
 }
 
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_rocket_select(const SeqDesc *_
   const bool room = count < sd.cap;
   const uint32_t *akeys = reinterpret_cast<const uint32_t *>(sd.akeys) + h * stride_slots(sd);
   rocket_select<kTopkThreads, kRegKeys>(
-      sd, st, h, room ? count + 1 : count, room, count, pos, [&](int j) { return gld(akeys + j); }, L);
+      sd, st, h, room ? count + 1 : count, room, count, pos, KeyRow{akeys}, L);
 }
 
 // ---- prefill: every sequence of a method in one launch per stage ---------------------------------

@@ -67,12 +67,14 @@ struct ScoreStage {
   uint4 row[2][kScoreTile][D / 8 + 1];
 };
 
-// Sums over the 32 lanes of each half wave: lane lr gets the total of v[lr].  At step o the lanes with
-// bit o clear keep the even values of each pair and the others the odd ones.
-MKV_DEV float half_wave_sums(float (&v)[32]) {
+// Sums over the 32 lanes of each half wave: lane lr gets the total of v[lr % N].  At step o the lanes
+// with bit o clear keep the even values of each pair and the others the odd ones.
+template <int N>
+MKV_DEV float half_wave_sums(float (&v)[N]) {
+  static_assert(N == 16 || N == 32, "a value per lane, or per two lanes");
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int o = 1, n = 32; o < 32; o <<= 1, n >>= 1) {
+  for (int o = 1, n = N; n > 1; o <<= 1, n >>= 1) {
     const bool odd = lane & o;
 #pragma unroll
     for (int i = 0; i < n / 2; ++i) {
@@ -80,7 +82,7 @@ MKV_DEV float half_wave_sums(float (&v)[32]) {
       v[i] = keep + __shfl_xor(send, o);
     }
   }
-  return v[0];
+  return N == 32 ? v[0] : v[0] + __shfl_xor(v[0], 16);
 }
 
 // Query row of virtual row r (clamped to the prompt) of kv head h, in 16-byte units.
@@ -308,6 +310,17 @@ __global__ __launch_bounds__(NT) void k_h2o_sum(const SeqDesc *__restrict__ seqs
   gst(reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0 + j, acc);
 }
 
+// Keys of the scores at and before p, in descending order of position.
+struct ReversedScores {
+  const float *p;
+  MKV_DEV uint32_t operator()(int i) const { return float_key(gld(p - i)); }
+  MKV_DEV uint4 four(int i) const {
+    const uint4 x = gld16w(reinterpret_cast<const uint32_t *>(p - i - 3));
+    return make_uint4(float_key(__uint_as_float(x.w)), float_key(__uint_as_float(x.z)),
+                      float_key(__uint_as_float(x.y)), float_key(__uint_as_float(x.x)));
+  }
+};
+
 // Keep the R most recent prompt tokens plus the top B - R scores of the rest (newer on ties): their
 // positions into slots 0..kept-1 in ascending order, and the head's state.  The selection runs over
 // the candidates in reverse order (index ncand - 1 - j), so that its lower-index tie rule prefers
@@ -332,7 +345,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_h2o_keep(const SeqDesc *__rest
     if (H > 0) {
       // the scratch of the row statistics (no longer needed) takes the reversed selection
       int32_t *rsel = reinterpret_cast<int32_t *>(sd.aux1) + (size_t)h * n0;
-      select_keys<kTopkThreads, 32>(ncand, H, [&](int i) { return float_key(gld(S + (ncand - 1 - i))); }, rsel, L);
+      select_keys<kTopkThreads, 32>(ncand, H, ReversedScores{S + (ncand - 1)}, rsel, L);
       __syncthreads();
       for (int i = threadIdx.x; i < H; i += kTopkThreads) pos[H - 1 - i] = ncand - 1 - gld(rsel + i);
     }
@@ -394,24 +407,27 @@ __global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ s
 
 // ---- SnapKV prefill -------------------------------------------------------------------------------
 // Window row r = i * G + g (query head h*G + g at position n0 - w + i; it attends to keys
-// 0 .. n0 - w + i).  Pass 1: per 256-key chunk the partial (max, sum of exp2) of every row.  Pass 2:
-// each row's partials merged.  Pass 3: the votes of a chunk's keys, the logits recomputed.  Pass 4: max
+// 0 .. n0 - w + i).  Pass 1: per span of keys the partial (max, sum of exp2) of every row.  Pass 2:
+// each row's partials merged.  Pass 3: the votes of a span's keys, the logits recomputed.  Pass 4: max
 // pooling into order-preserving keys.  Pass 5: the selection; pass 6: the kept rows gathered.  Every
 // pass is one launch over all RocketKV sequences (grid as for H2O).
 //
 // Logit tiles as in the H2O scoring: S^T = K Q^T, a lane owning one row and 16 keys of a 32 x 32 tile.
-// A wave holds 64 keys in registers and takes the window rows from LDS, 64 staged at a time, so K is
-// read once per pass, straight into operands.  4 prompts of 32768 tokens (268 MB of K a pass): row
-// statistics 96 us and votes 81, where per-row shuffles and launches per sequence took 231 and 146.
-constexpr int SNAP_CHUNK = 256;  // keys per workgroup: 64 per wave
-constexpr int SNAP_ROWS = 64;    // window rows staged in LDS at a time
+// A workgroup takes a span of keys and holds ROWS window rows in LDS; a wave holds 32 keys as operands,
+// loaded while it computes the 32 before, so the loads of K run under the products and exponentials
+// and the rows are staged once per span.  (With one chunk of 256 keys per workgroup and the rows
+// staged 64 at a time, every workgroup waited for its keys and again for its rows.)  4 prompts of
+// 32768 tokens (268 MB of K a pass): row statistics 78 us and votes 62, before 96 and 81.
+constexpr int SNAP_CHUNK = 256;  // the shortest span (the scratch holds a partial per chunk and row)
+constexpr int SNAP_KEYS = 32 * (NT / 64);  // keys a workgroup takes at a time
 
-// The window rows [r0, r0 + 64) (clamped to the last row) as fp16 operands in LDS.
-template <int D>
+// The window rows [r0, r0 + ROWS) (clamped to the last row) as fp16 operands in LDS.
+template <int D, int ROWS>
 MKV_DEV void stage_window(uint4 (*sq)[D / 8 + 1], const uint16_t *qw, const SeqDesc &sd, int h, int lg, int Hq, int rows,
                           int r0) {
   constexpr int U = D / 8;
-  for (int e = threadIdx.x; e < SNAP_ROWS * U; e += NT) {
+  const int n = min(ROWS, (rows - r0 + 31) & ~31);
+  for (int e = threadIdx.x; e < n * U; e += NT) {
     const int rr = e / U, u = e % U;
     const int r = min(r0 + rr, rows - 1), i = r >> lg, g = r & ((1 << lg) - 1);
     // the last w_eff of the `window` rows
@@ -420,86 +436,102 @@ MKV_DEV void stage_window(uint4 (*sq)[D / 8 + 1], const uint16_t *qw, const SeqD
   }
 }
 
-// A wave's 64 keys as matrix operands: key 32 u + lr, channels 8 lh .. 8 lh + 7 of k-step s.
-template <int D>
-MKV_DEV void snap_key_operands(const SeqDesc &sd, int h, int key0, uint4 (&ka)[2][D / 16]) {
+// f(key0, operands) over a wave's steps of 32 keys in the span [a, b): key key0 + lr, channels
+// 8 lh .. 8 lh + 7 of k-step s, the next step's loads in flight (keys past the prompt: its last).
+template <int D, typename F>
+MKV_DEV void snap_steps(const SeqDesc &sd, int h, int a, int b, F f) {
   constexpr int U = D / 8;
   const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
                                                     h * stride_stage(sd, D));
-  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5, last = sd.n0 - 1;
+  auto load = [&](int key0, uint4 (&ka)[D / 16]) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s)
-      ka[u][s] = gld16(ks + (size_t)min(key0 + 32 * u + lr, sd.n0 - 1) * U + 2 * s + lh);
-}
-
-template <int D>
-MKV_DEV void snap_logits(const uint4 (&ka)[2][D / 16], const uint4 (*sq)[D / 8 + 1], int row, int lh, f16v (&S)[2]) {
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s) {
-    const uint4 b = sq[row][2 * s + lh];
-    S[0] = mfma32(ka[0][s], b, S[0]);
-    S[1] = mfma32(ka[1][s], b, S[1]);
+    for (int s = 0; s < D / 16; ++s) ka[s] = gld16(ks + (size_t)min(key0 + lr, last) * U + 2 * s + lh);
+  };
+  uint4 x[D / 16], y[D / 16];
+  int key0 = a + 32 * (threadIdx.x >> 6);
+  if (key0 < b) load(key0, x);
+  for (; key0 < b; key0 += 2 * SNAP_KEYS) {
+    load(key0 + SNAP_KEYS, y);
+    f(key0, x);
+    if (key0 + SNAP_KEYS >= b) break;
+    load(key0 + 2 * SNAP_KEYS, x);
+    f(key0 + SNAP_KEYS, y);
   }
 }
 
 template <int D>
+MKV_DEV f16v snap_logits(const uint4 (&ka)[D / 16], const uint4 (*sq)[D / 8 + 1], int row, int lh) {
+  f16v S = {};
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) S = mfma32(ka[s], sq[row][2 * s + lh], S);
+  return S;
+}
+
+template <int D, int ROWS>
 __global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict__ seqs,
                                                       const int32_t *__restrict__ list,
                                                       const uint16_t *__restrict__ qw, int Hq, int Hkv, int lg,
-                                                      float scale2) {
-  __shared__ uint4 sq[SNAP_ROWS][D / 8 + 1];
-  __shared__ float2 s_part[NT / 64][SNAP_ROWS];
+                                                      int span, float scale2) {
+  constexpr int kTiles = ROWS / 32, kParts = 2 * (NT / 64);
+  __shared__ uint4 sq[ROWS][D / 8 + 1];
+  float2(*s_part)[ROWS] = reinterpret_cast<float2(*)[ROWS]>(&sq[0][0]);  // once the rows are used
+  static_assert(sizeof(float2) * kParts * ROWS <= sizeof(sq), "the partials fit the rows");
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, chunk = (int)blockIdx.x / Hkv;
-  const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
-  if (chunk >= nchunk || sd.T >= n0) return;
+  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, a = (int)blockIdx.x / Hkv * span;
+  if (a >= n0 || sd.T >= n0) return;
+  const int nspan = (n0 + span - 1) / span, b = min(a + span, n0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
-  const int key0 = chunk * SNAP_CHUNK + 64 * wave;
-  uint4 ka[2][D / 16];
-  snap_key_operands<D>(sd, h, key0, ka);
   const int rows = w << lg;
-  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * rows * nchunk;
-  for (int r0 = 0; r0 < rows; r0 += SNAP_ROWS) {
-    stage_window<D>(sq, qw, sd, h, lg, Hq, rows, r0);
+  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * rows * nspan;
+  for (int r0 = 0; r0 < rows; r0 += ROWS) {
+    if (r0 > 0) __syncthreads();
+    stage_window<D, ROWS>(sq, qw, sd, h, lg, Hq, rows, r0);
     __syncthreads();
-#pragma unroll 1
-    for (int t = 0; t < SNAP_ROWS / 32 && r0 + 32 * t < rows; ++t) {
-      f16v S[2] = {};
-      snap_logits<D>(ka, sq, 32 * t + lr, lh, S);
-      if (key0 + 63 > n0 - w) {
-        const int rel = n0 - w + ((r0 + 32 * t + lr) >> lg) - key0 - 4 * lh;  // compared with constants
-        const int end = n0 - 1 - key0 - 4 * lh;
+    // the lane's (max, sum of exp2) of row r0 + 32 t + lr over its own keys
+    float m[kTiles], l[kTiles];
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-          const int c = 32 * (i / 16) + 8 * ((i / 4) & 3) + (i & 3);
-          S[i / 16][i % 16] = c <= min(rel, end) ? S[i / 16][i % 16] : -INFINITY;
+    for (int t = 0; t < kTiles; ++t) m[t] = -INFINITY, l[t] = 0.f;
+    snap_steps<D>(sd, h, a, b, [&](int key0, const uint4 (&ka)[D / 16]) {
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) {
+        if (r0 + 32 * t >= rows) continue;
+        f16v S = snap_logits<D>(ka, sq, 32 * t + lr, lh);
+        if (key0 + 31 > n0 - w) {
+          const int rel = n0 - w + ((r0 + 32 * t + lr) >> lg) - key0 - 4 * lh;  // compared with constants
+          const int end = n0 - 1 - key0 - 4 * lh;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int c = 8 * (i / 4) + (i & 3);
+            S[i] = c <= min(rel, end) ? S[i] : -INFINITY;
+          }
         }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[i]);
+        mx = fmaxf(m[t], mx * scale2);
+        const float ref = mx == -INFINITY ? 0.f : mx;  // no visible key yet: a sum of 0
+        float u[2] = {l[t] * fexp2(m[t] - ref), 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) u[i & 1] += fexp2(fmaf(S[i], scale2, -ref));
+        l[t] = u[0] + u[1];
+        m[t] = mx;
       }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 32; ++i) mx = fmaxf(mx, S[i / 16][i % 16]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale2;
-      const float ref = mx == -INFINITY ? 0.f : mx;  // no key of the wave's is visible: a sum of 0
-      float l[2] = {0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 32; ++i) l[i & 1] += fexp2(fmaf(S[i / 16][i % 16], scale2, -ref));
-      l[0] += l[1];
-      l[0] += __shfl_xor(l[0], 32);
-      if (lh == 0) s_part[wave][32 * t + lr] = make_float2(mx, l[0]);
-    }
+    });
     __syncthreads();
-    if (threadIdx.x < SNAP_ROWS && r0 + (int)threadIdx.x < rows) {
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) s_part[2 * wave + lh][32 * t + lr] = make_float2(m[t], l[t]);
+    __syncthreads();
+    for (int r = threadIdx.x; r < ROWS && r0 + r < rows; r += NT) {
       float M = -INFINITY, L = 0.f;
 #pragma unroll
-      for (int v = 0; v < NT / 64; ++v) M = fmaxf(M, s_part[v][threadIdx.x].x);
+      for (int v = 0; v < kParts; ++v) M = fmaxf(M, s_part[v][r].x);
 #pragma unroll
-      for (int v = 0; v < NT / 64; ++v) {
-        const float2 p = s_part[v][threadIdx.x];
+      for (int v = 0; v < kParts; ++v) {
+        const float2 p = s_part[v][r];
         L += p.x == -INFINITY ? 0.f : p.y * fexp2(p.x - M);
       }
-      part[(size_t)(r0 + threadIdx.x) * nchunk + chunk] = make_float2(M, L);
+      part[(size_t)(r0 + r) * nspan + a / span] = make_float2(M, L);
     }
   }
 }
@@ -507,10 +539,10 @@ __global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict_
 // Merge each window row's partials (one wave per row); entry 0 of the row then holds (max, 1 / sum of
 // exp2) over all its keys.
 __global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
-                                                   int Hkv, int lg) {
+                                                   int Hkv, int lg, int span) {
   const SeqDesc &sd = seqs[list[blockIdx.y]];
   const int n0 = sd.n0, rows = sd.w_eff << lg, h = blockIdx.x % Hkv;
-  const int np = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
+  const int np = (n0 + span - 1) / span;
   const int lane = threadIdx.x & 63, r = (int)blockIdx.x / Hkv * (NT / 64) + (threadIdx.x >> 6);
   if (r >= rows || sd.T >= n0) return;
   float2 *pr = reinterpret_cast<float2 *>(sd.aux1) + ((size_t)h * rows + r) * np;
@@ -527,49 +559,52 @@ __global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ s
   if (lane == 0) pr[0] = make_float2(M, 1.f / L);
 }
 
-// Votes of a chunk's keys before the window: sum over the window rows of exp2(s - M_r) / L_r.  (Window
+// Votes of a span's keys before the window: sum over the window rows of exp2(s - M_r) / L_r.  (Window
 // keys get sums too, over rows that do not see them; they are not written.)
-template <int D>
+template <int D, int ROWS>
 __global__ __launch_bounds__(NT) void k_snap_votes(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
                                                    const uint16_t *__restrict__ qw, int Hq, int Hkv, int lg,
-                                                   float scale2) {
-  __shared__ uint4 sq[SNAP_ROWS][D / 8 + 1];
-  __shared__ float2 sml[SNAP_ROWS];  // (M, 1 / L) of the staged rows
+                                                   int span, float scale2) {
+  constexpr int kTiles = ROWS / 32;
+  __shared__ uint4 sq[ROWS][D / 8 + 1];
+  __shared__ float2 sml[ROWS];  // (M, 1 / L) of the staged rows
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, chunk = (int)blockIdx.x / Hkv;
-  const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
-  if (chunk >= nchunk || sd.T >= n0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
-  const int key0 = chunk * SNAP_CHUNK + 64 * wave;
-  uint4 ka[2][D / 16];
-  snap_key_operands<D>(sd, h, key0, ka);
+  const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, a = (int)blockIdx.x / Hkv * span;
+  if (a >= n0 - w || sd.T >= n0) return;
+  const int nspan = (n0 + span - 1) / span, b = min(a + span, n0 - w);
+  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const int rows = w << lg;
-  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * rows * nchunk;
-  float acc[32];
-#pragma unroll
-  for (int i = 0; i < 32; ++i) acc[i] = 0.f;
-  for (int r0 = 0; r0 < rows; r0 += SNAP_ROWS) {
-    __syncthreads();
-    stage_window<D>(sq, qw, sd, h, lg, Hq, rows, r0);
-    if (threadIdx.x < SNAP_ROWS) {
-      const int r = r0 + (int)threadIdx.x;
-      const float *ml = reinterpret_cast<const float *>(part + (size_t)min(r, rows - 1) * nchunk);
+  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * rows * nspan;
+  float *votes = reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0;
+  for (int r0 = 0; r0 < rows; r0 += ROWS) {
+    if (r0 > 0) __syncthreads();
+    stage_window<D, ROWS>(sq, qw, sd, h, lg, Hq, rows, r0);
+    for (int t = threadIdx.x; t < ROWS; t += NT) {
+      const float *ml = reinterpret_cast<const float *>(part + (size_t)min(r0 + t, rows - 1) * nspan);
       const float iL = gld(ml + 1);
-      sml[threadIdx.x] = make_float2(gld(ml), r < rows ? iL : 0.f);
+      sml[t] = make_float2(gld(ml), r0 + t < rows ? iL : 0.f);
     }
     __syncthreads();
-#pragma unroll 1
-    for (int t = 0; t < SNAP_ROWS / 32 && r0 + 32 * t < rows; ++t) {
-      f16v S[2] = {};
-      snap_logits<D>(ka, sq, 32 * t + lr, lh, S);
-      const float2 mi = sml[32 * t + lr];
+    snap_steps<D>(sd, h, a, b, [&](int key0, const uint4 (&ka)[D / 16]) {
+      float acc[16];
 #pragma unroll
-      for (int i = 0; i < 32; ++i) acc[i] = fmaf(fexp2(fmaf(S[i / 16][i % 16], scale2, -mi.x)), mi.y, acc[i]);
-    }
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) {
+        if (r0 + 32 * t >= rows) continue;
+        const f16v S = snap_logits<D>(ka, sq, 32 * t + lr, lh);
+        const float2 mi = sml[32 * t + lr];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = fmaf(fexp2(fmaf(S[i], scale2, -mi.x)), mi.y, acc[i]);
+      }
+      const float sum = half_wave_sums(acc);
+      const int key = key0 + 8 * ((lr / 4) & 3) + 4 * lh + (lr & 3);
+      if (lr < 16 && key < b) {
+        if (r0 > 0) votes[key] += sum;
+        else votes[key] = sum;
+      }
+    });
   }
-  const float sum = half_wave_sums(acc);
-  const int key = key0 + 32 * (lr / 16) + 8 * ((lr / 4) & 3) + 4 * lh + (lr & 3);
-  if (key < n0 - w) gst(reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0 + key, sum);
 }
 
 // Max pooling of the candidates' votes (odd kernel `pool`, clipped to [0, n0 - w)) into
@@ -605,7 +640,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_snap_keep(const SeqDesc *__res
   } else {
     if (want > 0) {
       const uint32_t *keys = reinterpret_cast<const uint32_t *>(sd.aux1) + (size_t)h * n0;
-      select_keys<kTopkThreads, 32>(ncand, want, [&](int j) { return gld(keys + j); }, pos, L);
+      select_keys<kTopkThreads, 32>(ncand, want, KeyRow{keys}, pos, L);
     }
     for (int i = threadIdx.x; i < w; i += kTopkThreads) pos[want + i] = ncand + i;
   }
@@ -709,18 +744,31 @@ hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &long
   const float scale2 = kLog2e / sqrtf((float)D);
   const MethodSeqs &ms = dv.of[ROCKET];
   const int lg = __builtin_ctz((unsigned)sh.G);
-  const unsigned H = sh.Hkv, chunks = (longest.n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
-  const unsigned rows = (unsigned)ms.max_vote_rows << lg;
+  const unsigned H = sh.Hkv, rows = (unsigned)ms.max_vote_rows << lg;
+  // Keys per workgroup: the span whose rounds of workgroups (two per CU) take the least time, a round
+  // its keys and the set-up, as long as about 200 of them.  4 prompts of 32768 tokens: one round of
+  // 2048 keys 78 and 62 us (row statistics, votes), two of 1024 89 and 66, four waves a CU with 4096 80
+  // and 82.  40 prompts of 1500: three rounds of 512 ahead of an uneven two of 1024 (270 us, 277).
+  int span = SNAP_CHUNK;
+  int64_t best = INT64_MAX;
+  for (int s = SNAP_CHUNK; s <= 2048; s += SNAP_KEYS) {
+    const int64_t wgs = (int64_t)H * std::min(ms.n, kMaxGridY) * ((longest.n0 + s - 1) / s);
+    const int64_t time = (wgs + 2 * kCus - 1) / (2 * kCus) * (s + 200);
+    if (time < best) best = time, span = s;
+  }
+  const unsigned spans = (longest.n0 + span - 1) / span;
   for (int a = 0; a < ms.n; a += kMaxGridY) {
     const unsigned n = std::min(ms.n - a, kMaxGridY);
     const int32_t *list = ms.list + a;
     if (rows > 0) {  // some sequence keeps less than its prompt
-      hipLaunchKernelGGL(k_snap_rowstats<D>, dim3(H * chunks, n), dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv,
-                         lg, scale2);
+      // all rows of 32-token windows of up to 4, or of 8 query heads, in LDS at once: K is read once a pass
+      // (8 prompts of 6000-9000 tokens of 8 heads: 152 us with 128 rows and two passes over K, 137 with 256)
+      hipLaunchKernelGGL((rows <= 128 ? k_snap_rowstats<D, 128> : k_snap_rowstats<D, 256>), dim3(H * spans, n),
+                         dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, span, scale2);
       hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + NT / 64 - 1) / (NT / 64)), n), dim3(NT), 0, st, dv.seqs,
-                         list, sh.Hkv, lg);
-      hipLaunchKernelGGL(k_snap_votes<D>, dim3(H * chunks, n), dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg,
-                         scale2);
+                         list, sh.Hkv, lg, span);
+      hipLaunchKernelGGL((rows <= 128 ? k_snap_votes<D, 128> : k_snap_votes<D, 256>), dim3(H * spans, n), dim3(NT),
+                         0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, span, scale2);
       hipLaunchKernelGGL(k_snap_pool, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list,
                          sh.Hkv);
     }

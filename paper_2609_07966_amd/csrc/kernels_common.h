@@ -54,6 +54,13 @@ MKV_DEV uint4 gld16h(const uint16_t *p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// 16 bytes of a buffer aligned to its 4-byte elements
+MKV_DEV uint4 gld16w(const uint32_t *p) {
+  typedef uint32_t u32x4w __attribute__((ext_vector_type(4), aligned(4)));
+  const u32x4w v = *(const MKV_GLOBAL u32x4w *)p;
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // 16 bytes as four scalars (the backend merges the four loads into one 16-byte load); loader
 // state holds plain scalars rather than vector types
 struct U4 {

@@ -98,7 +98,6 @@ double token_cost(const SeqDesc &s, int D) {
 // workgroups per slot (256 CUs x 3 resident workgroups) to balance: about 4 rounds, within
 // 64 to 192 KiB (measured best for batches of ~40 MB and ~600 MB per step); then adjusted to
 // whole rounds (below).
-constexpr int kCus = 256;
 constexpr int kTileSlots = kCus * 3;  // resident attention workgroups (3 per CU)
 double tile_bytes_for(double total_bytes) {
   constexpr double kRounds = 4;

@@ -32,6 +32,7 @@ enum StateWord : int32_t {
   ST_WORDS = 8
 };
 
+constexpr int kCus = 256;
 constexpr int kTileThreads = 256;
 constexpr int kMaxG = 8;
 constexpr uint32_t kNoOutlier = 0xFFFFFFFFu;  // fp16 bits 0xFFFF (a NaN) never occur in an entry

@@ -160,6 +160,38 @@ def test_snap_prompts_at_chunk_edges(hkv, g, d, window, pool):
     c.close()
 
 
+@pytest.mark.parametrize("seqs,longest", [(48, 1100), (30, 1100), (12, 2300)])
+def test_snap_prompts_in_long_spans(seqs, longest):
+    """Batches that fill the chip take spans of several 128-key steps (of all of a prompt, half of one and
+    a quarter here, an odd number of steps among them): keep-sets within the tie band, for prompts that end
+    within the first step, at its end and in the last span."""
+    import torch
+    from gpu_harness import _keep_set_tie_ok
+    from oracle import snapkv
+    from paper_2609_07966_amd.cache import KVCache
+    hkv, g, d, window, pool, keep = 8, 2, 64, 32, 7, 90
+    lens = [longest - 17 * s for s in range(seqs)]
+    lens[1:4] = 100, 128, 129
+    cfgs = [{"method": "rocket", "keep_tokens": keep, "window": window, "pool": pool, "topk": 0, "n_channels": 16}] * seqs
+    r = np.random.default_rng(seqs)
+    n, at = sum(lens), np.concatenate([[0], np.cumsum(lens)])
+    k = r.standard_normal((n, hkv, d)).astype(np.float16)
+    qw = r.standard_normal((window * seqs, hkv * g, d)).astype(np.float16)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    c = KVCache((seqs, hkv * g, hkv, d, 1), cfgs, lens)
+    c.append_prompt(dev(k), dev(k))
+    c.snap_prefill(dev(qw))
+    for s in (0, 1, 2, 3, 4, seqs - 1):
+        m = lens[s]
+        for h in (0, hkv - 1):
+            kp, win = k[at[s]:at[s] + m, h], qw[s * window:(s + 1) * window, h * g:(h + 1) * g]
+            u = np.concatenate([snapkv.pooled_votes(win, kp, window, pool), np.full(window, np.inf)])
+            ok, _ = _keep_set_tie_ok(u, c.export(s, h, "positions"), snapkv.snap_keep(win, kp, keep, window, pool),
+                                     set(range(m - window, m)))
+            assert ok, f"sequence {s} ({m} tokens) head {h}"
+    c.close()
+
+
 @pytest.mark.parametrize("hkv,g,d", [(1, 2, 128), (3, 4, 64), (2, 1, 128)])
 def test_uniform_prompts_at_block_edges(hkv, g, d):
     """Ragged uniform 4-bit prompts beside fp16 ones, quantized together: codes and (min, step) pairs bit
