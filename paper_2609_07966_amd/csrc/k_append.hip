@@ -355,18 +355,18 @@ __global__ __launch_bounds__(kQuantThreads) void k_uq_values(const SeqDesc *__re
 // ---- KVQ prompts ----------------------------------------------------------------------------------
 // 8 prompts of 3000-6000 tokens (8 kv heads x 128), where launches per sequence, one workgroup per
 // token (keys) or 4-token block (values) and 16 workgroups per calibration stood before: thresholds
-// 1176 -> 58 us, key codes and outliers 364 -> 54, values 201 -> 57, scan 72 -> 5.  Reading K or V once
-// takes 15 us here; the codes' compares bound the quantizing kernels, LDS atomics and load latency the
-// calibration.
+// 1176 -> 39 us, key codes and outliers 364 -> 54, values 201 -> 57, scan 72 -> 5.  Reading K or V once
+// takes 15 us here; the codes' compares bound the quantizing kernels, load latency the calibration.
 
 // KVQ key thresholds: the n_o-th largest |k| (0-based) of every channel over the prompt, by a
 // two-pass radix select on the 15-bit fp16 magnitude.  A workgroup takes 32 channels of one kv head;
-// its waves read 16 tokens per load, kCalibBatch loads in flight, and count into one 256-bin
-// histogram per channel by LDS atomics (in the second pass only keys of the selected digit count);
-// then a wave per channel finds its digit by a scan.  32 channels instead of 64 per workgroup give
-// 256 of them on 8 sequences.
-constexpr int kCalibThreads = 512;
-constexpr int kCalibBatch = 8;
+// its waves read 16 tokens per load, kCalibBatch loads counted while the next are in flight, into one
+// 256-bin histogram per channel by LDS atomics (in the second pass only keys of the selected digit);
+// then a wave per channel finds its digit by a scan.  32 channels instead of 64 per workgroup give 256
+// of them on 8 sequences, and 16 waves the loads in flight that one workgroup per CU needs: 8 prompts
+// of 3000-6000 tokens 39 us, with 8 waves 58 (counting only the keys that may still matter: no gain).
+constexpr int kCalibThreads = 1024;
+constexpr int kCalibBatch = 2;
 constexpr int kCalibChannels = 32;
 template <int D>
 __global__ __launch_bounds__(kCalibThreads) void k_kvq_calibrate(const SeqDesc *__restrict__ seqs,
@@ -388,20 +388,24 @@ __global__ __launch_bounds__(kCalibThreads) void k_kvq_calibrate(const SeqDesc *
   const int cl = 8 * (lane % LC);  // this lane's first channel of the workgroup's
   const uint16_t *kc = k + ((size_t)sd.row0 * Hkv + h) * D + c0 + cl;
   const size_t pitch = (size_t)Hkv * D;
+  constexpr int kStep = NW * TPL;  // tokens a load of every wave takes
+  auto load = [&](int t, uint4 (&w)[kCalibBatch]) {
+#pragma unroll
+    for (int b = 0; b < kCalibBatch; ++b) w[b] = gld16h(kc + (size_t)min(t + b * kStep, n0 - 1) * pitch);
+  };
+  const int tl = wave * TPL + lane / LC;
   for (int pass = 0; pass < 2; ++pass) {
+    uint4 x[kCalibBatch], y[kCalibBatch];
+    load(tl, x);
     for (int e = threadIdx.x; e < kCalibChannels * 260; e += kCalibThreads) (&hist[0][0])[e] = 0u;
     __syncthreads();
     uint32_t sel[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) sel[e] = pass == 0 ? 0u : s_sel[cl + e];
-    for (int t0 = wave * TPL; t0 < n0; t0 += NW * TPL * kCalibBatch) {
-      uint4 w[kCalibBatch];
-#pragma unroll
-      for (int b = 0; b < kCalibBatch; ++b)
-        w[b] = gld16h(kc + (size_t)min(t0 + b * NW * TPL + lane / LC, n0 - 1) * pitch);
+    auto count = [&](int t, const uint4 (&w)[kCalibBatch]) {
 #pragma unroll
       for (int b = 0; b < kCalibBatch; ++b) {
-        if (t0 + b * NW * TPL + lane / LC >= n0) break;
+        if (t + b * kStep >= n0) break;
         const uint32_t ww[4] = {w[b].x, w[b].y, w[b].z, w[b].w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -410,6 +414,12 @@ __global__ __launch_bounds__(kCalibThreads) void k_kvq_calibrate(const SeqDesc *
           else if ((key >> 8) == sel[e]) atomicAdd(&hist[cl + e][key & 255u], 1u);
         }
       }
+    };
+    for (int t = tl; t - tl < n0; t += 2 * kCalibBatch * kStep) {
+      load(t + kCalibBatch * kStep, y);
+      count(t, x);
+      load(t + 2 * kCalibBatch * kStep, x);
+      count(t + kCalibBatch * kStep, y);
     }
     __syncthreads();
     for (int c = wave; c < kCalibChannels; c += NW) {

@@ -103,6 +103,32 @@ def test_kvq_prompts_at_block_edges(hkv, g, d, bp):
     c.close()
 
 
+@pytest.mark.parametrize("d,bp", [(128, 100), (64, 5000), (128, 30)])
+def test_kvq_thresholds_of_drifting_prompts(d, bp):
+    """Thresholds of prompts around the 256-token loads and 512-token batches of the calibration, whose
+    magnitudes grow, shrink, stay or alternate along the prompt."""
+    import torch
+    from oracle import kvquant
+    from paper_2609_07966_amd.cache import KVCache
+    lens = [255, 257, 511, 512, 513, 1023, 1025, 1500, 2049]
+    r = np.random.default_rng(bp)
+    k = []
+    for n in lens:
+        x = np.linspace(-3.0, 3.0, n)[:, None]
+        drift = np.stack([x, -x, 0 * x, 3 * np.sign(np.sin(9 * x))])[:, :, 0].T
+        k.append((r.standard_normal((n, 1, d)) * np.exp2(drift[:, np.arange(d) % 4])[:, None]).astype(np.float16))
+        k[-1][:, :, d // 2:d // 2 + 4] = 1.5
+    dev = torch.from_numpy(np.concatenate(k)).cuda()
+    cfgs = [{"method": "kvq", "bits": 2, "outlier_bp": bp}] * len(lens)
+    books = [float(i) for b in (2, 3, 4) for _ in range(2) for i in range(1 << b)]
+    c = KVCache((len(lens), 1, 1, d, 1), cfgs, lens, codebooks=books)
+    c.append_prompt(dev, dev)
+    for s, n in enumerate(lens):
+        np.testing.assert_array_equal(c.export(s, 0, "scales_k"), kvquant.calibrate_keys(k[s][:, 0], bp)[0],
+                                      err_msg=f"{n} tokens")
+    c.close()
+
+
 @pytest.mark.parametrize("hkv,g,d,window,pool", [(1, 4, 128, 32, 7), (2, 1, 64, 5, 1), (1, 8, 128, 40, 3), (3, 2, 128, 32, 7)])
 def test_snap_prompts_at_chunk_edges(hkv, g, d, window, pool):
     """Ragged RocketKV prompts selected in one launch per stage, some keeping everything: keep-sets
