@@ -32,7 +32,8 @@ PEAK_HBM_GBS = 8000.0
 MALL_BYTES = 256 << 20
 ROOFLINE_KERNEL = "k_attn_partial_mx<128, 4>"
 # the sources the attention partial kernel is compiled from, and the committed counter record
-KERNEL_SOURCES = ("paper_2609_07966_amd/csrc/k_attn.hip", "paper_2609_07966_amd/csrc/kernels_common.h",
+KERNEL_SOURCES = ("paper_2609_07966_amd/csrc/k_attn.hip", "paper_2609_07966_amd/csrc/append_dev.h",
+                  "paper_2609_07966_amd/csrc/kernels_common.h",
                   "paper_2609_07966_amd/csrc/mkv_internal.h")
 TRAFFIC_RECORD = "profiles/attn_partial_mx_mixed64_traffic.md"
 

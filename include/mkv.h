@@ -216,13 +216,15 @@ mkv_status mkv_decode_attention_noalloc(mkv_cache *cache, const uint16_t *q, flo
  * enqueues nothing and leaves the handle unchanged.  Only MKV_EHIP can come
  * after a launch, and then the step may be partly enqueued.
  *
- * With RocketKV sequences in the batch the step's append launch also computes
- * their approximate scores, spread over several workgroups per kv head, and a
- * selection launch follows (the effect is that of the two calls in order).
+ * Without RocketKV sequences in the batch the attention launch appends the
+ * step's tokens.  With them the step's append launch also computes their
+ * approximate scores, spread over several workgroups per kv head, and selects
+ * where every kv head has one of them, else a selection launch follows (the
+ * effect is that of the calls in order).
  *
- * Graph capture: the step enqueues three or four kernels on `stream` (the
- * append, with the scores when RocketKV sequences are present; their
- * selection; attention partial; combine) and nothing else (no allocation,
+ * Graph capture: the step enqueues two to four kernels on `stream` (append
+ * with scores and selection, in none, one or two launches; attention partial;
+ * combine) and nothing else (no allocation,
  * copy, memset or synchronization; profiling events only when enabled), and
  * every per-step quantity (counts, positions, H2O eviction candidates,
  * outlier fills) lives in device state, so a captured step may be replayed
@@ -283,7 +285,8 @@ mkv_status mkv_fit_codebooks(const uint16_t *k, const uint16_t *v, int32_t n_tok
  * 0 attention partial (one launch over every sequence's tiles), 1 attention
  * combine, 2 append, 3 top-k select, 4 the append of mkv_decode_step with
  * RocketKV sequences present (it also computes their approximate scores; the
- * step's selection then counts as kind 3).
+ * step's selection then counts as kind 3).  A step's append or selection that
+ * would be part of another launch has one of its own while its kind is selected.
  */
 mkv_status mkv_profile_enable(mkv_cache *cache, int32_t enable, int32_t max_launches);
 mkv_status mkv_profile_read(mkv_cache *cache, int32_t kind, int32_t *launches, double *total_ms);

@@ -208,7 +208,7 @@ MKV_DEV int lane_group_before(int x) {
 }
 
 // ---- uniform 4-bit prompts ------------------------------------------------------------------------
-// 6 prompts of 1.6-23 thousand tokens (8 kv heads x 128; 230 MB of K and V): 66 + 40 us, against
+// 6 prompts of 1.2-19 thousand tokens (8 kv heads x 128; 219 MB of K and V): 67 + 40 us, against
 // 176 + 138 with launches per sequence, one 128-thread workgroup per 4-token value block and key blocks
 // read twice at 2 bytes a lane.
 
