@@ -182,6 +182,7 @@ template <int D, int G, int BITS>
 struct MKVQ {
   static constexpr int NM = MG<D>::NM, CPL = MG<D>::CPL, VPL = MG<D>::VPL;
   static constexpr int NS = 2;           // 32-token batches (the key-outlier tags are slot mod 32)
+  static constexpr float kLazy = 4.f;    // see kLazyRows
   static constexpr int SEG = CPL * BITS;  // bits per lane segment (keys; values alike)
   // words per segment: a segment starts at bit SEG * lane_index, which is word aligned unless
   // SEG = 48 (d = 64, 3 bits), where it starts at bit 0 or 16 of a word and still spans 2 words
@@ -407,6 +408,7 @@ struct MUQ {
   static constexpr int NGRP = D / 64;     // value groups
   static constexpr int KW = RES ? CPL / 2 : CPL / 8;  // key words per lane and step
   static constexpr int NS = RES ? 1 : 2;  // the fp16 block (at most 63 tokens) in 16-token batches
+  static constexpr float kLazy = 8.f;     // see kLazyRows
   const uint8_t *kc, *vc;
   const float *kmeta, *vmeta;             // float2 pairs (min, step)
   const uint16_t *kres;
@@ -600,12 +602,17 @@ struct MUQ {
   }
 };
 
-// The running max of head lr moves only when a logit exceeds it by more than kLazyMax (log2
-// units): between moves the probabilities 2^(s - m_run) stay below 2^kLazyMax, well inside fp16
-// and float32, and most steps skip the cross-lane max and the rescale altogether.  The max that
-// is kept is a reference for the sums, not the exact maximum; the merges of waves and tiles
-// rescale by the references' differences, so the results are the same.
-constexpr float kLazyMax = 8.f;
+// The running max of head lr moves only when a logit exceeds it by more than a few log2 units: between
+// moves the probabilities 2^(s - m_run) stay well inside fp16 and float32, and most steps skip the
+// cross-lane max and the rescale altogether.  The max that is kept is a reference for the sums, not
+// the exact maximum; the merges of waves and tiles rescale by the references' differences.  A larger
+// limit saves rescales, a smaller one rounds less: the tokens that weigh most have a probability
+// near 1, exact in fp16 at the reference itself.  Error of a step's output against 64 bits
+// (8 x 8192 tokens under H2O-20; 8 x 4096 FP16; KVQuant of 3000-6000) at a limit of 8: 9.0e-5, 1.3e-4,
+// 1.3e-4; at 4: -, -, 8.4e-5; at 2: 3.2e-5, 6.6e-5, 6.3e-5; times of rows at 2 and of KVQuant at 4 the
+// same, of KVQuant at 2 2 % more.  (Uniform 4-bit probabilities are rounded times their steps,
+// at any reference.)
+constexpr float kLazyRows = 2.f;  // of the quantized paths: kLazy
 
 // Move head lr's reference to the wave-wide max of this step's logits (lane max `mx`) and
 // rescale the sums; called wave-uniformly.
@@ -644,7 +651,7 @@ MKV_DEV void rows_step(const MRows<D, G, GATHER> &ld, const typename MRows<D, G,
     for (int j = 0; j < 4; ++j)
       if (sc[j] != -INFINITY) gst(logit_out + (size_t)(base + 4 * lq + j) * G + lr, sc[j]);
   }
-  if (__any(mx > m_run + kLazyMax)) rescale_to(ld, mx, m_run, l_part, O);
+  if (__any(mx > m_run + kLazyRows)) rescale_to(ld, mx, m_run, l_part, O);
   float pp[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -730,7 +737,7 @@ MKV_DEV void mfma_batch(L &ld, int base, int b, const Batch<L> &x, QB<D> &qb, fl
       mx = fmaxf(mx, sc[s][j]);
     }
   }
-  if (__any(mx > m_run + kLazyMax)) rescale_to(ld, mx, m_run, l_part, O);
+  if (__any(mx > m_run + L::kLazy)) rescale_to(ld, mx, m_run, l_part, O);
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     float p[4], pp[4];
