@@ -300,7 +300,9 @@ MKV_DEV NewToken load_token(const SeqDesc &sd, const int32_t *st, int seq, int h
 // that all call this.  False, with nothing written, if a region is full (reachable only by replaying a
 // captured decode step past max_new_tokens: the token is dropped instead of written past the region).
 // Only the counts are left to the caller: those after the append are (count + (victim < 0),
-// position + 1).  A workgroup that goes on to read what was written waits for its stores and a barrier.
+// position + 1).  A workgroup that goes on to read what was written waits for its stores and a barrier;
+// one that goes on to use the LDS of L for something else needs that barrier after either result (a
+// dropped token leaves load_token's stores into L unordered between the waves).
 template <int D, int NT>
 MKV_DEV bool append_pair(const SeqDesc &sd, int32_t *st, const NewToken &tok, int h, int count, int pos, int slot,
                          int victim, AppendLds<D> &L) {

@@ -855,16 +855,20 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
     int victim;
     const int pos = st[ST_NEXT_POS], at = append_slot(sd, h, n_cnt, &victim);
     AppendLds<D> &al = *reinterpret_cast<AppendLds<D> *>(&s_wave[0][0]);
-    if (at >= tile.z && at < tile.w &&
-        append_pair<D, kTileThreads>(sd, st, load_token<D, kTileThreads>(sd, st, seq, h, Hkv, k_new, v_new, cbtab, al),
-                                     h, n_cnt, pos, at, victim, al)) {
-      // the stores have reached the CU's cache before any wave reads them
+    if (at >= tile.z && at < tile.w) {  // (the same in all threads)
+      const NewToken tok = load_token<D, kTileThreads>(sd, st, seq, h, Hkv, k_new, v_new, cbtab, al);
+      const bool appended = append_pair<D, kTileThreads>(sd, st, tok, h, n_cnt, pos, at, victim, al);
+      // the stores have reached the CU's cache before any wave reads them; and, where the token was
+      // dropped too, the codebooks that waves 0 and 1 put into the wave regions are there before the
+      // waves clear their own
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      n_cnt += victim < 0 ? 1 : 0;
-      if (threadIdx.x == 0) {
-        st[ST_STEP_COUNT] = n_cnt;
-        st[ST_STEP_POS] = pos + 1;
+      if (appended) {
+        n_cnt += victim < 0 ? 1 : 0;
+        if (threadIdx.x == 0) {
+          st[ST_STEP_COUNT] = n_cnt;
+          st[ST_STEP_POS] = pos + 1;
+        }
       }
     }
   }

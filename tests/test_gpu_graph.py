@@ -54,13 +54,16 @@ def _state(c, cfgs, Hkv):
 
 
 @pytest.mark.gpu
-def test_graph_replay_matches_eager():
+@pytest.mark.parametrize("names", [["FP16", "UQ4-g64", "KVQ4", "KVQ2", "H2O-10", "Rocket-1024", "H2O-50"],
+                                   ["FP16", "UQ4-g64", "KVQ4", "KVQ2", "H2O-10", "KVQ3", "H2O-50"]],
+                         ids=["append_launch", "append_in_attention"])
+def test_graph_replay_matches_eager(names):
     import torch
     from gpu_harness import log
     from workloads import step_inputs
     wl = make_workload("custom", seed=21, n_seqs=7, n_q_heads=32, n_kv_heads=8, head_dim=128,
                        prompt_lens=[900, 1300, 700, 1700, 2300, 1100, 600], steps=8,
-                       config_ids=["FP16", "UQ4-g64", "KVQ4", "KVQ2", "H2O-10", "Rocket-1024", "H2O-50"])
+                       config_ids=names)
     steps, S, Hkv, Hq, D = 8, wl.n_seqs, wl.n_kv_heads, wl.n_q_heads, wl.head_dim
     log("[graph] eager and captured caches: 7 sequences, 8 decode steps")
     eager, cfgs = _setup(wl, steps)
@@ -97,7 +100,10 @@ def test_graph_replay_matches_eager():
 
 
 @pytest.mark.gpu
-def test_graph_replay_past_capacity_drops_tokens():
+@pytest.mark.parametrize("names", [["FP16", "UQ4-g64", "KVQ3", "H2O-20", "Rocket-1024", "KVQ4"],
+                                   ["FP16", "UQ4-g64", "KVQ3", "H2O-20", "KVQ2", "KVQ4"]],
+                         ids=["append_launch", "append_in_attention"])
+def test_graph_replay_past_capacity_drops_tokens(names):
     """Replays beyond max_new_tokens leave the full regions unchanged (no write past them); H2O
     keeps evicting and appending within its budget."""
     import torch
@@ -106,7 +112,7 @@ def test_graph_replay_past_capacity_drops_tokens():
     max_new, replays = 3, 7
     wl = make_workload("custom", seed=22, n_seqs=6, n_q_heads=8, n_kv_heads=4, head_dim=64,
                        prompt_lens=[300, 257, 400, 350, 500, 280], steps=replays,
-                       config_ids=["FP16", "UQ4-g64", "KVQ3", "H2O-20", "Rocket-1024", "KVQ4"])
+                       config_ids=names)
     S, Hkv, Hq, D = wl.n_seqs, wl.n_kv_heads, wl.n_q_heads, wl.head_dim
     side = torch.cuda.Stream()
     c, cfgs = _setup(wl, max_new, stream=side)
@@ -140,4 +146,59 @@ def test_graph_replay_past_capacity_drops_tokens():
                 assert kept0[i] + max_new <= held <= kept0[i] + max_new + 3, (cf["name"], hh, held)
             else:  # H2O: at most budget + 1 held, and every replay appended a token
                 assert held <= kept0[i] + replays and next_pos == wl.prompt_lens[i] + replays, (cf["name"], hh)
+    c.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hkv,g,d", [(2, 4, 128), (1, 1, 64), (1, 1, 128), (1, 8, 128)])
+def test_graph_replay_with_a_full_outlier_pool(hkv, g, d):
+    """KVQuant sequences of one new token with three slots to spare, whose outlier pool the first token
+    fills: the later replays drop theirs, and each output is the attention over the tokens held (the
+    launch that attends is the one that tried to append)."""
+    import torch
+    from gpu_harness import TOL
+    from oracle.attention import softmax_attention
+    from oracle.sequence import Sequence
+    from paper_2609_07966_amd.cache import KVCache
+    lens = [64, 256, 300, 512]  # slots are rounded up to 4: lens[s] + 4 of them
+    bits = [2, 3, 4, 4]
+    cfgs = [{"method": "kvq", "bits": b, "outlier_bp": 100} for b in bits]
+    r = np.random.default_rng(hkv + g + d)
+    books = {b: [np.sort(r.uniform(-1, 1, 1 << b)).astype(np.float16).astype(np.float32) for _ in range(2)]
+             for b in (2, 3, 4)}
+    S, replays, side = len(lens), 4, torch.cuda.Stream()
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    kp, vp = ([r.standard_normal((n, hkv, d)).astype(np.float16) for n in lens] for _ in range(2))
+    seqs = [Sequence(cfgs[s], kp[s], vp[s], hkv * g, codebooks=books) for s in range(S)]
+    c = KVCache((S, hkv * g, hkv, d, 1), cfgs, lens,
+                codebooks=[float(x) for b in (2, 3, 4) for half in books[b] for x in half], stream=side)
+    c.append_prompt(dev(np.concatenate(kp)), dev(np.concatenate(vp)))
+    kb, vb = (torch.zeros((S, hkv, d), dtype=torch.float16, device="cuda") for _ in range(2))
+    qb = torch.zeros((S, hkv * g, d), dtype=torch.float16, device="cuda")
+    out = torch.empty((S, hkv * g, d), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        c.step(kb, vb, qb, out)
+    for t in range(replays):
+        kn = (50 * r.standard_normal((S, hkv, d))).astype(np.float16)  # past most channels' thresholds
+        vn = r.standard_normal((S, hkv, d)).astype(np.float16)
+        q = (r.standard_normal((S, hkv * g, d)) / 64).astype(np.float16)  # so that every token counts
+        kb.copy_(dev(kn))
+        vb.copy_(dev(vn))
+        qb.copy_(dev(q))
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        for s, seq in enumerate(seqs):
+            if t == 0:
+                seq.step(kn[s], vn[s], q[s])
+            for h in range(hkv):
+                assert c.counts(s, h)[:2] == (lens[s] + 1, lens[s] + 1), (t, s, h)
+                assert seq.kq[h]["outlier"][-1].sum() > 0
+                hq, v = slice(h * g, (h + 1) * g), seq.vq[h]["eff"]
+                ref, _ = softmax_attention(q[s, hq], seq.kq[h]["eff"], v)
+                assert np.abs(got[s, hq] - ref).max() <= TOL * np.sqrt(np.mean(v * v)), f"replay {t} sequence {s} head {h}"
     c.close()
