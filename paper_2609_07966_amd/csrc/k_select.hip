@@ -407,7 +407,7 @@ __global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ s
 
 // ---- SnapKV prefill -------------------------------------------------------------------------------
 // Window row r = i * G + g (query head h*G + g at position n0 - w + i; it attends to keys
-// 0 .. n0 - w + i).  Pass 1: per span of keys the partial (max, sum of exp2) of every row.  Pass 2:
+// 0 .. n0 - w + i).  Pass 1: per chunk of keys the partial (max, sum of exp2) of every row.  Pass 2:
 // each row's partials merged.  Pass 3: the votes of a span's keys, the logits recomputed.  Pass 4: max
 // pooling into order-preserving keys.  Pass 5: the selection; pass 6: the kept rows gathered.  Every
 // pass is one launch over all RocketKV sequences (grid as for H2O).
@@ -416,10 +416,24 @@ __global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ s
 // A workgroup takes a span of keys and holds ROWS window rows in LDS; a wave holds 32 keys as operands,
 // loaded while it computes the 32 before, so the loads of K run under the products and exponentials
 // and the rows are staged once per span.  (With one chunk of 256 keys per workgroup and the rows
-// staged 64 at a time, every workgroup waited for its keys and again for its rows.)  4 prompts of
-// 32768 tokens (268 MB of K a pass): row statistics 78 us and votes 62, before 96 and 81.
-constexpr int SNAP_CHUNK = 256;  // the shortest span (the scratch holds a partial per chunk and row)
-constexpr int SNAP_KEYS = 32 * (NT / 64);  // keys a workgroup takes at a time
+// staged 64 at a time, every workgroup waited for its keys and again for its rows.)
+//
+// The spans are chosen for the whole batch, so nothing may depend on them: a row's sum is taken per lane
+// over 64 keys, those of a 256-key chunk folded in ascending order, then the two lane halves, then the
+// chunks, whichever waves took them; a key's votes are summed over the rows alone.  (Sums over whole
+// spans rounded differently in other batches, and a near-tie in a keep-set fell differently.)  The whole
+// selection, with sums over spans and now: 4 prompts of 32768 tokens 215 and 214 us, one of them 82 and 88
+// (spans of 512 keys were the best there), 40 of 1500 145 and 136, 6 of 400 38 and 37.
+constexpr int SNAP_CHUNK = 256;  // keys of a partial; with one chunk a workgroup, its waves take 64 keys each
+constexpr int SNAP_KEYS = 32 * (NT / 64);  // keys a workgroup takes at a time (votes)
+static_assert(SNAP_CHUNK == 64 * (NT / 64), "a wave per 64 keys of a chunk");
+
+// (max, sum) of two disjoint key sets; an empty set is (-inf, 0).
+MKV_DEV void snap_fold(float &M, float &L, float m, float l) {
+  const float mx = fmaxf(M, m), ref = mx == -INFINITY ? 0.f : mx;
+  L = L * fexp2(M - ref) + l * fexp2(m - ref);
+  M = mx;
+}
 
 // The window rows [r0, r0 + ROWS) (clamped to the last row) as fp16 operands in LDS.
 template <int D, int ROWS>
@@ -468,31 +482,44 @@ MKV_DEV f16v snap_logits(const uint4 (&ka)[D / 16], const uint4 (*sq)[D / 8 + 1]
   return S;
 }
 
+// span: SNAP_CHUNK (the chunk's waves take 64 keys each), or a multiple of 4 chunks (a wave takes whole
+// chunks).  Partials: [head][chunk][row].
 template <int D, int ROWS>
 __global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict__ seqs,
                                                       const int32_t *__restrict__ list,
                                                       const uint16_t *__restrict__ qw, int Hq, int Hkv, int lg,
                                                       int span, float scale2) {
-  constexpr int kTiles = ROWS / 32, kParts = 2 * (NT / 64);
+  constexpr int kTiles = ROWS / 32, kParts = 2 * (NT / 64), U = D / 8;
   __shared__ uint4 sq[ROWS][D / 8 + 1];
   float2(*s_part)[ROWS] = reinterpret_cast<float2(*)[ROWS]>(&sq[0][0]);  // once the rows are used
   static_assert(sizeof(float2) * kParts * ROWS <= sizeof(sq), "the partials fit the rows");
   const SeqDesc &sd = seqs[list[blockIdx.y]];
   const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, a = (int)blockIdx.x / Hkv * span;
   if (a >= n0 || sd.T >= n0) return;
-  const int nspan = (n0 + span - 1) / span, b = min(a + span, n0);
+  const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK, b = min(a + span, n0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
   const int rows = w << lg;
-  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * rows * nspan;
+  const bool split = span == SNAP_CHUNK;
+  const int run = split ? 64 : SNAP_CHUNK;  // consecutive keys a wave takes
+  float2 *part = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * nchunk * rows;
+  const uint4 *ks = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(sd.stage_k) +
+                                                    h * stride_stage(sd, D));
+  auto load = [&](int key0, uint4 (&ka)[D / 16]) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) ka[s] = gld16(ks + (size_t)min(key0 + lr, n0 - 1) * U + 2 * s + lh);
+  };
   for (int r0 = 0; r0 < rows; r0 += ROWS) {
     if (r0 > 0) __syncthreads();
     stage_window<D, ROWS>(sq, qw, sd, h, lg, Hq, rows, r0);
     __syncthreads();
-    // the lane's (max, sum of exp2) of row r0 + 32 t + lr over its own keys
-    float m[kTiles], l[kTiles];
+    // of row r0 + 32 t + lr over the lane's own keys: (max, sum of exp2) of the 64 keys in progress, and
+    // of those before them in the chunk
+    float m[kTiles], l[kTiles], cm[kTiles], cl[kTiles];
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) m[t] = -INFINITY, l[t] = 0.f;
-    snap_steps<D>(sd, h, a, b, [&](int key0, const uint4 (&ka)[D / 16]) {
+    for (int t = 0; t < kTiles; ++t) m[t] = cm[t] = -INFINITY, l[t] = cl[t] = 0.f;
+    auto step = [&](int key0, const uint4 (&ka)[D / 16]) {
+      const bool end64 = (key0 + 32) % 64 == 0 || key0 + 32 >= b;
+      const bool end_run = (key0 + 32) % run == 0 || key0 + 32 >= b;
 #pragma unroll
       for (int t = 0; t < kTiles; ++t) {
         if (r0 + 32 * t >= rows) continue;
@@ -516,47 +543,78 @@ __global__ __launch_bounds__(NT) void k_snap_rowstats(const SeqDesc *__restrict_
         for (int i = 0; i < 16; ++i) u[i & 1] += fexp2(fmaf(S[i], scale2, -ref));
         l[t] = u[0] + u[1];
         m[t] = mx;
+        if (end64) {
+          snap_fold(cm[t], cl[t], m[t], l[t]);
+          m[t] = -INFINITY, l[t] = 0.f;
+        }
+        if (end_run && !split) {
+          const float mo = __shfl_xor(cm[t], 32), lo = __shfl_xor(cl[t], 32);
+          snap_fold(cm[t], cl[t], mo, lo);
+          const int r = r0 + 32 * t + lr;
+          if (lh == 0 && r < rows) part[(size_t)(key0 / SNAP_CHUNK) * rows + r] = make_float2(cm[t], cl[t]);
+          cm[t] = -INFINITY, cl[t] = 0.f;
+        }
       }
-    });
+    };
+    // the next step's keys load while one is computed; after a run the wave skips those of the others
+    // (loads past the span repeat rows of the prompt)
+    auto next = [&](int key0) {
+      key0 += 32;
+      return key0 % run == 0 ? key0 + 3 * run : key0;
+    };
+    int key0 = a + run * wave;
+    uint4 x[D / 16], y[D / 16];
+    if (key0 < b) load(key0, x);
+    while (key0 < b) {
+      int to = next(key0);
+      load(to, y);
+      step(key0, x);
+      if (to >= b) break;
+      key0 = to;
+      to = next(key0);
+      load(to, x);
+      step(key0, y);
+      key0 = to;
+    }
+    if (!split) continue;
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) s_part[2 * wave + lh][32 * t + lr] = make_float2(m[t], l[t]);
+    for (int t = 0; t < kTiles; ++t) s_part[2 * wave + lh][32 * t + lr] = make_float2(cm[t], cl[t]);
     __syncthreads();
     for (int r = threadIdx.x; r < ROWS && r0 + r < rows; r += NT) {
-      float M = -INFINITY, L = 0.f;
+      float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < kParts; ++v) M = fmaxf(M, s_part[v][r].x);
-#pragma unroll
-      for (int v = 0; v < kParts; ++v) {
-        const float2 p = s_part[v][r];
-        L += p.x == -INFINITY ? 0.f : p.y * fexp2(p.x - M);
-      }
-      part[(size_t)(r0 + r) * nspan + a / span] = make_float2(M, L);
+      for (int v = 0; v < kParts; ++v) snap_fold(M[v & 1], L[v & 1], s_part[v][r].x, s_part[v][r].y);
+      snap_fold(M[0], L[0], M[1], L[1]);
+      part[(size_t)(a / SNAP_CHUNK) * rows + r0 + r] = make_float2(M[0], L[0]);
     }
   }
 }
 
-// Merge each window row's partials (one wave per row); entry 0 of the row then holds (max, 1 / sum of
-// exp2) over all its keys.
+// Merge the window rows' partials, 32 rows a workgroup, every eighth chunk to a thread; chunk 0's entry
+// of a row then holds (max, 1 / sum of exp2) over all its keys.
+constexpr int kMergeRows = 32;
 __global__ __launch_bounds__(NT) void k_snap_merge(const SeqDesc *__restrict__ seqs, const int32_t *__restrict__ list,
-                                                   int Hkv, int lg, int span) {
+                                                   int Hkv, int lg) {
+  constexpr int kSlices = NT / kMergeRows;
+  __shared__ float2 s_part[kSlices][kMergeRows];
   const SeqDesc &sd = seqs[list[blockIdx.y]];
-  const int n0 = sd.n0, rows = sd.w_eff << lg, h = blockIdx.x % Hkv;
-  const int np = (n0 + span - 1) / span;
-  const int lane = threadIdx.x & 63, r = (int)blockIdx.x / Hkv * (NT / 64) + (threadIdx.x >> 6);
-  if (r >= rows || sd.T >= n0) return;
-  float2 *pr = reinterpret_cast<float2 *>(sd.aux1) + ((size_t)h * rows + r) * np;
+  const int n0 = sd.n0, rows = sd.w_eff << lg, h = blockIdx.x % Hkv, r0 = (int)blockIdx.x / Hkv * kMergeRows;
+  const int np = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK;
+  if (r0 >= rows || sd.T >= n0) return;
+  const int rl = threadIdx.x % kMergeRows, sl = threadIdx.x / kMergeRows, r = min(r0 + rl, rows - 1);
+  float2 *pr = reinterpret_cast<float2 *>(sd.aux1) + (size_t)h * np * rows + r;
   float m = -INFINITY, l = 0.f;
-  for (int e = lane; e < np; e += 64) {
-    const float xm = gld(reinterpret_cast<const float *>(pr + e)), xl = gld(reinterpret_cast<const float *>(pr + e) + 1);
-    if (xm == -INFINITY) continue;
-    const float mx = fmaxf(m, xm);
-    l = l * fexp2(m - mx) + xl * fexp2(xm - mx);  // arguments <= 0 (m = -inf gives 0)
-    m = mx;
+#pragma unroll 4
+  for (int e = sl; e < np; e += kSlices) {
+    const float *p = reinterpret_cast<const float *>(pr + (size_t)e * rows);
+    snap_fold(m, l, gld(p), gld(p + 1));
   }
-  const float M = wave_max(m);
-  const float L = wave_sum(m == -INFINITY ? 0.f : l * fexp2(m - M));
-  if (lane == 0) pr[0] = make_float2(M, 1.f / L);
+  s_part[sl][rl] = make_float2(m, l);
+  __syncthreads();
+  if (sl > 0) return;
+  for (int v = 1; v < kSlices; ++v) snap_fold(m, l, s_part[v][rl].x, s_part[v][rl].y);
+  if (r0 + rl < rows) pr[0] = make_float2(m, 1.f / l);
 }
 
 // Votes of a span's keys before the window: sum over the window rows of exp2(s - M_r) / L_r.  (Window
@@ -571,16 +629,16 @@ __global__ __launch_bounds__(NT) void k_snap_votes(const SeqDesc *__restrict__ s
   const SeqDesc &sd = seqs[list[blockIdx.y]];
   const int n0 = sd.n0, w = sd.w_eff, h = blockIdx.x % Hkv, a = (int)blockIdx.x / Hkv * span;
   if (a >= n0 - w || sd.T >= n0) return;
-  const int nspan = (n0 + span - 1) / span, b = min(a + span, n0 - w);
+  const int nchunk = (n0 + SNAP_CHUNK - 1) / SNAP_CHUNK, b = min(a + span, n0 - w);
   const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const int rows = w << lg;
-  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * rows * nspan;
+  const float2 *part = reinterpret_cast<const float2 *>(sd.aux1) + (size_t)h * nchunk * rows;
   float *votes = reinterpret_cast<float *>(sd.aux0) + (size_t)h * n0;
   for (int r0 = 0; r0 < rows; r0 += ROWS) {
     if (r0 > 0) __syncthreads();
     stage_window<D, ROWS>(sq, qw, sd, h, lg, Hq, rows, r0);
     for (int t = threadIdx.x; t < ROWS; t += NT) {
-      const float *ml = reinterpret_cast<const float *>(part + (size_t)min(r0 + t, rows - 1) * nspan);
+      const float *ml = reinterpret_cast<const float *>(part + min(r0 + t, rows - 1));
       const float iL = gld(ml + 1);
       sml[t] = make_float2(gld(ml), r0 + t < rows ? iL : 0.f);
     }
@@ -746,29 +804,33 @@ hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &long
   const int lg = __builtin_ctz((unsigned)sh.G);
   const unsigned H = sh.Hkv, rows = (unsigned)ms.max_vote_rows << lg;
   // Keys per workgroup: the span whose rounds of workgroups (two per CU) take the least time, a round
-  // its keys and the set-up, as long as about 200 of them.  4 prompts of 32768 tokens: one round of
-  // 2048 keys 78 and 62 us (row statistics, votes), two of 1024 89 and 66, four waves a CU with 4096 80
-  // and 82.  40 prompts of 1500: three rounds of 512 ahead of an uneven two of 1024 (270 us, 277).
-  int span = SNAP_CHUNK;
-  int64_t best = INT64_MAX;
-  for (int s = SNAP_CHUNK; s <= 2048; s += SNAP_KEYS) {
-    const int64_t wgs = (int64_t)H * std::min(ms.n, kMaxGridY) * ((longest.n0 + s - 1) / s);
-    const int64_t time = (wgs + 2 * kCus - 1) / (2 * kCus) * (s + 200);
-    if (time < best) best = time, span = s;
-  }
-  const unsigned spans = (longest.n0 + span - 1) / span;
+  // its keys and the set-up, as long as about 200 of them; for the row statistics one chunk or whole
+  // chunks for each wave.  (4 prompts of 32768 tokens: one round of 2048 keys 78 and 62 us, row statistics
+  // and votes, two of 1024 89 and 66, four waves a CU with 4096 80 and 82.)
+  const auto best_span = [&](int step) {
+    int span = SNAP_CHUNK;
+    int64_t best = INT64_MAX;
+    for (int s = SNAP_CHUNK; s <= 2048; s = s + step - s % step) {
+      const int64_t wgs = (int64_t)H * std::min(ms.n, kMaxGridY) * ((longest.n0 + s - 1) / s);
+      const int64_t time = (wgs + 2 * kCus - 1) / (2 * kCus) * (s + 200);
+      if (time < best) best = time, span = s;
+    }
+    return span;
+  };
+  const int sspan = best_span(4 * SNAP_CHUNK), vspan = best_span(SNAP_KEYS);
+  const unsigned sspans = (longest.n0 + sspan - 1) / sspan, vspans = (longest.n0 + vspan - 1) / vspan;
   for (int a = 0; a < ms.n; a += kMaxGridY) {
     const unsigned n = std::min(ms.n - a, kMaxGridY);
     const int32_t *list = ms.list + a;
     if (rows > 0) {  // some sequence keeps less than its prompt
       // all rows of 32-token windows of up to 4, or of 8 query heads, in LDS at once: K is read once a pass
       // (8 prompts of 6000-9000 tokens of 8 heads: 152 us with 128 rows and two passes over K, 137 with 256)
-      hipLaunchKernelGGL((rows <= 128 ? k_snap_rowstats<D, 128> : k_snap_rowstats<D, 256>), dim3(H * spans, n),
-                         dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, span, scale2);
-      hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + NT / 64 - 1) / (NT / 64)), n), dim3(NT), 0, st, dv.seqs,
-                         list, sh.Hkv, lg, span);
-      hipLaunchKernelGGL((rows <= 128 ? k_snap_votes<D, 128> : k_snap_votes<D, 256>), dim3(H * spans, n), dim3(NT),
-                         0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, span, scale2);
+      hipLaunchKernelGGL((rows <= 128 ? k_snap_rowstats<D, 128> : k_snap_rowstats<D, 256>), dim3(H * sspans, n),
+                         dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, sspan, scale2);
+      hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + kMergeRows - 1) / kMergeRows), n), dim3(NT), 0, st, dv.seqs,
+                         list, sh.Hkv, lg);
+      hipLaunchKernelGGL((rows <= 128 ? k_snap_votes<D, 128> : k_snap_votes<D, 256>), dim3(H * vspans, n), dim3(NT),
+                         0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, vspan, scale2);
       hipLaunchKernelGGL(k_snap_pool, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list,
                          sh.Hkv);
     }

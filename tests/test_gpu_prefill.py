@@ -218,6 +218,42 @@ def test_snap_prompts_in_long_spans(seqs, longest):
     c.close()
 
 
+def test_snap_keep_sets_alone_and_in_a_batch():
+    """A sequence keeps the same tokens alone, with a few others (256-key workgroups) and in a batch that
+    fills the chip (longer spans).  Two window rows see the same logits in another order, so that their
+    sums differ by a rounding at most, and the votes of 40 keys hang on the one, those of 40 others on the
+    other: which 60 of them are kept follows the roundings."""
+    import torch
+    from paper_2609_07966_amd.cache import KVCache
+    hkv, g, d, n, seqs = 16, 2, 64, 1024, 24
+    cfg = {"method": "rocket", "keep_tokens": 61, "window": 1, "pool": 1, "topk": 0, "n_channels": 8}
+    r = np.random.default_rng(7)
+    k = np.zeros((seqs, n, hkv, d), np.float16)
+    for s in range(seqs):
+        for h in range(hkv):
+            at = r.permutation(n - 1)
+            x = np.minimum(r.standard_normal(n - 81), 2.0)
+            k[s, at[:40], h, :2] = 3.0, -3.0
+            k[s, at[40:80], h, :2] = -3.0, 3.0
+            k[s, at[80:], h, 0], k[s, at[80:], h, 1] = x, r.permutation(x)
+    qw = np.zeros((seqs, hkv * g, d), np.float16)
+    qw[:, 0::2, 0] = qw[:, 1::2, 1] = 8.0  # the logits are the keys' first two channels
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+    def kept(which):
+        c = KVCache((len(which), hkv * g, hkv, d, 1), [cfg] * len(which), [n] * len(which))
+        x = dev(k[which].reshape(-1, hkv, d))
+        c.append_prompt(x, x)
+        c.snap_prefill(dev(qw[which]))
+        got = [[c.export(i, h, "positions") for h in range(hkv)] for i in range(min(3, len(which)))]
+        c.close()
+        return got
+
+    alone = [kept([s])[0] for s in range(3)]
+    for which in ([0, 1, 2], list(range(seqs))):
+        np.testing.assert_array_equal(kept(which), alone, err_msg=f"{len(which)} sequences")
+
+
 @pytest.mark.parametrize("hkv,g,d", [(1, 2, 128), (3, 4, 64), (2, 1, 128)])
 def test_uniform_prompts_at_block_edges(hkv, g, d):
     """Ragged uniform 4-bit prompts beside fp16 ones, quantized together: codes and (min, step) pairs bit
