@@ -160,6 +160,19 @@ int main() {
       for (int j = 0; j < (int)z.size(); ++j) CHECK(z[j] == j * d.chunk);
     }
   }
+  // uniform 4-bit tiles of d = 64 in short launches: 64 tokens or more for each of a workgroup's 4 waves
+  for (int S : {1, 3, 8})
+    for (int with : {MKV_UQ, MKV_FP16, MKV_KVQ})
+      for (int len : {100, 512, 700, 4000}) {
+        mkv_shape sh{S, 8, 4, 64, 4};
+        std::vector<mkv_config> cs(S, cfg(MKV_UQ, 4));
+        if (S > 1) cs[S - 1] = cfg(with, 4, 100);
+        std::vector<int32_t> pl(S, len);
+        std::vector<int4> tiles;
+        std::vector<mkv::SeqDesc> sd;
+        CHECK(mkv::layout_tiles(&sh, cs.data(), pl.data(), &tiles, &sd) == MKV_OK);
+        CHECK(sd[0].chunk % 256 == 0);
+      }
   // the configuration choice
   {
     mkv_candidate c[3] = {{MKV_KVQ, 0, 3.0, 5.0, 0.6}, {MKV_H2O, 1, 1.0, 9.0, 0.5}, {MKV_FP16, 0, 2.0, 20.0, 0.7}};
