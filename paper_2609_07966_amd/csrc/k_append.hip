@@ -1,7 +1,5 @@
 // Append and quantize-on-append kernels: prompts, and the decode appends that have a launch of their
 // own (what a method's append writes: append_dev.h).
-#include <algorithm>
-
 #include "append_dev.h"
 #include "select_dev.h"
 
@@ -133,7 +131,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_rocket_select(const SeqDesc *_
       sd, st, h, room ? count + 1 : count, room, count, pos, KeyRow{akeys}, L);
 }
 
-// ---- prefill: every sequence of a method in one launch per stage ---------------------------------
+// ---- prefill: a group of a method's sequences in one launch per stage ----------------------------
 // Grid: x = kv head (fastest) x blocks of the longest prompt, y = sequence (longest first);
 // workgroups past a shorter prompt's end leave at once.  Launches per sequence left the chip idle
 // between them: a 20-sequence batch of 100-700 tokens enqueued about 100 of them, most under 5 us.
@@ -739,41 +737,36 @@ hipError_t append_select_impl(const Dev &dv, const Shape &sh, const uint16_t *k,
 }
 
 template <int D>
-hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *k, const uint16_t *v,
+hipError_t prefill_impl(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *k, const uint16_t *v,
                         hipStream_t st) {
   const int Hkv = sh.Hkv;
-  const unsigned H = Hkv, blocks = (longest.n0 + kQuantTokens - 1) / kQuantTokens;
-  const MethodSeqs &ms = dv.of[longest.method];
-  for (int a = 0; a < ms.n; a += kMaxGridY) {
-    const unsigned n = std::min(ms.n - a, kMaxGridY);
-    const int32_t *list = ms.list + a;
-    switch (longest.method) {
-      case FP16:
-      case H2O:
-      case ROCKET: {
-        const int64_t chunks = (int64_t)longest.n0 * Hkv * (D / 8);
-        hipLaunchKernelGGL(k_prefill_copy<D>, dim3((unsigned)((chunks + 255) / 256), n), dim3(256), 0, st, dv.seqs,
-                           list, dv.state, k, v, Hkv);
-        break;
-      }
-      case UQ:
-        hipLaunchKernelGGL(k_uq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, v, Hkv);
-        hipLaunchKernelGGL(k_uq_keys<D>, dim3(H * (longest.n0 / 64 + 1), n), dim3(kQuantThreads), 0, st, dv.seqs,
-                           list, dv.state, k, Hkv);
-        break;
-      case KVQ:
-        hipLaunchKernelGGL(k_kvq_calibrate<D>, dim3(H * (D / kCalibChannels), n), dim3(kCalibThreads), 0, st, dv.seqs,
-                           list, k, Hkv);
-        hipLaunchKernelGGL(k_kvq_keys<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, k, dv.cbtab,
-                           Hkv);
-        hipLaunchKernelGGL(k_kvq_scan, dim3(H, n), dim3(kScanThreads), 0, st, dv.seqs, list, dv.state, Hkv);
-        hipLaunchKernelGGL(k_kvq_outliers<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, k, Hkv);
-        hipLaunchKernelGGL(k_kvq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, list, v,
-                           dv.cbtab, Hkv);
-        break;
-      default:
-        return hipErrorInvalidValue;
+  const unsigned H = Hkv, n = sg.n, blocks = (sg.longest + kQuantTokens - 1) / kQuantTokens;
+  switch (sg.method) {
+    case FP16:
+    case H2O:
+    case ROCKET: {
+      const int64_t chunks = (int64_t)sg.longest * Hkv * (D / 8);
+      hipLaunchKernelGGL(k_prefill_copy<D>, dim3((unsigned)((chunks + 255) / 256), n), dim3(256), 0, st, dv.seqs,
+                         sg.list, dv.state, k, v, Hkv);
+      break;
     }
+    case UQ:
+      hipLaunchKernelGGL(k_uq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, sg.list, v, Hkv);
+      hipLaunchKernelGGL(k_uq_keys<D>, dim3(H * (sg.longest / 64 + 1), n), dim3(kQuantThreads), 0, st, dv.seqs,
+                         sg.list, dv.state, k, Hkv);
+      break;
+    case KVQ:
+      hipLaunchKernelGGL(k_kvq_calibrate<D>, dim3(H * (D / kCalibChannels), n), dim3(kCalibThreads), 0, st, dv.seqs,
+                         sg.list, k, Hkv);
+      hipLaunchKernelGGL(k_kvq_keys<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, sg.list, k, dv.cbtab,
+                         Hkv);
+      hipLaunchKernelGGL(k_kvq_scan, dim3(H, n), dim3(kScanThreads), 0, st, dv.seqs, sg.list, dv.state, Hkv);
+      hipLaunchKernelGGL(k_kvq_outliers<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, sg.list, k, Hkv);
+      hipLaunchKernelGGL(k_kvq_values<D>, dim3(H * blocks, n), dim3(kQuantThreads), 0, st, dv.seqs, sg.list, v,
+                         dv.cbtab, Hkv);
+      break;
+    default:
+      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -800,9 +793,9 @@ hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *
   }
 }
 
-hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *k,
-                              const uint16_t *v, hipStream_t st) {
-  return sh.D == 64 ? prefill_impl<64>(dv, sh, hs, k, v, st) : prefill_impl<128>(dv, sh, hs, k, v, st);
+hipError_t launch_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *k, const uint16_t *v,
+                          hipStream_t st) {
+  return sh.D == 64 ? prefill_impl<64>(dv, sh, sg, k, v, st) : prefill_impl<128>(dv, sh, sg, k, v, st);
 }
 
 }  // namespace mkv

@@ -5,8 +5,6 @@
 // observation window votes for (SnapKV), then attends to a top-k subset per decode step.
 // Selections are block-wide radix selects on order-preserving 32-bit keys followed by an
 // ascending-position compaction, so ties resolve by position exactly as specified.
-#include <algorithm>
-
 #include "select_dev.h"
 
 namespace mkv {
@@ -410,7 +408,7 @@ __global__ __launch_bounds__(NT) void k_h2o_gather(const SeqDesc *__restrict__ s
 // 0 .. n0 - w + i).  Pass 1: per chunk of keys the partial (max, sum of exp2) of every row.  Pass 2:
 // each row's partials merged.  Pass 3: the votes of a span's keys, the logits recomputed.  Pass 4: max
 // pooling into order-preserving keys.  Pass 5: the selection; pass 6: the kept rows gathered.  Every
-// pass is one launch over all RocketKV sequences (grid as for H2O).
+// pass is one launch over a group's sequences (grid as for H2O).
 //
 // Logit tiles as in the H2O scoring: S^T = K Q^T, a lane owning one row and 16 keys of a 32 x 32 tile.
 // A workgroup takes a span of keys and holds ROWS window rows in LDS; a wave holds 32 keys as operands,
@@ -772,37 +770,30 @@ hipError_t topk_impl(const Dev &dv, const Shape &sh, const uint16_t *q, int32_t 
 }
 
 template <int D>
-hipError_t h2o_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *q, hipStream_t st) {
+hipError_t h2o_prefill_impl(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *q, hipStream_t st) {
   const float scale2 = kLog2e / sqrtf((float)D);
-  const MethodSeqs &ms = dv.of[H2O];
   const int lg = __builtin_ctz((unsigned)sh.G);
   // grid x: kv heads (fastest) x the longest prompt's blocks; workgroups past a shorter prompt's end
   // leave at once
-  const unsigned vblocks = (unsigned)((((int64_t)longest.n0 << lg) + kScoreBlock - 1) / kScoreBlock);
-  const unsigned kblocks = (longest.n0 + kScoreBlock - 1) / kScoreBlock, H = sh.Hkv;
-  for (int a = 0; a < ms.n; a += kMaxGridY) {
-    const unsigned n = std::min(ms.n - a, kMaxGridY);
-    const int32_t *list = ms.list + a;
-    hipLaunchKernelGGL(k_h2o_rowstats<D>, dim3(H * vblocks, n), dim3(NT), 0, st, dv.seqs, list, q, sh.Hq, sh.Hkv, lg,
-                       scale2);
-    hipLaunchKernelGGL(k_h2o_colsums<D>, dim3(H * kblocks * kScoreSegs, n), dim3(NT), 0, st, dv.seqs, list, q, sh.Hq,
-                       sh.Hkv, lg, scale2);
-    hipLaunchKernelGGL(k_h2o_sum, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list, sh.Hkv,
-                       lg);
-    hipLaunchKernelGGL(k_h2o_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, list, dv.state, sh.Hkv);
-    hipLaunchKernelGGL(k_h2o_gather<D>, dim3(H * ((ms.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0,
-                       st, dv.seqs, list, sh.Hkv);
-  }
+  const unsigned vblocks = (unsigned)((((int64_t)sg.longest << lg) + kScoreBlock - 1) / kScoreBlock);
+  const unsigned kblocks = (sg.longest + kScoreBlock - 1) / kScoreBlock, H = sh.Hkv, n = sg.n;
+  hipLaunchKernelGGL(k_h2o_rowstats<D>, dim3(H * vblocks, n), dim3(NT), 0, st, dv.seqs, sg.list, q, sh.Hq, sh.Hkv, lg,
+                     scale2);
+  hipLaunchKernelGGL(k_h2o_colsums<D>, dim3(H * kblocks * kScoreSegs, n), dim3(NT), 0, st, dv.seqs, sg.list, q, sh.Hq,
+                     sh.Hkv, lg, scale2);
+  hipLaunchKernelGGL(k_h2o_sum, dim3(H * ((sg.longest + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, sg.list, sh.Hkv,
+                     lg);
+  hipLaunchKernelGGL(k_h2o_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, sg.list, dv.state, sh.Hkv);
+  hipLaunchKernelGGL(k_h2o_gather<D>, dim3(H * ((sg.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0, st,
+                     dv.seqs, sg.list, sh.Hkv);
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &longest, const uint16_t *qw,
-                             hipStream_t st) {
+hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *qw, hipStream_t st) {
   const float scale2 = kLog2e / sqrtf((float)D);
-  const MethodSeqs &ms = dv.of[ROCKET];
   const int lg = __builtin_ctz((unsigned)sh.G);
-  const unsigned H = sh.Hkv, rows = (unsigned)ms.max_vote_rows << lg;
+  const unsigned H = sh.Hkv, n = sg.n, rows = (unsigned)sg.max_vote_rows << lg;
   // Keys per workgroup: the span whose rounds of workgroups (two per CU) take the least time, a round
   // its keys and the set-up, as long as about 200 of them; for the row statistics one chunk or whole
   // chunks for each wave.  (4 prompts of 32768 tokens: one round of 2048 keys 78 and 62 us, row statistics
@@ -811,33 +802,29 @@ hipError_t snap_prefill_impl(const Dev &dv, const Shape &sh, const SeqDesc &long
     int span = SNAP_CHUNK;
     int64_t best = INT64_MAX;
     for (int s = SNAP_CHUNK; s <= 2048; s = s + step - s % step) {
-      const int64_t wgs = (int64_t)H * std::min(ms.n, kMaxGridY) * ((longest.n0 + s - 1) / s);
+      const int64_t wgs = (int64_t)H * n * ((sg.longest + s - 1) / s);
       const int64_t time = (wgs + 2 * kCus - 1) / (2 * kCus) * (s + 200);
       if (time < best) best = time, span = s;
     }
     return span;
   };
   const int sspan = best_span(4 * SNAP_CHUNK), vspan = best_span(SNAP_KEYS);
-  const unsigned sspans = (longest.n0 + sspan - 1) / sspan, vspans = (longest.n0 + vspan - 1) / vspan;
-  for (int a = 0; a < ms.n; a += kMaxGridY) {
-    const unsigned n = std::min(ms.n - a, kMaxGridY);
-    const int32_t *list = ms.list + a;
-    if (rows > 0) {  // some sequence keeps less than its prompt
-      // all rows of 32-token windows of up to 4, or of 8 query heads, in LDS at once: K is read once a pass
-      // (8 prompts of 6000-9000 tokens of 8 heads: 152 us with 128 rows and two passes over K, 137 with 256)
-      hipLaunchKernelGGL((rows <= 128 ? k_snap_rowstats<D, 128> : k_snap_rowstats<D, 256>), dim3(H * sspans, n),
-                         dim3(NT), 0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, sspan, scale2);
-      hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + kMergeRows - 1) / kMergeRows), n), dim3(NT), 0, st, dv.seqs,
-                         list, sh.Hkv, lg);
-      hipLaunchKernelGGL((rows <= 128 ? k_snap_votes<D, 128> : k_snap_votes<D, 256>), dim3(H * vspans, n), dim3(NT),
-                         0, st, dv.seqs, list, qw, sh.Hq, sh.Hkv, lg, vspan, scale2);
-      hipLaunchKernelGGL(k_snap_pool, dim3(H * ((longest.n0 + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, list,
-                         sh.Hkv);
-    }
-    hipLaunchKernelGGL(k_snap_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, list, dv.state, sh.Hkv);
-    hipLaunchKernelGGL(k_snap_gather<D>, dim3(H * ((ms.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0,
-                       st, dv.seqs, list, sh.Hkv);
+  const unsigned sspans = (sg.longest + sspan - 1) / sspan, vspans = (sg.longest + vspan - 1) / vspan;
+  if (rows > 0) {  // some sequence keeps less than its prompt
+    // all rows of 32-token windows of up to 4, or of 8 query heads, in LDS at once: K is read once a pass
+    // (8 prompts of 6000-9000 tokens of 8 heads: 152 us with 128 rows and two passes over K, 137 with 256)
+    hipLaunchKernelGGL((rows <= 128 ? k_snap_rowstats<D, 128> : k_snap_rowstats<D, 256>), dim3(H * sspans, n), dim3(NT),
+                       0, st, dv.seqs, sg.list, qw, sh.Hq, sh.Hkv, lg, sspan, scale2);
+    hipLaunchKernelGGL(k_snap_merge, dim3(H * ((rows + kMergeRows - 1) / kMergeRows), n), dim3(NT), 0, st, dv.seqs,
+                       sg.list, sh.Hkv, lg);
+    hipLaunchKernelGGL((rows <= 128 ? k_snap_votes<D, 128> : k_snap_votes<D, 256>), dim3(H * vspans, n), dim3(NT), 0,
+                       st, dv.seqs, sg.list, qw, sh.Hq, sh.Hkv, lg, vspan, scale2);
+    hipLaunchKernelGGL(k_snap_pool, dim3(H * ((sg.longest + NT - 1) / NT), n), dim3(NT), 0, st, dv.seqs, sg.list,
+                       sh.Hkv);
   }
+  hipLaunchKernelGGL(k_snap_keep, dim3(H, n), dim3(kTopkThreads), 0, st, dv.seqs, sg.list, dv.state, sh.Hkv);
+  hipLaunchKernelGGL(k_snap_gather<D>, dim3(H * ((sg.max_kept + kGatherSlots - 1) / kGatherSlots), n), dim3(NT), 0, st,
+                     dv.seqs, sg.list, sh.Hkv);
   return hipGetLastError();
 }
 
@@ -858,15 +845,14 @@ hipError_t launch_topk(const Dev &dv, const Shape &sh, const uint16_t *q, int32_
   }
 }
 
-hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *q_rows,
-                                  hipStream_t st) {
-  return sh.D == 64 ? h2o_prefill_impl<64>(dv, sh, hs, q_rows, st) : h2o_prefill_impl<128>(dv, sh, hs, q_rows, st);
+hipError_t launch_h2o_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *q_rows,
+                              hipStream_t st) {
+  return sh.D == 64 ? h2o_prefill_impl<64>(dv, sh, sg, q_rows, st) : h2o_prefill_impl<128>(dv, sh, sg, q_rows, st);
 }
 
-hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int, const uint16_t *q_window,
-                                   hipStream_t st) {
-  return sh.D == 64 ? snap_prefill_impl<64>(dv, sh, hs, q_window, st)
-                    : snap_prefill_impl<128>(dv, sh, hs, q_window, st);
+hipError_t launch_snap_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *q_window,
+                               hipStream_t st) {
+  return sh.D == 64 ? snap_prefill_impl<64>(dv, sh, sg, q_window, st) : snap_prefill_impl<128>(dv, sh, sg, q_window, st);
 }
 
 }  // namespace mkv

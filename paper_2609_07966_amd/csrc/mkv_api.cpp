@@ -58,8 +58,8 @@ struct Layout {
   std::vector<int4> prep;      // decode-step append / scoring work list
   std::vector<int2> rk_pairs;  // RocketKV (seq, kv head) pairs
   std::vector<int4> comb;      // combine work list
-  std::vector<int32_t> lists;  // sequences grouped by method, longest prompt first
-  MethodSeqs of[kMethods];     // `list` not set (the place in `lists` follows from the counts)
+  std::vector<int32_t> lists;    // the groups' sequences, one group after another
+  std::vector<SeqGroup> groups;  // `list` not set (the place in `lists` follows from the counts)
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -223,19 +223,33 @@ void fill_lists(Layout *L, int Hkv) {
       for (int h = 0; h < Hkv; ++h)
         for (int p = 0; p < parts; ++p) L->comb.push_back(make_int4(s, h, p, parts));
     }
+  // Prefill groups.  A launch has workgroups for every sequence's length up to the longest's, and those
+  // past a shorter one's end leave at once, 4-5 a nanosecond (1 where they hold the H2O scores' LDS); a
+  // launch of its own costs a few microseconds.  A group ends where the idle tokens would pass twice its
+  // own, plus 2^20 per kv head.  (One fp16 prompt of 131072
+  // tokens with 127 of 300: 704 us with launches per sequence, 1885 in one group, 227 in two; uniform 4-bit
+  // 3416, 1187, 313; one of 32768 with 31 of 300 under KVQuant at 3 bits 3258, 394, 370.)
+  const double spare = double(1 << 20) / Hkv;
   for (int m = 0; m < kMethods; ++m) {
-    MethodSeqs &ms = L->of[m];
-    for (int s = 0; s < S; ++s) {
-      const SeqDesc &d = L->seqs[s];
-      if (d.method != m) continue;
-      L->lists.push_back(s);
-      ++ms.n;
-      if (m == ROCKET && d.T < d.n0) ms.max_vote_rows = std::max(ms.max_vote_rows, d.w_eff);
-      ms.max_kept = std::max(ms.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
-    }
-    std::stable_sort(L->lists.end() - ms.n, L->lists.end(),
+    const size_t first = L->lists.size();
+    for (int s = 0; s < S; ++s)
+      if (L->seqs[s].method == m) L->lists.push_back(s);
+    std::stable_sort(L->lists.begin() + first, L->lists.end(),
                      [&](int32_t a, int32_t b) { return L->seqs[a].n0 > L->seqs[b].n0; });
-    if (ms.n > 0) ms.longest = L->lists[L->lists.size() - ms.n];
+    double own = 0.0, idle = 0.0;
+    for (size_t i = first; i < L->lists.size(); ++i) {
+      const SeqDesc &d = L->seqs[L->lists[i]];
+      if (i > first) idle += L->groups.back().longest - d.n0;
+      if (i == first || idle > 2 * own + spare || L->groups.back().n == kMaxGridY) {
+        L->groups.push_back(SeqGroup{nullptr, m, 0, d.n0, 0, 0});
+        own = idle = 0.0;
+      }
+      SeqGroup &sg = L->groups.back();
+      ++sg.n;
+      own += d.n0;
+      if (m == ROCKET && d.T < d.n0) sg.max_vote_rows = std::max(sg.max_vote_rows, d.w_eff);
+      sg.max_kept = std::max(sg.max_kept, m == H2O ? std::min(d.B, d.n0) : m == ROCKET ? std::min(d.T, d.n0) : d.n0);
+    }
   }
 }
 
@@ -518,6 +532,7 @@ struct mkv_cache {
   Shape sh{};
   std::vector<mkv_config> cfg;
   std::vector<SeqDesc> hs;  // absolute device pointers
+  std::vector<SeqGroup> groups;
   char *arena = nullptr;
   Dev dv{};
   Phase phase = PH_CREATED;
@@ -559,6 +574,15 @@ mkv_status layout_tiles(const mkv_shape *shape, const mkv_config *cfg, const int
   if (st != MKV_OK) return st;
   *tiles = L.tiles;
   *seqs = L.seqs;
+  return MKV_OK;
+}
+mkv_status layout_groups(const mkv_shape *shape, const mkv_config *cfg, const int32_t *prompt_len,
+                         std::vector<SeqGroup> *groups, std::vector<int32_t> *lists) {
+  Layout L;
+  const mkv_status st = make_layout(shape, cfg, prompt_len, &L, true);
+  if (st != MKV_OK) return st;
+  *groups = L.groups;
+  *lists = L.lists;
   return MKV_OK;
 }
 }  // namespace mkv
@@ -680,10 +704,10 @@ mkv_status mkv_cache_create(const mkv_shape *shape, const mkv_config *cfg, const
   c->dv.n_tiles_uq = L.n_tiles_uq;
   c->dv.n_tiles_rk = L.n_tiles_rk;
   const int32_t *list = reinterpret_cast<const int32_t *>(c->arena + L.off_lists);
-  for (int m = 0; m < kMethods; ++m) {
-    c->dv.of[m] = L.of[m];
-    c->dv.of[m].list = list;
-    list += L.of[m].n;
+  c->groups = std::move(L.groups);
+  for (SeqGroup &sg : c->groups) {
+    sg.list = list;
+    list += sg.n;
   }
   hipStream_t hst = static_cast<hipStream_t>(stream);
   // the tables in one copy (each copy from pageable memory costs the host several microseconds)
@@ -769,9 +793,8 @@ mkv_status mkv_append_quantize(mkv_cache *c, const uint16_t *k, const uint16_t *
       if (cu_new[s + 1] - cu_new[s] != c->hs[s].n0)
         return fail(MKV_EINVAL, "prefill: seq %d appends %d rows, prompt_len is %d", s, cu_new[s + 1] - cu_new[s],
                     c->hs[s].n0);
-    for (const MethodSeqs &ms : c->dv.of) {
-      if (ms.n == 0) continue;
-      hipError_t e = launch_prefill_seq(c->dv, c->sh, c->hs[ms.longest], ms.longest, k, v, hst);
+    for (const SeqGroup &sg : c->groups) {
+      hipError_t e = launch_prefill(c->dv, c->sh, sg, k, v, hst);
       if (e != hipSuccess) return hip_fail(e, "prefill append");
     }
     c->phase = (c->any_h2o || c->any_rocket) ? PH_PROMPT : PH_READY;
@@ -788,9 +811,9 @@ mkv_status mkv_h2o_update_evict(mkv_cache *c, const uint16_t *q_prompt, void *st
   if (q_prompt != nullptr) {
     if (c->phase != PH_PROMPT || c->h2o_done)
       return fail(MKV_ESTATE, "H2O prefill scoring runs once, after the prefill append");
-    if (c->any_h2o) {
-      const int longest = c->dv.of[H2O].longest;
-      hipError_t e = launch_h2o_prefill_seq(c->dv, c->sh, c->hs[longest], longest, q_prompt, hst);
+    for (const SeqGroup &sg : c->groups) {
+      if (sg.method != H2O) continue;
+      hipError_t e = launch_h2o_prefill(c->dv, c->sh, sg, q_prompt, hst);
       if (e != hipSuccess) return hip_fail(e, "H2O prefill");
     }
     c->h2o_done = true;
@@ -813,9 +836,11 @@ mkv_status mkv_snap_prefill_evict(mkv_cache *c, const uint16_t *q_window, void *
     return fail(MKV_ESTATE, "SnapKV prefill eviction runs once, after the prefill append");
   if (!q_window) return fail(MKV_EINVAL, "q_window is NULL");
   hipStream_t hst = static_cast<hipStream_t>(stream);
-  const int longest = c->dv.of[ROCKET].longest;
-  hipError_t e = launch_snap_prefill_seq(c->dv, c->sh, c->hs[longest], longest, q_window, hst);
-  if (e != hipSuccess) return hip_fail(e, "SnapKV prefill");
+  for (const SeqGroup &sg : c->groups) {
+    if (sg.method != ROCKET) continue;
+    hipError_t e = launch_snap_prefill(c->dv, c->sh, sg, q_window, hst);
+    if (e != hipSuccess) return hip_fail(e, "SnapKV prefill");
+  }
   c->snap_done = true;
   if (!c->any_h2o || c->h2o_done) c->phase = PH_READY;
   return MKV_OK;

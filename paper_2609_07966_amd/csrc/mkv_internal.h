@@ -147,14 +147,15 @@ constexpr int kCombineSlots = 2048;
 
 // H2O prefill scoring: a prompt's query rows are summed over in at most this many segments.
 constexpr int kScoreSegs = 8;
-// Sequences of one launch over a method's sequences (the grid's y extent).
+// Sequences of one launch over a group of them (the grid's y extent).
 constexpr int kMaxGridY = 32768;
 
-// The sequences of one method, longest prompt first, the most tokens one of them keeps after prefill,
-// and the most window positions one votes with (0: every one keeps its whole prompt).
-struct MethodSeqs {
+// Sequences of one method whose prompts go through each prefill stage in one launch, longest first:
+// their number, the longest prompt, the most tokens one of them keeps after prefill, and the most window
+// positions one votes with (0: every one keeps its whole prompt).
+struct SeqGroup {
   const int32_t *list = nullptr;  // device
-  int n = 0, longest = -1, max_kept = 0, max_vote_rows = 0;
+  int method = 0, n = 0, longest = 0, max_kept = 0, max_vote_rows = 0;
 };
 
 // Kernel launchers (defined in the .hip files).  All enqueue on `st`.
@@ -174,7 +175,6 @@ struct Dev {
   int n_prep, n_rk_pairs, n_comb;
   // the step's tokens, when the attention partial launch is to append them itself (else nullptr)
   const uint16_t *k_new = nullptr, *v_new = nullptr;
-  MethodSeqs of[kMethods];
 };
 
 // Optional timing events of one launch: when set, they record the kernel's own start and end
@@ -186,10 +186,9 @@ struct LaunchEv {
 // H2O pairs whose last attention pass chose a victim write the token into its slot.
 hipError_t launch_append_decode(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                                 hipStream_t st, LaunchEv ev = {});
-// The prompt append of every sequence of one method, one launch per stage; hs, seq: the method's
-// sequence with the longest prompt; k, v: the whole batch's rows.
-hipError_t launch_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
-                              const uint16_t *k, const uint16_t *v, hipStream_t st);
+// The prompt append of a group, one launch per stage; k, v: the whole batch's rows.
+hipError_t launch_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *k, const uint16_t *v,
+                          hipStream_t st);
 hipError_t launch_attention_partial(const Dev &dv, const Shape &sh, const uint16_t *q, hipStream_t st,
                                     LaunchEv ev = {});
 // The static split-K workspace of the current device (kStaticScratchBytes), its address looked up
@@ -197,9 +196,12 @@ hipError_t launch_attention_partial(const Dev &dv, const Shape &sh, const uint16
 constexpr size_t kStaticScratchBytes = size_t(8) << 20;
 hipError_t static_scratch(float **ptr, size_t *bytes);
 // The attention tiles of a cache layout in launch order, and the sequences' descriptors (tile
-// bookkeeping: tile_first, tile_count, chunk); host only, for checks of the layout rules.
+// bookkeeping: tile_first, tile_count, chunk); and its prefill groups with the sequences of all of them in
+// turn; host only, for checks of the layout rules.
 mkv_status layout_tiles(const mkv_shape *shape, const mkv_config *cfg, const int32_t *prompt_len,
                         std::vector<int4> *tiles, std::vector<SeqDesc> *seqs);
+mkv_status layout_groups(const mkv_shape *shape, const mkv_config *cfg, const int32_t *prompt_len,
+                         std::vector<SeqGroup> *groups, std::vector<int32_t> *lists);
 hipError_t launch_attention_combine(const Dev &dv, const Shape &sh, float *out, hipStream_t st,
                                     LaunchEv ev = {});
 hipError_t launch_topk(const Dev &dv, const Shape &sh, const uint16_t *q, int32_t *pos_out, int topk_max,
@@ -209,13 +211,13 @@ hipError_t launch_topk(const Dev &dv, const Shape &sh, const uint16_t *q, int32_
 // launch_append_decode followed by launch_topk without positions.
 hipError_t launch_append_select(const Dev &dv, const Shape &sh, const uint16_t *k, const uint16_t *v,
                                 const uint16_t *q, hipStream_t st, LaunchEv ev_score = {}, LaunchEv ev_select = {});
-// Scoring and keep-set of every H2O sequence, one launch per stage; hs, seq: the one with the longest
-// prompt; q_rows: the prompt queries of all of them, in sequence order.
-hipError_t launch_h2o_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
-                                  const uint16_t *q_rows, hipStream_t st);
-// SnapKV of every RocketKV sequence, likewise; q_window: their window queries in sequence order.
-hipError_t launch_snap_prefill_seq(const Dev &dv, const Shape &sh, const SeqDesc &hs, int seq,
-                                   const uint16_t *q_window, hipStream_t st);
+// Scoring and keep-set of a group of H2O sequences, one launch per stage; q_rows: the prompt queries of
+// all the batch's H2O sequences, in sequence order.
+hipError_t launch_h2o_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *q_rows,
+                              hipStream_t st);
+// SnapKV of a group of RocketKV sequences, likewise; q_window: the batch's window queries.
+hipError_t launch_snap_prefill(const Dev &dv, const Shape &sh, const SeqGroup &sg, const uint16_t *q_window,
+                               hipStream_t st);
 // Streaming read of `bytes` (a multiple of `chunk`, itself a multiple of 16 KiB); sink: device
 // uint32 [256], written only in the (practically never taken) branch that keeps the loads alive.
 hipError_t launch_probe_read(const void *buf, size_t bytes, size_t chunk, uint32_t *sink, hipStream_t st);

@@ -15,13 +15,13 @@
 namespace mkv {
 // stubs: every path exercised here fails or returns before any launch
 hipError_t launch_append_decode(const Dev &, const Shape &, const uint16_t *, const uint16_t *, hipStream_t, LaunchEv) { return hipErrorNotSupported; }
-hipError_t launch_prefill_seq(const Dev &, const Shape &, const SeqDesc &, int, const uint16_t *, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_prefill(const Dev &, const Shape &, const SeqGroup &, const uint16_t *, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_attention_partial(const Dev &, const Shape &, const uint16_t *, hipStream_t, LaunchEv) { return hipErrorNotSupported; }
 hipError_t launch_attention_combine(const Dev &, const Shape &, float *, hipStream_t, LaunchEv) { return hipErrorNotSupported; }
 hipError_t launch_topk(const Dev &, const Shape &, const uint16_t *, int32_t *, int, hipStream_t, LaunchEv) { return hipErrorNotSupported; }
 hipError_t launch_append_select(const Dev &, const Shape &, const uint16_t *, const uint16_t *, const uint16_t *, hipStream_t, LaunchEv, LaunchEv) { return hipErrorNotSupported; }
-hipError_t launch_h2o_prefill_seq(const Dev &, const Shape &, const SeqDesc &, int, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_snap_prefill_seq(const Dev &, const Shape &, const SeqDesc &, int, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_h2o_prefill(const Dev &, const Shape &, const SeqGroup &, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_snap_prefill(const Dev &, const Shape &, const SeqGroup &, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_init_state(const Dev &, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_probe_read(const void *, size_t, size_t, uint32_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t static_scratch(float **, size_t *) { return hipErrorNotSupported; }
@@ -173,6 +173,43 @@ int main() {
         CHECK(mkv::layout_tiles(&sh, cs.data(), pl.data(), &tiles, &sd) == MKV_OK);
         CHECK(sd[0].chunk % 256 == 0);
       }
+  // prefill groups: every sequence once, one method a group, longest prompts first, and the tokens that
+  // shorter prompts leave idle under the longest one bounded, with few groups for ordinary batches
+  for (int kind = 0; kind < 4; ++kind) {
+    const int S = kind == 3 ? 40000 : 300, Hkv = kind == 3 ? 1 : 8;
+    mkv_shape sh{S, Hkv, Hkv, 64, 1};
+    std::vector<mkv_config> cs(S);
+    std::vector<int32_t> pl(S);
+    uint32_t r = 99u + kind;
+    for (int i = 0; i < S; ++i) {
+      r = r * 1664525u + 1013904223u;
+      cs[i] = kind == 3 ? cfg(MKV_FP16) : all[i % n];
+      // one long prompt per method among short ones; between 1000 and 32000 tokens; all alike; very many
+      const int ragged = i < n ? 60000 : 100 + (int)((r >> 8) % 300u);
+      const int spread = (int)(1000.0 * std::exp(3.46 * ((r >> 8) % 1000u) / 1000.0));
+      pl[i] = kind == 0 ? ragged : kind == 1 ? spread : 100;
+    }
+    std::vector<mkv::SeqGroup> gs;
+    std::vector<int32_t> lists;
+    CHECK(mkv::layout_groups(&sh, cs.data(), pl.data(), &gs, &lists) == MKV_OK);
+    CHECK((int)lists.size() == S);
+    std::vector<int> seen(S, 0);
+    size_t at = 0;
+    for (const mkv::SeqGroup &sg : gs) {
+      double own = 0, idle = 0;
+      CHECK(sg.n >= 1 && sg.n <= mkv::kMaxGridY && at + sg.n <= lists.size());
+      for (int i = 0; i < sg.n && at < lists.size(); ++i, ++at) {
+        const int s = lists[at];
+        ++seen[s];
+        CHECK(cs[s].method == sg.method && pl[s] <= sg.longest && (i > 0 || pl[s] == sg.longest));
+        own += pl[s];
+        idle += sg.longest - pl[s];
+      }
+      CHECK(idle <= 2 * own + (1 << 20) / Hkv);
+    }
+    for (int v : seen) CHECK(v == 1);
+    CHECK(kind == 3 ? gs.size() == 2 : gs.size() <= (kind == 2 ? 5 : 15));
+  }
   // the configuration choice
   {
     mkv_candidate c[3] = {{MKV_KVQ, 0, 3.0, 5.0, 0.6}, {MKV_H2O, 1, 1.0, 9.0, 0.5}, {MKV_FP16, 0, 2.0, 20.0, 0.7}};

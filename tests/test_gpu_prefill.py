@@ -311,3 +311,51 @@ def test_uniform_prompts_at_block_edges(hkv, g, d):
         assert np.abs(out[s] - ref).max() <= TOL * max(rms, 1.0), f"sequence {s} ({m} tokens)"
         at += m
     c.close()
+
+
+def test_one_long_prompt_among_short_ones():
+    """Batches whose short prompts are prefilled apart from the long one of their method: what a short
+    sequence holds is what it holds alone, and its first step attends to its own tokens."""
+    import torch
+    from gpu_harness import TOL
+    from paper_2609_07966_amd.cache import KVCache
+    d, longest, short = 64, 60000, 24  # one kv head: groups end at 2^20 idle tokens and twice their own
+    methods = [{"method": "fp16"}, {"method": "uq", "bits": 4, "group": 64}, {"method": "kvq", "bits": 3, "outlier_bp": 100},
+               {"method": "h2o", "budget_pct": 50},
+               {"method": "rocket", "keep_tokens": 60, "window": 16, "pool": 3, "topk": 0, "n_channels": 8}]
+    cfgs, lens = [], []
+    for s in range(short + 1):
+        cfgs += methods
+        lens += [longest if s == 7 else 90 + 3 * s] * len(methods)
+    n, S, at = sum(lens), len(lens), np.concatenate([[0], np.cumsum(lens)])
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *shape: torch.randn(shape, generator=g, device="cuda").half()
+    k, v, kn, vn, q, qw = rand(n, 1, d), rand(n, 1, d), rand(S, 1, d), rand(S, 1, d), rand(S, 1, d), rand(S, 16, 1, d)
+    books = [float(i) / 16 - 0.5 for b in (2, 3, 4) for _ in range(2) for i in range(1 << b)]
+
+    def admit(which):
+        c = KVCache((len(which), 1, 1, d, 1), [cfgs[s] for s in which], [lens[s] for s in which], codebooks=books)
+        rows = lambda x: torch.cat([x[at[s]:at[s + 1]] for s in which])
+        c.append_prompt(rows(k), rows(v))
+        of = lambda m: [s for s in which if cfgs[s]["method"] == m]
+        if of("h2o"):
+            c.h2o_prefill(torch.cat([k[at[s]:at[s + 1]] for s in of("h2o")]))  # (queries equal to the keys)
+        if of("rocket"):
+            c.snap_prefill(qw[of("rocket")].contiguous())
+        held = lambda i, s: [c.export(i, 0, what) for what in
+                             {"fp16": ["counts"], "uq": ["codes_k", "codes_v", "scales_v"],
+                              "kvq": ["codes_k", "codes_v", "outliers_k", "scales_k"],
+                              "h2o": ["positions", "scores"], "rocket": ["positions"]}[cfgs[s]["method"]]]
+        out = torch.empty((len(which), 1, d), dtype=torch.float32, device="cuda")
+        got = [held(i, s) for i, s in enumerate(which)]
+        c.step(kn[which].contiguous(), vn[which].contiguous(), q[which].contiguous(), out)
+        out = out.cpu().numpy()
+        c.close()
+        return got, out
+
+    batch, out = admit(list(range(S)))
+    for s in list(range(0, 10)) + list(range(S - 10, S)):
+        alone, ref = admit([s])
+        for a, b in zip(batch[s], alone[0]):
+            np.testing.assert_array_equal(a, b, err_msg=f"sequence {s}: {cfgs[s]}")
+        assert np.abs(out[s] - ref[0]).max() <= TOL, f"sequence {s}: {cfgs[s]}"
