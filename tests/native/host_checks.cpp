@@ -22,7 +22,6 @@ hipError_t launch_topk(const Dev &, const Shape &, const uint16_t *, int32_t *, 
 hipError_t launch_append_select(const Dev &, const Shape &, const uint16_t *, const uint16_t *, const uint16_t *, hipStream_t, LaunchEv, LaunchEv) { return hipErrorNotSupported; }
 hipError_t launch_h2o_prefill(const Dev &, const Shape &, const SeqGroup &, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_snap_prefill(const Dev &, const Shape &, const SeqGroup &, const uint16_t *, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_init_state(const Dev &, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_probe_read(const void *, size_t, size_t, uint32_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t static_scratch(float **, size_t *) { return hipErrorNotSupported; }
 }  // namespace mkv
@@ -50,6 +49,57 @@ static mkv_config cfg(int method, int bits = 0, int bp = 0, int pct = 0, int kee
   c.n_channels = 32;
   c.keep_ratio = ratio;
   return c;
+}
+
+// Attention tile layout: every (sequence, kv head)'s ranges cover its tokens once in multiples of 64
+// tokens (a key block and a 4-token value block lie within a tile, on which the append in the attention
+// launch relies), partial slots are distinct, RocketKV tiles launch last, and the quantized tiles are
+// spread over the first 3/4 of the others (so about a quarter of the fp16-row tiles follow the last of
+// them).  Returns the number of tiles.
+static int check_tiles(const mkv_shape &sh, const std::vector<mkv_config> &cs, const std::vector<int32_t> &pl) {
+  const int S = sh.n_seqs, Hkv = sh.n_kv_heads;
+  std::vector<int4> tiles;
+  std::vector<mkv::SeqDesc> sd;
+  CHECK(mkv::layout_tiles(&sh, cs.data(), pl.data(), &tiles, &sd) == MKV_OK);
+  int expect = 0;
+  for (int i = 0; i < S; ++i) expect += Hkv * sd[i].tile_count;
+  CHECK((int)tiles.size() == expect);
+  std::vector<int> seen(tiles.size(), 0);
+  std::vector<std::vector<int>> cover(S * Hkv);
+  int last_nonrocket = -1, first_rocket = (int)tiles.size(), last_quant = -1, n_rows = 0;
+  for (int i = 0; i < (int)tiles.size(); ++i) {
+    const int4 t = tiles[i];
+    CHECK(t.x >= 0 && t.x < S && t.y >= 0 && t.y < Hkv);
+    if (!(t.x >= 0 && t.x < S && t.y >= 0 && t.y < Hkv)) continue;
+    const mkv::SeqDesc &d = sd[t.x];
+    const int amax = d.method == mkv::ROCKET ? d.topk : d.cap;
+    CHECK(d.chunk > 0 && d.chunk % 64 == 0 && t.z % d.chunk == 0);
+    CHECK(t.z < t.w && t.w == std::min(amax, t.z + d.chunk));
+    const int slot = d.tile_first + t.y * d.tile_count + t.z / d.chunk;
+    CHECK(slot >= 0 && slot < (int)tiles.size());
+    if (slot >= 0 && slot < (int)tiles.size()) ++seen[slot];
+    cover[t.x * Hkv + t.y].push_back(t.z);
+    if (d.method == mkv::ROCKET) {
+      first_rocket = std::min(first_rocket, i);
+    } else {
+      last_nonrocket = i;
+      if (d.method == mkv::KVQ || d.method == mkv::UQ) last_quant = i;
+      else ++n_rows;
+    }
+  }
+  for (int v : seen) CHECK(v == 1);
+  CHECK(last_nonrocket < first_rocket);
+  int rows_after = 0;
+  for (int i = last_quant + 1; i < first_rocket; ++i) rows_after += 1;
+  CHECK(last_quant < 0 || rows_after >= n_rows / 4 - 1);
+  for (int p = 0; p < S * Hkv; ++p) {
+    std::vector<int> z = cover[p];
+    std::sort(z.begin(), z.end());
+    const mkv::SeqDesc &d = sd[p / Hkv];
+    CHECK((int)z.size() == d.tile_count);
+    for (int j = 0; j < (int)z.size(); ++j) CHECK(z[j] == j * d.chunk);
+  }
+  return (int)tiles.size();
 }
 
 int main() {
@@ -103,13 +153,10 @@ int main() {
     CHECK(mkv_cache_create(&sh, &kv, &L, off.data(), fake, b, nullptr, &h) == MKV_EINVAL);
     CHECK(mkv_cache_destroy(nullptr) == MKV_OK);
   }
-  // attention tile layout: every (sequence, kv head)'s ranges cover its tokens once, partial
-  // slots are distinct, RocketKV tiles launch last, and the quantized tiles are spread over the
-  // first 3/4 of the others (so about a quarter of the fp16-row tiles follow the last of them);
-  // a long mixed launch (several rounds of workgroups) and a short one
+  // attention tiles: a long mixed launch (several rounds of workgroups) and a short one
   for (int big = 0; big < 2; ++big) {
-    const int S = big ? 64 : 6, Hkv = 8, D = 128;
-    mkv_shape sh{S, 4 * Hkv, Hkv, D, 128};
+    const int S = big ? 64 : 6;
+    mkv_shape sh{S, 32, 8, 128, 128};
     std::vector<mkv_config> cs(S);
     std::vector<int32_t> pl(S);
     uint32_t r = 777u + big;
@@ -118,47 +165,35 @@ int main() {
       r = r * 1664525u + 1013904223u;
       pl[i] = 1024 + (int)((r >> 8) % (big ? 31744u : 3000u));
     }
-    std::vector<int4> tiles;
-    std::vector<mkv::SeqDesc> sd;
-    CHECK(mkv::layout_tiles(&sh, cs.data(), pl.data(), &tiles, &sd) == MKV_OK);
-    int expect = 0;
-    for (int i = 0; i < S; ++i) expect += Hkv * sd[i].tile_count;
-    CHECK((int)tiles.size() == expect);
-    std::vector<int> seen(tiles.size(), 0);
-    std::vector<std::vector<int>> cover(S * Hkv);
-    int last_nonrocket = -1, first_rocket = (int)tiles.size(), last_quant = -1, n_rows = 0;
-    for (int i = 0; i < (int)tiles.size(); ++i) {
-      const int4 t = tiles[i];
-      CHECK(t.x >= 0 && t.x < S && t.y >= 0 && t.y < Hkv);
-      if (!(t.x >= 0 && t.x < S && t.y >= 0 && t.y < Hkv)) continue;
-      const mkv::SeqDesc &d = sd[t.x];
-      const int amax = d.method == mkv::ROCKET ? d.topk : d.cap;
-      CHECK(d.chunk > 0 && d.chunk % 64 == 0 && t.z % d.chunk == 0);
-      CHECK(t.z < t.w && t.w == std::min(amax, t.z + d.chunk));
-      const int slot = d.tile_first + t.y * d.tile_count + t.z / d.chunk;
-      CHECK(slot >= 0 && slot < (int)tiles.size());
-      if (slot >= 0 && slot < (int)tiles.size()) ++seen[slot];
-      cover[t.x * Hkv + t.y].push_back(t.z);
-      if (d.method == mkv::ROCKET) {
-        first_rocket = std::min(first_rocket, i);
-      } else {
-        last_nonrocket = i;
-        if (d.method == mkv::KVQ || d.method == mkv::UQ) last_quant = i;
-        else ++n_rows;
-      }
-    }
-    for (int v : seen) CHECK(v == 1);
-    CHECK(last_nonrocket < first_rocket);
-    int rows_after = 0;
-    for (int i = last_quant + 1; i < first_rocket; ++i) rows_after += 1;
-    CHECK(last_quant < 0 || rows_after >= n_rows / 4 - 1);
-    for (int p = 0; p < S * Hkv; ++p) {
-      std::vector<int> z = cover[p];
-      std::sort(z.begin(), z.end());
-      const mkv::SeqDesc &d = sd[p / Hkv];
-      CHECK((int)z.size() == d.tile_count);
-      for (int j = 0; j < (int)z.size(); ++j) CHECK(z[j] == j * d.chunk);
-    }
+    check_tiles(sh, cs, pl);
+  }
+  // the rules for fp16 rows alone, quantized sequences alone and the two mixed, from one short sequence to
+  // several rounds of workgroups; a launch that one round of 64 KiB tiles holds (768 of them) has partials
+  // well within the static workspace of mkv_decode_attention_noalloc, and so must it under any other rule
+  for (int d : {64, 128})
+    for (int g : {1, 8})
+      for (int kind = 0; kind < 4; ++kind)
+        for (int S : {1, 3, 8, 24})
+          for (int len : {70, 1000, 4096, 9000}) {
+            mkv_shape sh{S, 8 * g, 8, d, 5};
+            std::vector<mkv_config> cs(S);
+            std::vector<int32_t> pl(S);
+            double rows = 0;
+            for (int i = 0; i < S; ++i) {
+              cs[i] = kind == 0 ? all[5 * (i & 1)] : kind == 1 ? all[1 + i % 4] : kind == 2 ? all[1] : all[i % n];
+              pl[i] = len + 37 * i;
+              rows += pl[i] + 8;
+            }
+            const int tiles = check_tiles(sh, cs, pl);
+            if (8 * rows * 4 * d <= 768.0 * 65536 - 8 * S * 65536.0)
+              CHECK((size_t)tiles * g * (d + 2) * sizeof(float) <= mkv::kStaticScratchBytes);
+          }
+  // ... nor may a launch of three rounds lose it whose general rule keeps to it (its own would not)
+  for (int len : {9106, 14402}) {
+    std::vector<mkv_config> cs(9, cfg(MKV_FP16));
+    for (int i = 1; i < 9; i += 2) cs[i] = cfg(MKV_KVQ, 2, 100);
+    const int tiles = check_tiles(mkv_shape{9, 64, 8, 128, 5}, cs, std::vector<int32_t>(9, len));
+    CHECK((size_t)tiles * 8 * 130 * sizeof(float) <= mkv::kStaticScratchBytes);
   }
   // uniform 4-bit tiles of d = 64 in short launches: 64 tokens or more for each of a workgroup's 4 waves
   for (int S : {1, 3, 8})
