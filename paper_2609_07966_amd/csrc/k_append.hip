@@ -30,19 +30,6 @@ __global__ __launch_bounds__(128) void k_append_decode(const SeqDesc *__restrict
   append_alone<D>(seqs[seq], state + ((size_t)seq * Hkv + h) * ST_WORDS, seq, h, Hkv, k, v, cbtab, L);
 }
 
-// The decode step's first two launches when RocketKV sequences are present.
-//
-// k_append_score, workgroups of kScoreThreads threads over a work list (int4: seq, kv head,
-// part, parts): part -1 appends the token of a non-RocketKV pair on its first D threads (the
-// other waves leave at once; a barrier waits only for waves that have not ended).  A RocketKV pair
-// has ceil(cap / kScoreTokens) parts: part 0 appends its token (rows, channel-major copy,
-// position) and every part picks the channels and scores its kScoreTokens tokens, the new one
-// from the key it holds in LDS.  The state of a RocketKV pair is left to the selecting launch.  Where
-// every pair has one part (SELECT: caps up to kScoreTokens tokens), that workgroup selects from the
-// keys it has in LDS and there is no selecting launch.
-//
-// k_rocket_select, one workgroup of kTopkThreads threads per RocketKV pair (int2: seq, kv head):
-// the top-k of the scores, then the pair's state (count, next position, selection count).
 // The selection of a pair with n tokens (the new one included, if there was room for it) from the keys
 // src(j), and the pair's state after the step; count and pos are those before it, read by every thread
 // before a barrier.
@@ -63,6 +50,19 @@ MKV_DEV void rocket_select(const SeqDesc &sd, int32_t *st, int h, int n, bool ro
   }
 }
 
+// The decode step's first two launches when RocketKV sequences are present.
+//
+// k_append_score, workgroups of kScoreThreads threads over a work list (int4: seq, kv head,
+// part, parts): part -1 appends the token of a non-RocketKV pair on its first D threads (the
+// other waves leave at once; a barrier waits only for waves that have not ended).  A RocketKV pair
+// has ceil(cap / kScoreTokens) parts: part 0 appends its token (rows, channel-major copy,
+// position) and every part picks the channels and scores its kScoreTokens tokens, the new one
+// from the key it holds in LDS.  The state of a RocketKV pair is left to the selecting launch.  Where
+// every pair has one part (SELECT: caps up to kScoreTokens tokens), that workgroup selects from the
+// keys it has in LDS and there is no selecting launch.
+//
+// k_rocket_select, one workgroup of kTopkThreads threads per RocketKV pair (int2: seq, kv head):
+// the top-k of the scores, then the pair's state (count, next position, selection count).
 template <int D, int G, bool SELECT>
 __global__ __launch_bounds__(kScoreThreads) void k_append_score(const SeqDesc *__restrict__ seqs, int32_t *state,
                                                                 const int4 *__restrict__ items,

@@ -14,9 +14,9 @@
 // lane reads 32 contiguous channels of one token), and its result layout is exactly the operand
 // layout of P^T in O^T = V^T P^T (channels x query heads), so probabilities feed the second
 // product without moving.  KVQuant codes become packed fp16 pairs by one LDS table lookup per
-// two codes (codebook entries are fp16 values); its key thresholds are folded into q and its
-// value scales into p, both of which are fp32: their fp16 rounding residual rides in the spare
-// columns G..2G-1 of the same product and is added back after it.  Outliers are sparse
+// two codes (codebook entries are fp16 values); its key thresholds are folded into q, whose fp16
+// rounding residual rides in the spare columns G..2G-1 of the same product and is added back after it,
+// and its value scales into p, rounded to fp16 once.  Outliers are sparse
 // corrections: the logit terms of a batch's key outliers are computed by the whole wave at once,
 // one entry per lane, into LDS and summed per token by the token's lane (LDS atomics measured
 // slower there); value outliers add p (x - s cb[code]) to the wave's per-head LDS rows by LDS
@@ -25,7 +25,7 @@
 //
 // Uniform 4-bit tiles run the same matrix loop: 4-bit codes become exact fp16 integers (one
 // and-or and one packed subtraction per pair), each 64-token block's key steps are folded into q
-// (computed once per channel and head across the wave and staged in LDS), each token's value
+// (computed once per channel and head across the wave and staged in LDS, with its residual), each token's value
 // steps into p, and the minima enter as per-head bias terms.
 //
 // Logits use the base-2 exponent (scaled by log2(e)/sqrt(d)).  fp16-row tiles keep the loads of
@@ -100,7 +100,7 @@ MKV_DEV uint32_t pk_f16(float lo, float hi) { return __builtin_bit_cast(uint32_t
 //   S              token rows 4*lq + j, query head lr
 //   p.v operand A  channel VPL*lr + m, tokens 4*lq + j
 //   O^T            channel VPL*(4*lq + i) + m, query head lr
-// Where q or p carry an fp16 rounding residual, the residual of head g sits in column 2G-1-g,
+// Where q carries an fp16 rounding residual, the residual of head g sits in column 2G-1-g,
 // so one DPP mirror (quad, half-row or row) adds it to column g.
 template <int D>
 struct MG {
@@ -779,7 +779,7 @@ MKV_DEV void wave_mfma(L &ld, int a, int b, Batch<L> &x, QB<D> &qb, float &m_run
 // ================================================================================================
 // The partial kernel: one launch over the tiles of every sequence, whatever its method.
 // ================================================================================================
-// Contiguous token range [a, b) of this wave within its tile, a multiple of 32 tokens.
+// Contiguous token range [a, b) of this wave within its tile, a multiple of `step` tokens.
 struct WaveRange {
   int a, b;
 };
@@ -847,10 +847,11 @@ __global__ __launch_bounds__(kTileThreads) void k_attn_partial_mx(
   const int n_sel = st[ST_SEL_COUNT];
   if constexpr (APPEND) {
     // The step's token is appended here, by the tile that owns its slot: a launch of its own costs
-    // about 4.5 us, an owner's append 1-3 us while the other tiles run (8 x 4096 tokens, per layer:
-    // FP16 35.8 -> 33.4 us, uniform 4-bit 23.5 -> 20.9; 8 x 8192 under H2O-20 27.9 -> 25.0).  No other
-    // tile reads what it writes (a key block and a 4-token value block lie within a tile), and the
-    // counts that all tiles read stay until the combine launch.
+    // about 4.5 us, an owner's append 1-3 us while the other tiles run (steps that append, per layer, the
+    // separate calls and this: 8 x 4096 tokens FP16 38.1 -> 34.8 us, uniform 4-bit 22.7 -> 20.8, KVQuant at 4
+    // bits 33.8 -> 29.1; 8 x 8192 under H2O-20 24.1 -> 21.2).  No other tile reads what it writes (a key
+    // block and a 4-token value block lie within a tile), and the counts that all tiles read stay until
+    // the combine launch.
     static_assert(sizeof(AppendLds<D>) <= sizeof(s_wave), "the append's LDS fits the wave regions");
     int victim;
     const int pos = st[ST_NEXT_POS], at = append_slot(sd, h, n_cnt, &victim);
@@ -1222,7 +1223,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_attn_combine(const SeqDesc 
       const int j = j0 + u * kCombineThreads;
       float acc = 0.f;
 #pragma unroll
-      for (int g = 0; g < G; ++g) acc += fexp2(lgv[u][g] - M[g]) * invL[g];  // arguments <= 0
+      for (int g = 0; g < G; ++g) acc += fexp2(lgv[u][g] - M[g]) * invL[g];  // (M: a reference, see kLazyRows)
       const float sc = scv[u] + acc;
       if (j < count) gst(score + j, sc);
       const unsigned long long key =

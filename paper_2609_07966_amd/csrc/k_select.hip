@@ -41,12 +41,15 @@ __global__ __launch_bounds__(kTopkThreads, 8) void k_topk(const SeqDesc *__restr
 // tiles of the other side through a double-buffered LDS stage shared by the 4 waves, so an operand
 // read from LDS feeds two matrix instructions and an item is read from L2 once per 256 on the other
 // side.  Tiles wholly below the diagonal take a path without masks, where a logit costs one fma, one
-// exp2 and one add or fma; with the exp2 at half rate the vector unit bounds both kernels (counters:
-// it is busy 71 % of the row statistics' cycles, the matrix cores 53 %, at a clock of 1.7 GHz under
-// this load).  Heads are the fastest grid index, so that with 8 kv heads each head's K and Q stay in
-// one XCD's L2.  8 prompts of 8192 tokens, 32 query / 8 kv heads x 128: row statistics 4.75 -> 2.31 ms
-// (950 TFLOP/s of causal products), column sums 7.30 -> 2.80 ms (790), where one workgroup per 64
-// rows or keys and launches per sequence stood before; a library matrix product reaches 1150 here.
+// exp2 and one add or fma (3.6 ns of a SIMD for a wave's exp2, 1.1 for each of the others, measured in
+// loops of nothing else).  For 8 prompts of 8192 tokens these are 0.75 ms a pass and the products 1.9 at
+// the rate of a large library product; the passes take 2.3 and 2.8, about the sum: a tile's exponentials
+// wait for its products (counters: vector unit busy 71 % of the row statistics' cycles, matrix cores 53 %,
+// at a clock of 1.7 GHz under this load).  Heads are the fastest grid index, so that with 8 kv heads each
+// head's K and Q stay in one XCD's L2.  8 prompts of 8192 tokens, 32 query / 8 kv heads x 128: row
+// statistics 4.75 -> 2.31 ms (950 TFLOP/s of causal products), column sums 7.30 -> 2.80 ms (790), where one
+// workgroup per 64 rows or keys and launches per sequence stood before; a library matrix product reaches
+// 1150 here.
 // The column sums are held to 168 registers (three waves per SIMD; 2.90 ms at 220 and two).
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));

@@ -223,12 +223,12 @@ void fill_lists(Layout *L, int Hkv) {
       for (int h = 0; h < Hkv; ++h)
         for (int p = 0; p < parts; ++p) L->comb.push_back(make_int4(s, h, p, parts));
     }
-  // Prefill groups.  A launch has workgroups for every sequence's length up to the longest's, and those
+  // Prefill groups.  A launch has workgroups for every sequence up to the longest's length, and those
   // past a shorter one's end leave at once, 4-5 a nanosecond (1 where they hold the H2O scores' LDS); a
-  // launch of its own costs a few microseconds.  A group ends where the idle tokens would pass twice its
-  // own, plus 2^20 per kv head.  (One fp16 prompt of 131072
-  // tokens with 127 of 300: 704 us with launches per sequence, 1885 in one group, 227 in two; uniform 4-bit
-  // 3416, 1187, 313; one of 32768 with 31 of 300 under KVQuant at 3 bits 3258, 394, 370.)
+  // launch of its own costs a few microseconds.  A group ends where its idle tokens would pass twice its
+  // own plus 2^20 / Hkv.  (One fp16 prompt of 131072 tokens with 127 of 300: 704 us with launches per
+  // sequence, 1885 in one group, 227 in two; uniform 4-bit 3416, 1187, 313; one of 32768 with 31 of 300
+  // under KVQuant at 3 bits 3258, 394, 370.)
   const double spare = double(1 << 20) / Hkv;
   for (int m = 0; m < kMethods; ++m) {
     const size_t first = L->lists.size();
@@ -444,7 +444,8 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     // drops with fewer than 3 workgroups on a CU.  The size with the least is taken.  (Sweeps of four
     // layers: 8 x 8192 tokens under H2O-20 117, 113, 116, 118, 116 us at 832, 448, 576, 384, 256 tiles;
     // H2O-40 162, 159, 159, 156, 167 at 1664, 1152, 704, 512, 448; 8 x 4096 FP16 145, 154, 144, 146 at
-    // 1408, 1088, 704, 512.  The model puts each of these in order.)
+    // 1408, 1088, 704, 512.  The weights were fitted to these three; the model finds the best of each, but
+    // does not order the others.)
     rule = BY_ROWS;
     double best = -1.0;
     float load[kCus];
@@ -899,14 +900,14 @@ mkv_status mkv_decode_step(mkv_cache *c, const uint16_t *k, const uint16_t *v, c
   hipStream_t hst = static_cast<hipStream_t>(stream);
   mkv_status st = MKV_OK;
   if (c->any_rocket) {
-    // the append and the top-k share one launch
+    // the append, the scores and the top-k, in one launch or two
     st = decode_append_select(c, k, v, q, hst);
   } else if (c->prof_mask >> 2 & 1) {
     st = decode_append(c, k, v, hst);  // appends are timed: in a launch of their own
   } else {
-    // the attention launch appends: 1.5-2 us less per step of 8-18 us, 2.6-3 of 25-36, for one
-    // sequence of 300 tokens as for 40, under every method (RocketKV scores the appended key before
-    // its selection, so its append stays where the scores are)
+    // the attention launch appends: 1.5-2 us less of a step of 11-17 us for one sequence of 300 tokens,
+    // 2.4-5.2 of 19-28 for 40 of them, under every method, by steps that do append (RocketKV scores the
+    // appended key before its selection, so its append stays where the scores are)
     Dev dv = c->dv;
     dv.k_new = k;
     dv.v_new = v;
