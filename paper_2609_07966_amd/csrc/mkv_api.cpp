@@ -479,10 +479,15 @@ mkv_status make_layout(const mkv_shape *shp, const mkv_config *cfg, const int32_
     // One round: quantized tiles alone, bound by the latency of their batches, are best all resident at once
     // (8 x 8192 tokens, three layers: uniform 4-bit 93 us at 704 tiles of 768 tokens against 105 at
     // 1408 of 384, KVQ at 4 bits 144 against 156; 16 ragged sequences of three kinds, two layers, 101
-    // against 116): the smallest size that allows it, by time, up to 8 times the default.
-    if (!long_launch && n_quant == S) {
-      const double c = smallest(4096.0, 8 * tile_bytes, 1.03, kTileSlots, by_time);
-      if (count_at(c, by_time) <= kTileSlots) {
+    // against 116): the smallest size that allows it, by time, up to 8 times the default.  The kernel for
+    // groups of 8 heads of 128 takes 184 registers, which leaves room for 2 workgroups on a CU: KVQuant at 2
+    // bits, 48 x 640-800 tokens, 2 kv heads, two layers, 48.0 us with 314 tiles, 58.0 with 602 (and 50.1
+    // with 410 of the general rule).  Where no size has so few, as with more pairs than that, 3 on a CU.
+    const int resident = D == 128 && G == 8 ? 2 * kCus : kTileSlots;
+    for (const int slots : {resident, kTileSlots}) {
+      if (long_launch || n_quant < S || rule == BY_TIME) break;
+      const double c = smallest(4096.0, 8 * tile_bytes, 1.03, slots, by_time);
+      if (count_at(c, by_time) <= slots) {
         tile_bytes = c;
         rule = BY_TIME;
       }

@@ -195,6 +195,14 @@ int main() {
     const int tiles = check_tiles(mkv_shape{9, 64, 8, 128, 5}, cs, std::vector<int32_t>(9, len));
     CHECK((size_t)tiles * 8 * 130 * sizeof(float) <= mkv::kStaticScratchBytes);
   }
+  // quantized sequences alone: one round of resident workgroups, 3 on a CU, 2 for groups of 8 heads of 128
+  for (int g : {4, 8})
+    for (int S : {16, 48, 96})
+      for (int b : {2, 3, 4}) {
+        std::vector<mkv_config> cs(S, cfg(MKV_KVQ, b, 100));
+        const int tiles = check_tiles(mkv_shape{S, 2 * g, 2, 128, 4}, cs, std::vector<int32_t>(S, 40000 / S));
+        CHECK(tiles <= (g == 8 ? 512 : 768));
+      }
   // uniform 4-bit tiles of d = 64 in short launches: 64 tokens or more for each of a workgroup's 4 waves
   for (int S : {1, 3, 8})
     for (int with : {MKV_UQ, MKV_FP16, MKV_KVQ})
